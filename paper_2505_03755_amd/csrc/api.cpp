@@ -119,6 +119,7 @@ struct Plan {
 // Offsets of the workspace pieces of each operation.
 struct StepPlan {
   size_t ccat, xo, xa, kpart, vtmp, vpart, bpu, buv;
+  int64_t kpart_n;   // doubles at kpart: the K partials, and before them the Coulomb build's
   int nsplit;
 };
 
@@ -197,7 +198,8 @@ StepPlan plan_step(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t na
   p.xo = pl.take(caller_x ? 0 : naux * nao * nocc);
   p.xa = pl.take(caller_x ? 0 : naux * nao * nac);
   p.nsplit = dfk::syrk_splits(nao, naux, 1);
-  p.kpart = pl.take((int64_t)p.nsplit * nao * nao);
+  p.kpart_n = std::max((int64_t)p.nsplit * nao * nao, dfk::coulomb_part(naux, nao, 1));
+  p.kpart = pl.take(p.kpart_n);
   p.vtmp = pl.take(naux);
   p.vpart = pl.take(nocc > 0 ? naux * dfk::half_tiles(nao, ncol) : 0);
   p.bpu = pl.take(naux * np * nac);
@@ -212,10 +214,14 @@ StepPlan plan_step(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t na
 // can take, so the total grows with the chunk.
 struct BwdPlan {
   size_t ccat, xo, xa, g, u, upart, M, S, Y, kpart, Gs, buv, Z, apart;
+  size_t jpart;      // the Coulomb part's partial sums: the pieces from S on, which it runs before
+  int64_t jpart_n;   // doubles there
   int64_t chunk;
 };
 
-BwdPlan plan_backward(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t nac, int flags, int64_t chunk) {
+// `bounded`: under a scratch limit the Coulomb partials take only what the other pieces leave them.
+BwdPlan plan_backward(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t nac, int flags, int64_t chunk,
+                      bool bounded) {
   BwdPlan p{};
   const bool gj = flags & DF_BWD_GJ, gk = flags & DF_BWD_GK, ge = flags & DF_BWD_GERI;
   const bool cx = flags & DF_CALLER_X;
@@ -230,6 +236,7 @@ BwdPlan plan_backward(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t
   p.u = pl.take(gj && nocc > 0 ? naux : 0);
   p.upart = pl.take(gj && nocc > 0 ? (int64_t)dfk::jvec_packed_chunks() * naux : 0);
   p.M = pl.take(gj && nocc > 0 ? nao * nao : 0);
+  p.jpart = pl.total;
   p.S = pl.take(do_k ? nao * nao : 0);
   p.Y = pl.take(do_k ? ch * dfk::kpad16(nao) * nocc : 0);
   p.kpart = pl.take(do_k ? dfk::half_reduce_part_bound(nao, nocc, ch) : 0);
@@ -237,6 +244,9 @@ BwdPlan plan_backward(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t
   p.buv = pl.take(do_e ? ch * nac * nac : 0);
   p.Z = pl.take(do_e ? ch * nac * nac : 0);
   p.apart = pl.take(do_e ? (int64_t)dfk::gemm_splits_bound(nao, nac, (ch * nac + 15) / 16) * nao * nac : 0);
+  if (gj && nocc > 0 && !bounded)
+    pl.total = std::max(pl.total, p.jpart + align_up((size_t)dfk::coulomb_part(naux, nao, 1) * sizeof(double)));
+  p.jpart_n = (int64_t)((pl.total - p.jpart) / sizeof(double));
   return p;
 }
 
@@ -247,7 +257,7 @@ int64_t backward_rows(int64_t naux, int64_t nao, int64_t nocc, int64_t nac, int 
   if (limit == 0) return naux;
   auto need = [&](int64_t ch) {
     Plan pl;
-    plan_backward(pl, naux, nao, nocc, nac, flags, ch);
+    plan_backward(pl, naux, nao, nocc, nac, flags, ch, true);
     return pl.total;
   };
   if (need(1) > limit) return 0;
@@ -328,6 +338,7 @@ struct JkPlan {
   size_t ccat, x, kpart, vtmp, xw;
   SplitBuf cs, xos, xws;
   int64_t xplane;   // bytes of the planes of one density's X_occ
+  int64_t kpart_n;  // doubles at kpart: the K partials, and before them the Coulomb build's
   int nsplit;
 };
 // nsplit_fp64 > 0 sizes the FP64 K partials for that many splits instead of the call's own count.
@@ -353,7 +364,9 @@ JkPlan plan_jk(Plan& pl, int64_t naux, int64_t nao, int64_t ndm, int64_t nocc, b
                                        dfk::slice_gemm_steps(dfk::kpad64(naux * nocc)))
                         : 1;
   }
-  p.kpart = pl.take((int64_t)p.nsplit * ndm * nao * nao);
+  p.kpart_n = (int64_t)p.nsplit * ndm * nao * nao;
+  if (nsplit_fp64 == 0) p.kpart_n = std::max(p.kpart_n, dfk::coulomb_part(naux, nao, ndm));
+  p.kpart = pl.take(p.kpart_n);
   return p;
 }
 
@@ -457,6 +470,7 @@ SplitMmPlan plan_split_mm(Plan& pl, int64_t M, int64_t N, int64_t K, int nslice)
 struct StepSplitPlan {
   size_t ccat, xo, xa, bpu, buv, kpart, vtmp;
   SplitBuf cs, xos, xas, cps, cas, bpus, buvs;
+  int64_t kpart_n;   // doubles at kpart: the K partials, and before them the Coulomb build's
   int nsk;
 };
 StepSplitPlan plan_step_split(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t nac, int64_t np,
@@ -471,7 +485,8 @@ StepSplitPlan plan_step_split(Plan& pl, int64_t naux, int64_t nao, int64_t nocc,
   p.cs = take_split(pl, ncol, nao, nslice);
   p.xos = take_split(pl, nocc > 0 ? nao : 0, naux * nocc, nslice);
   p.nsk = slice_splits(dfk::slice_gemm_tiles(nao, nao, true), dfk::slice_gemm_steps(dfk::kpad64(naux * nocc)));
-  p.kpart = pl.take(nocc > 0 ? (int64_t)p.nsk * nao * nao : 0);
+  p.kpart_n = nocc > 0 ? std::max((int64_t)p.nsk * nao * nao, dfk::coulomb_part(naux, nao, 1)) : 0;
+  p.kpart = pl.take(p.kpart_n);
   p.vtmp = pl.take(naux);
   p.xas = take_split(pl, naux * nac, nao, nslice);
   p.cps = take_split(pl, nac > 0 ? np : 0, nao, nslice);
@@ -492,7 +507,7 @@ struct BwdSplitPlan {
 BwdSplitPlan plan_backward_split(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t nac, int flags,
                                  int nslice) {
   BwdSplitPlan p{};
-  p.f = plan_backward(pl, naux, nao, nocc, nac, (flags & ~DF_BWD_GK) | DF_CALLER_X, naux);
+  p.f = plan_backward(pl, naux, nao, nocc, nac, (flags & ~DF_BWD_GK) | DF_CALLER_X, naux, false);
   p.nsk = 1;
   if ((flags & DF_BWD_GK) && nocc > 0) {
     p.S = pl.take(nao * nao);
@@ -507,6 +522,7 @@ BwdSplitPlan plan_backward_split(Plan& pl, int64_t naux, int64_t nao, int64_t no
 // ---- batched problems ----
 struct BatchedPiece {
   size_t cpad, xo, xa, v, jp, kpart, buv, bpu, dfull, dw, vpart;
+  int64_t jp_n;   // doubles at jp: packed J of many densities, or the Coulomb build's partial sums
   int nsplit, vsplit;
 };
 int64_t batched_ncol(const df_problem& q) { return q.ndm * q.nocc + q.nac; }
@@ -711,6 +727,12 @@ bool tune_write(const df_ctx* c, const std::string& path, std::string* err) {
 // J of many densities as one product: Jp[z][pair] = sum_P v[z][P] b^P[pair] (then unpacked)
 bool batched_j_gemm(const df_problem& q) { return q.ndm > 4; }
 
+// Doubles of a problem's J scratch: its packed J, or the partial sums of the Coulomb build.
+int64_t batched_jp(const df_problem& q) {
+  if (!q.J || q.nocc <= 0) return 0;
+  return batched_j_gemm(q) ? q.ndm * q.nao * (q.nao + 1) / 2 : dfk::coulomb_part(q.naux, q.nao, q.ndm);
+}
+
 // The J-vectors from packed B and the packed densities (v = Dw B^T) instead of from X_occ, when
 // X_occ (naux nao ndm nocc) is the larger of the two to read (B: naux npair).
 bool batched_jvec_from_b(const df_problem& q) { return q.J && q.nocc > 0 && 2 * q.ndm * q.nocc > q.nao + 1; }
@@ -732,7 +754,8 @@ std::vector<BatchedPiece> plan_batched(Plan& pl, const df_problem* probs, int n)
     b.dw = pl.take(batched_jvec_from_b(q) ? q.ndm * npair : 0);
     b.vsplit = batched_jvec_from_b(q) ? dfk::gemm_splits(q.ndm, q.naux, (npair + 15) / 16) : 1;
     b.vpart = pl.take(b.vsplit > 1 ? (int64_t)b.vsplit * q.ndm * q.naux : 0);
-    b.jp = pl.take(q.J && q.nocc > 0 && batched_j_gemm(q) ? q.ndm * q.nao * (q.nao + 1) / 2 : 0);
+    b.jp_n = batched_jp(q);
+    b.jp = pl.take(b.jp_n);
     b.nsplit = ks[(size_t)i];
     b.kpart = pl.take(q.K && q.nocc > 0 ? (int64_t)b.nsplit * q.ndm * q.nao * q.nao : 0);
     b.buv = pl.take(q.eri && q.nac > 0 ? q.naux * q.nac * q.nac : 0);
@@ -745,6 +768,7 @@ std::vector<BatchedPiece> plan_batched(Plan& pl, const df_problem* probs, int n)
 // one region, sized for the largest).
 struct SplitPiece {
   size_t cc, xo, xa, v, jp, dfull, dw, vpart, kpart, buv, bpu;
+  int64_t jp_n;     // as in BatchedPiece
   SplitBuf cs, xos, xas, cas, cps, buvs, bpus;
   int64_t xplane;   // bytes of the planes of one density's X_occ
   int vsplit, nsk;
@@ -760,7 +784,8 @@ SplitPiece plan_split_piece(Plan& pl, const df_problem& q, int nslice, bool k_fp
   b.xo = pl.take(need_x ? q.naux * q.nao * no : 0);          // P-major [naux][nao][ndm*nocc]
   b.xa = pl.take(need_x ? q.naux * q.nao * q.nac : 0);      // AO-major [nao][naux][nac]
   b.v = pl.take(dj ? q.ndm * q.naux : 0);
-  b.jp = pl.take(dj && batched_j_gemm(q) ? q.ndm * npair : 0);
+  b.jp_n = batched_jp(q);
+  b.jp = pl.take(b.jp_n);
   b.dfull = pl.take(batched_jvec_from_b(q) ? q.ndm * q.nao * q.nao : 0);
   b.dw = pl.take(batched_jvec_from_b(q) ? q.ndm * npair : 0);
   b.vsplit = batched_jvec_from_b(q) ? dfk::gemm_splits(q.ndm, q.naux, (npair + 15) / 16) : 1;
@@ -1184,7 +1209,7 @@ df_status workspace_bytes(df_op op, const df_dims* d, size_t limit, size_t* byte
     case DF_OP_STEP_BACKWARD: {
       const int64_t rows = backward_rows(d->naux, d->nao, d->nocc, d->nac, d->flags, limit);
       if (rows == 0) return DF_ERR_WORKSPACE;
-      plan_backward(pl, d->naux, d->nao, d->nocc, d->nac, d->flags, rows);
+      plan_backward(pl, d->naux, d->nao, d->nocc, d->nac, d->flags, rows, limit != 0);
       break;
     }
     case DF_OP_STEP_SPLIT:
@@ -1373,7 +1398,8 @@ static df_status jk_run(df_ctx* c, char* ws, const JkPlan& p, const double* B, i
     DF_LAUNCH(DF_KERNEL_JVEC, dfk::launch_jvec(X, naux, nao, ncol, Cocc, w, nocc, ndm, vv, c->stream, 0, ldvv),
               "J-vector launch");
     if (J)
-      DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(B, naux, nao, vv, ndm, J, c->stream, acc_jk, ldvv),
+      DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(B, naux, nao, vv, ndm, J, (double*)(ws + p.kpart), p.kpart_n, c->stream, acc_jk,
+                                    ldvv),
                 "Coulomb launch");
     if (v && acc_v)
       DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_copy_rows(vv, ndm, naux, v, ldv, 1, c->stream), "add launch");
@@ -1931,7 +1957,8 @@ df_status df_step(df_ctx* ctx, const double* B, int64_t naux, int64_t nao, const
   else if (df_status s = run_half(c, B, naux, nao, cc, ncol, ox))
     return s;
   if (nocc > 0) {
-    if (J) DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(B, naux, nao, vv, 1, J, c->stream), "Coulomb launch");
+    if (J) DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(B, naux, nao, vv, 1, J, (double*)(c->ws + p.kpart), p.kpart_n,
+                                                       c->stream), "Coulomb launch");
     if (K)
       if (df_status s = run_k(c, Xo, w, naux, nao, nocc, nocc, 1, p.nsplit, (double*)(c->ws + p.kpart), K))
         return s;
@@ -1959,7 +1986,8 @@ static df_status bwd_coulomb(df_ctx* c, char* ws, const BwdPlan& p, const double
   DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_pair_weights(gJ, nao, g, c->stream), "pair weights");
   DF_LAUNCH(DF_KERNEL_JVEC, dfk::launch_jvec_packed(B, naux, nao, g, (double*)(ws + p.upart), u, c->stream),
             "J-vector launch");
-  DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(B, naux, nao, u, 1, M, c->stream), "Coulomb launch");
+  DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(B, naux, nao, u, 1, M, (double*)(ws + p.jpart), p.jpart_n, c->stream),
+            "Coulomb launch");
   const dfk::OpMap A = dfk::op_map(M, nao, nao, nao, 1);
   const dfk::OpMap Bm = dfk::op_map(Cocc, nocc, 1, nao, nocc);
   dfk::OutMap O = dfk::out_plain(dCocc, nao, nocc, nocc);
@@ -2032,7 +2060,7 @@ df_status df_step_backward(df_ctx* ctx, const double* B, int64_t naux, int64_t n
     return fail(c, DF_ERR_WORKSPACE, "the scratch limit of " + std::to_string(c->scratch_limit) +
                                          " bytes is below the workspace of one auxiliary row");
   Plan pl;
-  const BwdPlan p = plan_backward(pl, naux, nao, nocc, nac, pflags, rows);
+  const BwdPlan p = plan_backward(pl, naux, nao, nocc, nac, pflags, rows, c->scratch_limit != 0);
   if (!check_overlap(c, rs)) return DF_ERR_ARG;
   if (df_status s = need_ws(c, pl.total)) return s;
   if (pl.total) rs.push_back({c->ws, pl.total, "workspace", true});
@@ -2245,7 +2273,10 @@ df_status df_step_split(df_ctx* ctx, const double* B, const int8_t* Bs, const in
       double* vv = v ? v : (double*)(ws + p.vtmp);
       DF_LAUNCH(DF_KERNEL_JVEC, dfk::launch_jvec(Xo, naux, nao, nocc, Cocc, nullptr, nocc, 1, vv, c->stream),
                 "J-vector launch");
-      if (J) DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(B, naux, nao, vv, 1, J, c->stream), "Coulomb launch");
+      if (J)
+        DF_LAUNCH(DF_KERNEL_COULOMB,
+                  dfk::launch_coulomb(B, naux, nao, vv, 1, J, (double*)(ws + p.kpart), p.kpart_n, c->stream),
+                  "Coulomb launch");
     }
     // a5: K = sum_{P, c} X[P][i][c] X[P][j][c] from the split rows i of X_occ
     if (K) {
@@ -2488,7 +2519,7 @@ df_status df_batched_workspace_size(const df_problem* probs, int nprob, size_t* 
 // J (FP64) of problem q from its J-vectors: V B^T over the packed pairs for many densities, else
 // the Coulomb kernel.  v comes from X_occ (Xo) or, when that is the larger read, from packed B.
 static df_status batched_coulomb(df_ctx* c, const df_problem& q, const double* Xo, double* v, double* jp,
-                                 double* dfull, double* dw, int vsplit, double* vpart) {
+                                 int64_t jp_n, double* dfull, double* dw, int vsplit, double* vpart) {
   const int64_t npair = q.nao * (q.nao + 1) / 2;
   if (batched_jvec_from_b(q)) {
     DF_LAUNCH(DF_KERNEL_JVEC, dfk::launch_dens_pairs(q.Cocc, q.nao, q.nocc, q.ndm, dfull, dw, c->stream),
@@ -2510,7 +2541,8 @@ static df_status batched_coulomb(df_ctx* c, const df_problem& q, const double* X
               "Coulomb product launch");
     DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_unpack_sym(jp, q.ndm, q.nao, q.J, c->stream), "unpack launch");
   } else {
-    DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(q.B, q.naux, q.nao, v, q.ndm, q.J, c->stream), "Coulomb launch");
+    DF_LAUNCH(DF_KERNEL_COULOMB, dfk::launch_coulomb(q.B, q.naux, q.nao, v, q.ndm, q.J, jp, jp_n, c->stream),
+              "Coulomb launch");
   }
   return DF_OK;
 }
@@ -2700,7 +2732,7 @@ df_status df_batched_step(df_ctx* ctx, const df_problem* probs, int nprob, int f
     const double* Xo = (const double*)(ws + b.xo);
     const double* Xa = (const double*)(ws + b.xa);
     if (q.J && q.nocc > 0)
-      if (df_status s = batched_coulomb(c, q, Xo, (double*)(ws + b.v), (double*)(ws + b.jp), (double*)(ws + b.dfull),
+      if (df_status s = batched_coulomb(c, q, Xo, (double*)(ws + b.v), (double*)(ws + b.jp), b.jp_n, (double*)(ws + b.dfull),
                                         (double*)(ws + b.dw), b.vsplit, (double*)(ws + b.vpart)))
         return s;
     if (q.eri && q.nac > 0) {
@@ -2762,7 +2794,7 @@ static df_status split_problem_run(df_ctx* c, char* ws, const df_problem& q, con
                                    nullptr, c->stream),
             "slice product launch");
   if (q.J && q.nocc > 0)
-    if (df_status s = batched_coulomb(c, q, Xo, (double*)(ws + b.v), (double*)(ws + b.jp), (double*)(ws + b.dfull),
+    if (df_status s = batched_coulomb(c, q, Xo, (double*)(ws + b.v), (double*)(ws + b.jp), b.jp_n, (double*)(ws + b.dfull),
                                       (double*)(ws + b.dw), b.vsplit, (double*)(ws + b.vpart)))
       return s;
   if (q.K && q.nocc > 0 && k_fp64) {

@@ -127,9 +127,11 @@ hipError_t launch_jvec(const double* X, int64_t naux, int64_t nao, int64_t ldx, 
                        int64_t ldv = 0);
 
 // J[z][i][j] = sum_P v[z][P] b^P_{ij}, both triangles written (added to J when `accumulate`; v row
-// stride ldv, naux when 0).
-hipError_t launch_coulomb(const double* B, int64_t naux, int64_t nao, const double* v,
-                          int64_t nz, double* J, hipStream_t s, int accumulate = 0, int64_t ldv = 0);
+// stride ldv, naux when 0).  part: scratch of part_n doubles for the partial sums of a split over P
+// (coulomb_part() of them let it split as it wants; with fewer, or none, it splits less).
+int64_t coulomb_part(int64_t naux, int64_t nao, int64_t nz);
+hipError_t launch_coulomb(const double* B, int64_t naux, int64_t nao, const double* v, int64_t nz, double* J,
+                          double* part, int64_t part_n, hipStream_t s, int accumulate = 0, int64_t ldv = 0);
 // y[r][c] = x[r][c] (or += with `accumulate`) for x [rows][cols] contiguous, y of row stride ldy
 hipError_t launch_copy_rows(const double* x, int64_t rows, int64_t cols, double* y, int64_t ldy, int accumulate,
                             hipStream_t s);

@@ -22,6 +22,7 @@
 
 #include <math.h>
 
+#include <algorithm>
 #include <type_traits>
 #include <utility>
 
@@ -922,43 +923,68 @@ __global__ void __launch_bounds__(256) jvec_kernel(const double* __restrict__ X,
   }
 }
 
-// J[z][i][j] = sum_P v[z][P] b^P_{ij}, streaming B once.  A workgroup owns kCoulombPairs * 256
-// consecutive packed pairs (thread t the pairs t + 256 r) for every P, so each P row is read as
-// runs of 8 KB; v is staged through LDS in blocks of 256 P.
+// Row i and column j <= i of packed pair p = i(i+1)/2 + j.
+__device__ __forceinline__ void pair_ij(int64_t p, int64_t* i, int64_t* j) {
+  int64_t r = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
+  while (r * (r + 1) / 2 > p) --r;
+  while ((r + 1) * (r + 2) / 2 <= p) ++r;
+  *i = r;
+  *j = p - r * (r + 1) / 2;
+}
+
+// J[z][i][j] = sum_P v[z][P] b^P_{ij} for NZ densities, streaming B once.  Bound by HBM.  A workgroup
+// owns kCoulombPairs * 256 consecutive packed pairs (thread t the pairs t + 256 r), so each P row is
+// read as runs of 8 KB; v is staged through LDS in blocks of 256 P.  The pairs alone give 704
+// workgroups at N_ao = 1200 but 8 at 120, so the P range is split over grid y too (launch_coulomb):
+// partial sums go to part [split][z][npair] and coulomb_reduce_kernel adds them in split order.
 constexpr int kCoulombZ = 4;
 constexpr int kCoulombPairs = 4;
+template <int NZ>
 __global__ void __launch_bounds__(256) coulomb_kernel(const double* __restrict__ B, int64_t naux, int64_t nao,
-                                                      int64_t npair, const double* __restrict__ v, int nz,
-                                                      int64_t vstride, double* __restrict__ J, int64_t jstride,
-                                                      int accumulate) {
-  __shared__ double vs[kCoulombZ][256];
+                                                      int64_t npair, const double* __restrict__ v, int64_t vstride,
+                                                      double* __restrict__ J, int64_t jstride, int accumulate,
+                                                      double* __restrict__ part) {
+  __shared__ double vs[NZ][256];
   const int64_t p0 = (int64_t)blockIdx.x * (256 * kCoulombPairs) + threadIdx.x;
+  const int64_t Pb = naux * blockIdx.y / gridDim.y, Pe = naux * (blockIdx.y + 1) / gridDim.y;
   int64_t pc[kCoulombPairs];   // the pairs, clamped to the last one (read, never stored)
 #pragma unroll
   for (int r = 0; r < kCoulombPairs; ++r) pc[r] = p0 + 256 * r < npair ? p0 + 256 * r : npair - 1;
-  double acc[kCoulombPairs][kCoulombZ];
+  double acc[kCoulombPairs][NZ];
 #pragma unroll
   for (int r = 0; r < kCoulombPairs; ++r)
 #pragma unroll
-    for (int z = 0; z < kCoulombZ; ++z) acc[r][z] = 0.0;
-  for (int64_t P0 = 0; P0 < naux; P0 += 256) {
-    const int64_t cnt = naux - P0 < 256 ? naux - P0 : 256;
+    for (int z = 0; z < NZ; ++z) acc[r][z] = 0.0;
+  for (int64_t P0 = Pb; P0 < Pe; P0 += 256) {
+    const int cnt = (int)(Pe - P0 < 256 ? Pe - P0 : 256);
     __syncthreads();
-    for (int z = 0; z < nz; ++z) vs[z][threadIdx.x] = threadIdx.x < cnt ? v[z * vstride + P0 + threadIdx.x] : 0.0;
+#pragma unroll
+    for (int z = 0; z < NZ; ++z)
+      vs[z][threadIdx.x] = (int)threadIdx.x < cnt ? v[z * vstride + P0 + threadIdx.x] : 0.0;
     __syncthreads();
     const double* Bp = B + P0 * npair;
-#pragma unroll 2
-    for (int q = 0; q < cnt; ++q) {
-      double b[kCoulombPairs];
+    int q = 0;
+    for (; q + 4 <= cnt; q += 4) {   // 16 loads in flight per thread
+      double b[4][kCoulombPairs];
 #pragma unroll
-      for (int r = 0; r < kCoulombPairs; ++r) b[r] = Bp[(int64_t)q * npair + pc[r]];
+      for (int u = 0; u < 4; ++u)
 #pragma unroll
-      for (int z = 0; z < kCoulombZ; ++z) {
-        if (z < nz) {
-          const double w = vs[z][q];
+        for (int r = 0; r < kCoulombPairs; ++r) b[u][r] = Bp[(int64_t)(q + u) * npair + pc[r]];
 #pragma unroll
-          for (int r = 0; r < kCoulombPairs; ++r) acc[r][z] = fma(w, b[r], acc[r][z]);
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int z = 0; z < NZ; ++z) {
+          const double w = vs[z][q + u];
+#pragma unroll
+          for (int r = 0; r < kCoulombPairs; ++r) acc[r][z] = fma(w, b[u][r], acc[r][z]);
         }
+    }
+    for (; q < cnt; ++q) {
+#pragma unroll
+      for (int r = 0; r < kCoulombPairs; ++r) {
+        const double b = Bp[(int64_t)q * npair + pc[r]];
+#pragma unroll
+        for (int z = 0; z < NZ; ++z) acc[r][z] = fma(vs[z][q], b, acc[r][z]);
       }
     }
   }
@@ -966,16 +992,56 @@ __global__ void __launch_bounds__(256) coulomb_kernel(const double* __restrict__
   for (int r = 0; r < kCoulombPairs; ++r) {
     const int64_t p = p0 + 256 * r;
     if (p >= npair) break;
-    int64_t i = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
-    while (i * (i + 1) / 2 > p) --i;
-    while ((i + 1) * (i + 2) / 2 <= p) ++i;
-    const int64_t j = p - i * (i + 1) / 2;
-    for (int z = 0; z < nz; ++z) {
+    if (part) {
+#pragma unroll
+      for (int z = 0; z < NZ; ++z) part[((int64_t)blockIdx.y * NZ + z) * npair + p] = acc[r][z];
+      continue;
+    }
+    int64_t i, j;
+    pair_ij(p, &i, &j);
+#pragma unroll
+    for (int z = 0; z < NZ; ++z) {
       const double x = accumulate ? J[z * jstride + i * nao + j] + acc[r][z] : acc[r][z];   // J is symmetric
       J[z * jstride + i * nao + j] = x;
       J[z * jstride + j * nao + i] = x;
     }
   }
+}
+
+// Sum over s < nsplit of q[s * stride] by the kRedG threads of a column (thread y takes s = y, y +
+// kRedG, ...; then the kRedG partial sums in order): the same order for every launch.  Every thread
+// of the workgroup calls it; the sum is returned to the threads with y == 0.
+constexpr int kRedG = 8, kRedW = 32;   // threads per column, columns per workgroup
+__device__ __forceinline__ double split_sum(const double* q, int nsplit, int64_t stride, bool live) {
+  __shared__ double red[kRedG][kRedW];
+  const int x = threadIdx.x % kRedW, y = threadIdx.x / kRedW;
+  double s = 0.0;
+  if (live) {
+#pragma unroll 4
+    for (int sp = y; sp < nsplit; sp += kRedG) s += q[(int64_t)sp * stride];
+  }
+  red[y][x] = s;
+  __syncthreads();
+  double r = 0.0;
+  if (y == 0)
+#pragma unroll
+    for (int g = 0; g < kRedG; ++g) r += red[g][x];
+  return r;
+}
+
+// J[z][i][j] = J[z][j][i] = sum_s part[s][z][pair(i, j)] (+ J): kRedG threads per pair.
+__global__ void __launch_bounds__(kRedG* kRedW) coulomb_reduce_kernel(const double* __restrict__ part, int nsplit,
+                                                                      int64_t nao, int64_t npair,
+                                                                      double* __restrict__ J, int accumulate) {
+  const int64_t p = (int64_t)blockIdx.x * kRedW + threadIdx.x % kRedW, z = blockIdx.y, nz = gridDim.y;
+  const double s = split_sum(part + z * npair + p, nsplit, nz * npair, p < npair);
+  if (threadIdx.x >= kRedW || p >= npair) return;
+  int64_t i, j;
+  pair_ij(p, &i, &j);
+  double* Jz = J + z * nao * nao;
+  const double x = accumulate ? Jz[i * nao + j] + s : s;
+  Jz[i * nao + j] = x;
+  Jz[j * nao + i] = x;
 }
 
 __global__ void __launch_bounds__(256) add_kernel(const double* __restrict__ x, int64_t n, double* __restrict__ y) {
@@ -1899,17 +1965,48 @@ hipError_t launch_jvec(const double* X, int64_t naux, int64_t nao, int64_t ldx, 
   return hipGetLastError();
 }
 
+// P splits of a Coulomb build: enough workgroups to keep HBM busy (1024 with at least 4 rows of B
+// each; with one split N_ao = 120 had 8 workgroups).  None where the pairs alone give 512 (at 704,
+// N_ao = 1200, two splits read B no faster).  Unsplit against split: step at 120 x 480 583 -> 415 us,
+// J and K at 77 x 310 260 -> 157 us, two densities at 455 x 1822 8.21 -> 7.31 ms.
+static int coulomb_want(int64_t naux, int64_t nao) {
+  const int64_t bx = cdiv(nao * (nao + 1) / 2, 256 * kCoulombPairs);
+  if (bx >= 512) return 1;
+  return (int)std::max<int64_t>(1, std::min<int64_t>({cdiv(1024, bx), naux / 4, 128}));
+}
+
+int64_t coulomb_part(int64_t naux, int64_t nao, int64_t nz) {
+  const int64_t s = coulomb_want(naux, nao);
+  return s > 1 ? s * std::min<int64_t>(nz, kCoulombZ) * (nao * (nao + 1) / 2) : 0;
+}
+
 hipError_t launch_coulomb(const double* B, int64_t naux, int64_t nao, const double* v, int64_t nz, double* J,
-                          hipStream_t s, int accumulate, int64_t ldv) {
+                          double* part, int64_t part_n, hipStream_t s, int accumulate, int64_t ldv) {
   const int64_t npair = nao * (nao + 1) / 2;
   if (ldv == 0) ldv = naux;
   if (ldv < naux) return hipErrorInvalidValue;
   for (int64_t z0 = 0; z0 < nz; z0 += kCoulombZ) {
     const int nzc = (int)(nz - z0 < kCoulombZ ? nz - z0 : kCoulombZ);
-    coulomb_kernel<<<(unsigned)cdiv(npair, 256 * kCoulombPairs), 256, 0, s>>>(B, naux, nao, npair, v + z0 * ldv, nzc, ldv,
-                                                               J + z0 * nao * nao, nao * nao, accumulate);
+    const int64_t room = part ? part_n / (nzc * npair) : 0;
+    const int ns = (int)std::max<int64_t>(1, std::min<int64_t>(coulomb_want(naux, nao), room));
+    double* pt = ns > 1 ? part : nullptr;
+    const dim3 grid((unsigned)cdiv(npair, 256 * kCoulombPairs), (unsigned)ns);
+    const double* vz = v + z0 * ldv;
+    double* Jz = J + z0 * nao * nao;
+    switch (nzc) {
+      case 1: coulomb_kernel<1><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt); break;
+      case 2: coulomb_kernel<2><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt); break;
+      case 3: coulomb_kernel<3><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt); break;
+      default: coulomb_kernel<4><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt);
+    }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
+    if (pt) {
+      coulomb_reduce_kernel<<<dim3((unsigned)cdiv(npair, kRedW), (unsigned)nzc), kRedG * kRedW, 0, s>>>(
+          pt, ns, nao, npair, Jz, accumulate);
+      e = hipGetLastError();
+      if (e != hipSuccess) return e;
+    }
   }
   return hipSuccess;
 }
