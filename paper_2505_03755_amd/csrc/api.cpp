@@ -197,7 +197,7 @@ StepPlan plan_step(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t na
   p.ccat = pl.take(dfk::kpad16(nao) * ncol);
   p.xo = pl.take(caller_x ? 0 : naux * nao * nocc);
   p.xa = pl.take(caller_x ? 0 : naux * nao * nac);
-  p.nsplit = dfk::syrk_splits(nao, naux, 1);
+  p.nsplit = dfk::syrk_splits(nao, naux, nocc, 1);
   p.kpart_n = std::max((int64_t)p.nsplit * nao * nao, dfk::coulomb_part(naux, nao, 1));
   p.kpart = pl.take(p.kpart_n);
   p.vtmp = pl.take(naux);
@@ -351,7 +351,7 @@ JkPlan plan_jk(Plan& pl, int64_t naux, int64_t nao, int64_t ndm, int64_t nocc, b
   p.x = pl.take(naux * nao * ncol);
   p.vtmp = pl.take(ndm * naux);
   if (!sp) {
-    p.nsplit = nsplit_fp64 > 0 ? nsplit_fp64 : dfk::syrk_splits(nao, naux, ndm);
+    p.nsplit = nsplit_fp64 > 0 ? nsplit_fp64 : dfk::syrk_splits(nao, naux, nocc, ndm);
   } else {
     p.cs = take_split(pl, ncol, nao, nslice);
     p.xplane = nocc > 0 ? dfk::split_plane_bytes(nao, naux * nocc, nslice) : 0;
@@ -797,7 +797,7 @@ SplitPiece plan_split_piece(Plan& pl, const df_problem& q, int nslice, bool k_fp
   b.nsk = !dk ? 1
           : dks ? slice_splits(dfk::slice_gemm_tiles(q.nao, q.nao, true) * q.ndm,
                                dfk::slice_gemm_steps(dfk::kpad64(q.naux * q.nocc)))
-                : dfk::syrk_splits(q.nao, q.naux, q.ndm);
+                : dfk::syrk_splits(q.nao, q.naux, q.nocc, q.ndm);
   b.kpart = pl.take(dk ? (int64_t)b.nsk * q.ndm * q.nao * q.nao : 0);
   b.xas = take_split(pl, de || dp ? q.naux * q.nac : 0, q.nao, nslice);
   b.cas = take_split(pl, de ? q.nac : 0, q.nao, nslice);

@@ -107,8 +107,8 @@ hipError_t launch_symmetrize(const double* in, int64_t n, int64_t nz, double* ou
 // Lower-tile SYRK with a split over kb: Kpart[split][z][i][j] = sum_{kb in split, kc} A(i,(kb,kc)) Bw(j,(kb,kc))
 // for tile(i) >= tile(j) (Bw = A with an optional per-kc weight).  Kpart is dense [nsplit][nz][n][n];
 // syrk_splits() gives the number of splits the workspace is planned for.
-int syrk_splits(int64_t n, int64_t kb_n, int64_t nz);
-// The most splits syrk_splits(n, k, nz) gives for any k <= kb_n.
+int syrk_splits(int64_t n, int64_t kb_n, int64_t kc_n, int64_t nz);
+// The most splits syrk_splits(n, k, kc_n, nz) gives for any k <= kb_n.
 int syrk_splits_bound(int64_t n, int64_t kb_n, int64_t nz);
 // SYRK tile edge for an n x n result (64 up to n = 640, else 128); a group uses the edge of its
 // largest member.

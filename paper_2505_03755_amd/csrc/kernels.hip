@@ -470,14 +470,51 @@ __global__ void __launch_bounds__(CfgSq::NT) __attribute__((amdgpu_waves_per_eu(
     gemm_tile<CfgRowTail, AK, BK, false, false>(A, B, O, nband * CfgSq::BM, n0, 0, 1, 0, nullptr, smem);
 }
 
-// C(m, n) = alpha * sum_s part[s][m][n] (+ C), fixed order over s.
-__global__ void __launch_bounds__(256) split_reduce_kernel(const double* __restrict__ part, int nsplit, OutMap O) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t MN = O.M * O.N;
-  if (idx >= MN) return;
-  const int64_t m = idx / O.N, n = idx % O.N;
+// Row i and column j <= i of packed pair p = i(i+1)/2 + j.
+__device__ __forceinline__ void pair_ij(int64_t p, int64_t* i, int64_t* j) {
+  int64_t r = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
+  while (r * (r + 1) / 2 > p) --r;
+  while ((r + 1) * (r + 2) / 2 <= p) ++r;
+  *i = r;
+  *j = p - r * (r + 1) / 2;
+}
+
+// Sum over s < nsplit of q[s * stride] by the G threads of a column (thread y takes s = y, y + G,
+// ...; then the G partial sums in order): the same order for every launch.  256 threads, 256 / G
+// columns; every thread calls it, and the threads with y == 0 hold the sum.  Bound by latency when
+// the splits are many and the columns few (a thread per column took 123 us for 77 x 77 over 310
+// splits), so G = 8 from 8 splits on; below that the extra threads would find nothing to add.
+constexpr int kRedThreads = 256;
+template <int G>
+__device__ __forceinline__ double split_sum(const double* q, int nsplit, int64_t stride, bool live) {
+  constexpr int W = kRedThreads / G;
+  const int x = threadIdx.x % W, y = threadIdx.x / W;
   double s = 0.0;
-  for (int sp = 0; sp < nsplit; ++sp) s += part[(int64_t)sp * MN + idx];
+  if (live) {
+#pragma unroll 4
+    for (int sp = y; sp < nsplit; sp += G) s += q[(int64_t)sp * stride];
+  }
+  if constexpr (G == 1) return s;
+  __shared__ double red[G][W];
+  red[y][x] = s;
+  __syncthreads();
+  double r = 0.0;
+  if (y == 0)
+#pragma unroll
+    for (int g = 0; g < G; ++g) r += red[g][x];
+  return r;
+}
+static inline int red_group(int nsplit) { return nsplit >= 8 ? 8 : 1; }
+
+// C(m, n) = alpha * sum_s part[s][m][n] (+ C), fixed order over s.
+template <int G>
+__global__ void __launch_bounds__(kRedThreads) split_reduce_kernel(const double* __restrict__ part, int nsplit, OutMap O) {
+  constexpr int W = kRedThreads / G;
+  const int64_t idx = (int64_t)blockIdx.x * W + threadIdx.x % W;
+  const int64_t MN = O.M * O.N;
+  const double s = split_sum<G>(part + idx, nsplit, MN, idx < MN);
+  if (threadIdx.x >= W || idx >= MN) return;
+  const int64_t m = idx / O.N, n = idx % O.N;
   double* dst;
   if (n < O.nsplit) {
     dst = O.p + (m / O.ml) * O.s_mh + (m % O.ml) * O.s_ml + (n / O.nl) * O.s_nh + (n % O.nl) * O.s_nl;
@@ -573,17 +610,22 @@ __global__ void __launch_bounds__(C::NT) syrk_group_kernel(SyrkGroup g) {
                                    smem);
 }
 
-__global__ void __launch_bounds__(256) syrk_reduce_kernel(const double* __restrict__ Kpart, int nsplit,
-                                                          int64_t n, int64_t nz, double* __restrict__ K,
-                                                          int accumulate) {
-  const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t nn = n * n;
-  if (idx >= nn * nz) return;
-  const int64_t z = idx / nn, rem = idx % nn, i = rem / n, j = rem % n;
-  const int64_t a = i >= j ? i : j, b = i >= j ? j : i;   // the lower element, computed by the SYRK tiles
-  double s = 0.0;
-  for (int sp = 0; sp < nsplit; ++sp) s += Kpart[((int64_t)sp * nz + z) * nn + a * n + b];
-  K[idx] = accumulate ? K[idx] + s : s;
+// K[z][i][j] and K[z][j][i] (+)= sum_s Kpart[s][z][i][j] for the lower pairs i >= j, G threads each.
+template <int G>
+__global__ void __launch_bounds__(kRedThreads) syrk_reduce_kernel(const double* __restrict__ Kpart, int nsplit,
+                                                                  int64_t n, int64_t npair, double* __restrict__ K,
+                                                                  int accumulate) {
+  constexpr int W = kRedThreads / G;
+  const int64_t p = (int64_t)blockIdx.x * W + threadIdx.x % W, z = blockIdx.y, nz = gridDim.y, nn = n * n;
+  int64_t i = 0, j = 0;
+  if (p < npair) pair_ij(p, &i, &j);
+  const double s = split_sum<G>(Kpart + z * nn + i * n + j, nsplit, nz * nn, p < npair);
+  if (threadIdx.x >= W || p >= npair) return;
+  double* a = K + z * nn + i * n + j;
+  double* b = K + z * nn + j * n + i;
+  const double x = accumulate ? *a + s : s, y = accumulate ? *b + s : s;
+  *a = x;
+  *b = y;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -923,15 +965,6 @@ __global__ void __launch_bounds__(256) jvec_kernel(const double* __restrict__ X,
   }
 }
 
-// Row i and column j <= i of packed pair p = i(i+1)/2 + j.
-__device__ __forceinline__ void pair_ij(int64_t p, int64_t* i, int64_t* j) {
-  int64_t r = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
-  while (r * (r + 1) / 2 > p) --r;
-  while ((r + 1) * (r + 2) / 2 <= p) ++r;
-  *i = r;
-  *j = p - r * (r + 1) / 2;
-}
-
 // J[z][i][j] = sum_P v[z][P] b^P_{ij} for NZ densities, streaming B once.  Bound by HBM.  A workgroup
 // owns kCoulombPairs * 256 consecutive packed pairs (thread t the pairs t + 256 r), so each P row is
 // read as runs of 8 KB; v is staged through LDS in blocks of 256 P.  The pairs alone give 704
@@ -1008,34 +1041,15 @@ __global__ void __launch_bounds__(256) coulomb_kernel(const double* __restrict__
   }
 }
 
-// Sum over s < nsplit of q[s * stride] by the kRedG threads of a column (thread y takes s = y, y +
-// kRedG, ...; then the kRedG partial sums in order): the same order for every launch.  Every thread
-// of the workgroup calls it; the sum is returned to the threads with y == 0.
-constexpr int kRedG = 8, kRedW = 32;   // threads per column, columns per workgroup
-__device__ __forceinline__ double split_sum(const double* q, int nsplit, int64_t stride, bool live) {
-  __shared__ double red[kRedG][kRedW];
-  const int x = threadIdx.x % kRedW, y = threadIdx.x / kRedW;
-  double s = 0.0;
-  if (live) {
-#pragma unroll 4
-    for (int sp = y; sp < nsplit; sp += kRedG) s += q[(int64_t)sp * stride];
-  }
-  red[y][x] = s;
-  __syncthreads();
-  double r = 0.0;
-  if (y == 0)
-#pragma unroll
-    for (int g = 0; g < kRedG; ++g) r += red[g][x];
-  return r;
-}
-
-// J[z][i][j] = J[z][j][i] = sum_s part[s][z][pair(i, j)] (+ J): kRedG threads per pair.
-__global__ void __launch_bounds__(kRedG* kRedW) coulomb_reduce_kernel(const double* __restrict__ part, int nsplit,
-                                                                      int64_t nao, int64_t npair,
-                                                                      double* __restrict__ J, int accumulate) {
-  const int64_t p = (int64_t)blockIdx.x * kRedW + threadIdx.x % kRedW, z = blockIdx.y, nz = gridDim.y;
-  const double s = split_sum(part + z * npair + p, nsplit, nz * npair, p < npair);
-  if (threadIdx.x >= kRedW || p >= npair) return;
+// J[z][i][j] = J[z][j][i] = sum_s part[s][z][pair(i, j)] (+ J), G threads per pair.
+template <int G>
+__global__ void __launch_bounds__(kRedThreads) coulomb_reduce_kernel(const double* __restrict__ part, int nsplit,
+                                                                     int64_t nao, int64_t npair,
+                                                                     double* __restrict__ J, int accumulate) {
+  constexpr int W = kRedThreads / G;
+  const int64_t p = (int64_t)blockIdx.x * W + threadIdx.x % W, z = blockIdx.y, nz = gridDim.y;
+  const double s = split_sum<G>(part + z * npair + p, nsplit, nz * npair, p < npair);
+  if (threadIdx.x >= W || p >= npair) return;
   int64_t i, j;
   pair_ij(p, &i, &j);
   double* Jz = J + z * nao * nao;
@@ -1576,31 +1590,41 @@ int64_t gemm_slabs(const OpMap& A) { return A.kb_n * cdiv(A.kc_n, 16); }
 // for two workgroups per CU).  A launch of W equal workgroups takes ceil(W / kResident) rounds.
 static constexpr int64_t kResident = 512;
 
-// Split count s in [1, max_split] for a launch of tiles * s equal workgroups: the one that fills
-// its last round best, among counts that fill at least one round (when any does), the smaller
-// on ties (less partial-sum traffic).
-static int balanced_splits(int64_t tiles, int64_t max_split) {
+// Split count s in [1, max_split] for a launch of tiles * s equal workgroups over a contraction of
+// `slabs` 16-deep slabs: the one of least estimated time.  A workgroup takes its share of the slabs
+// plus about 4 for its prologue and epilogue, a slab `slab_us` with two workgroups on its CU (3.6 us
+// for a 128 x 128 tile: 64 MFMAs a wave); a last round that fills at most one workgroup per CU
+// takes 0.6 of a full one, and workgroups that start together do not end together: 0.2 of an item
+// more (K at 341 x 1365 took 492 us in one round of long items, 427 in four).  A split costs the write and the read of its partial sums (`out` doubles,
+// 4 TB/s) and, as soon as there is one, the reduction's launch (5 us).  Candidates fill whole rounds
+// of 256.  (Filling the rounds alone cut K at 77 x 310 into 310 splits of one P: 126 us of K against
+// 21 with this rule.)
+static int balanced_splits(int64_t tiles, int64_t max_split, int64_t slabs, int64_t out, double slab_us) {
   if (tiles <= 0) return 1;
-  if (max_split < 1) max_split = 1;
   if (max_split > 4096) max_split = 4096;
-  const int64_t s_fill = cdiv(kResident, tiles);
-  int64_t lo = s_fill <= max_split ? s_fill : max_split, hi = 4 * lo < max_split ? 4 * lo : max_split;
-  if (hi < lo) hi = lo;
-  int best = (int)lo;
-  double best_eff = -1.0;
-  for (int64_t sp = lo; sp <= hi; ++sp) {
-    const int64_t w = tiles * sp;
-    const double eff = (double)w / (double)(cdiv(w, kResident) * kResident);
-    if (eff > best_eff + 1e-9) {
-      best_eff = eff;
+  max_split = std::min(max_split, 4 * cdiv(kResident, tiles));
+  if (max_split <= 1 || slabs <= 1) return 1;
+  int best = 1;
+  double best_us = 0.0;
+  for (int64_t m = 0; m <= 32; ++m) {
+    int64_t sp = m == 0 ? 1 : 256 * m / tiles;
+    if (sp < 1) continue;
+    if (sp > max_split) sp = max_split;
+    const int64_t w = tiles * sp, full = w / kResident, rem = w % kResident;
+    const double rounds = (double)full + (rem == 0 ? 0.0 : rem <= kResident / 2 ? 0.6 : 1.0);
+    const double us = (rounds + 0.2) * (double)(cdiv(slabs, sp) + 4) * slab_us +
+                      (sp > 1 ? 5.0 + (double)sp * (double)out * 16.0 / 4.0e6 : 0.0);
+    if (m == 0 || us < best_us * (1.0 - 1e-9)) {
+      best_us = us;
       best = (int)sp;
     }
+    if (sp == max_split && m > 0) break;
   }
   return best;
 }
+static double slab_us(int64_t bm, int64_t bn) { return 3.6 * (double)(bm * bn) / 16384.0; }
 
-// balanced_splits(tiles, m) for any m <= max_split is at most this: its search runs over
-// [lo, 4 lo] with lo <= kResident / tiles rounded up, and never past max_split.
+// balanced_splits(tiles, m, ...) for any m <= max_split is at most this.
 static int balanced_splits_bound(int64_t tiles, int64_t max_split) {
   if (tiles <= 0 || max_split < 1) return 1;
   const int64_t b = 4 * cdiv(kResident, tiles);
@@ -1614,14 +1638,20 @@ int gemm_splits_bound(int64_t M, int64_t N, int64_t nslab) {
 
 int gemm_splits(int64_t M, int64_t N, int64_t nslab) {
   // at least four slabs per split; a tall tile takes the room of two resident workgroups
-  if (gemm_tall(M)) return balanced_splits(2 * cdiv(M, CfgTall::BM) * cdiv(N, CfgTall::BN), nslab / 4);
-  return balanced_splits(cdiv(M, CfgSq::BM) * cdiv(N, CfgSq::BN), nslab / 4);
+  if (gemm_tall(M))
+    return balanced_splits(2 * cdiv(M, CfgTall::BM) * cdiv(N, CfgTall::BN), nslab / 4, nslab, M * N,
+                           slab_us(CfgSq::BM, CfgSq::BN));
+  return balanced_splits(cdiv(M, CfgSq::BM) * cdiv(N, CfgSq::BN), nslab / 4, nslab, M * N,
+                         slab_us(CfgSq::BM, CfgSq::BN));
 }
 
 hipError_t launch_split_reduce(const double* part, int nsplit, const OutMap& O, hipStream_t s) {
   const int64_t MN = O.M * O.N;
   if (MN == 0) return hipSuccess;
-  split_reduce_kernel<<<(unsigned)cdiv(MN, 256), 256, 0, s>>>(part, nsplit, O);
+  const int g = red_group(nsplit);
+  const unsigned nb = (unsigned)cdiv(MN, kRedThreads / g);
+  if (g == 8) split_reduce_kernel<8><<<nb, kRedThreads, 0, s>>>(part, nsplit, O);
+  else split_reduce_kernel<1><<<nb, kRedThreads, 0, s>>>(part, nsplit, O);
   return hipGetLastError();
 }
 
@@ -1630,16 +1660,16 @@ hipError_t launch_gemm_split(const OpMap& A, const OpMap& Bm, const OutMap& O, i
   if (nsplit <= 1) return gemm_launch(A, Bm, O, 1, 1, nullptr, s);
   hipError_t e = gemm_launch(A, Bm, O, 1, nsplit, part, s);
   if (e != hipSuccess) return e;
-  const int64_t MN = O.M * O.N;
-  if (MN == 0) return hipSuccess;
-  split_reduce_kernel<<<(unsigned)cdiv(MN, 256), 256, 0, s>>>(part, nsplit, O);
-  return hipGetLastError();
+  return launch_split_reduce(part, nsplit, O, s);
 }
 
 // The P-summed packed product takes the half transform's tilings (half_scheme): each piece is a
 // launch of its own with its own P split (filling the resident workgroups) and its own partials
 // [splits][rows][cols], reduced into O piece by piece.
-static int half_reduce_seg_splits(const HalfSeg& g, int64_t naux) { return balanced_splits(half_seg_tiles(g), naux); }
+static int half_reduce_seg_splits(const HalfSeg& g, int64_t naux, int64_t nao) {
+  return balanced_splits(half_seg_tiles(g), naux, naux * cdiv(nao, 16), (g.r1 - g.r0) * (g.c1 - g.c0),
+                         slab_us(half_cfg_rows(g.cfg), half_cfg_cols(g.cfg)));
+}
 
 int64_t half_reduce_part_bound(int64_t nao, int64_t N, int64_t naux) {
   HalfSeg seg[3];
@@ -1674,7 +1704,7 @@ hipError_t launch_half_reduce(const double* B, int64_t naux, int64_t nao, const 
   const int n = half_scheme(nao, O.N, true, seg);
   for (int i = 0; i < n; ++i) {
     const HalfSeg& g = seg[i];
-    const int ns = half_reduce_seg_splits(g, naux);
+    const int ns = half_reduce_seg_splits(g, naux, nao);
     hipError_t e;
     switch (g.cfg) {
       case kH176: e = half_reduce_go<CfgH176>(B, naux, nao, Y, g, ns, part, s); break;
@@ -1691,8 +1721,7 @@ hipError_t launch_half_reduce(const double* B, int64_t naux, int64_t nao, const 
     if (Oc.p2) Oc.p2 += g.r0 * Oc.s2_m;
     Oc.M = g.r1 - g.r0;
     const int64_t MN = Oc.M * Oc.N;
-    split_reduce_kernel<<<(unsigned)cdiv(MN, 256), 256, 0, s>>>(part, ns, Oc);
-    e = hipGetLastError();
+    e = launch_split_reduce(part, ns, Oc, s);
     if (e != hipSuccess) return e;
     part += (int64_t)ns * MN;
   }
@@ -1746,9 +1775,10 @@ hipError_t launch_symmetrize(const double* in, int64_t n, int64_t nz, double* ou
 
 int syrk_tile_for(int64_t n) { return n <= 640 ? CfgSyrk64::BM : CfgSyrk::BM; }
 
-int syrk_splits(int64_t n, int64_t kb_n, int64_t nz) {
-  const int64_t T = cdiv(n, syrk_tile_for(n));
-  return balanced_splits(T * (T + 1) / 2 * (nz > 0 ? nz : 1), kb_n);
+int syrk_splits(int64_t n, int64_t kb_n, int64_t kc_n, int64_t nz) {
+  const int64_t tile = syrk_tile_for(n), T = cdiv(n, tile);
+  if (nz < 1) nz = 1;
+  return balanced_splits(T * (T + 1) / 2 * nz, kb_n, cdiv(kb_n * kc_n, 16), n * (n + 1) / 2 * nz, slab_us(tile, tile));
 }
 
 int syrk_splits_bound(int64_t n, int64_t kb_n, int64_t nz) {
@@ -1950,9 +1980,13 @@ hipError_t launch_syrk_group(const GroupSyrk* probs, int n, int tile, hipStream_
 
 hipError_t launch_syrk_reduce(const double* Kpart, int nsplit, int64_t n, int64_t nz, double* K, hipStream_t s,
                               int accumulate) {
-  const int64_t tot = n * n * nz;
-  if (tot == 0) return hipSuccess;
-  syrk_reduce_kernel<<<(unsigned)cdiv(tot, 256), 256, 0, s>>>(Kpart, nsplit, n, nz, K, accumulate);
+  const int64_t npair = n * (n + 1) / 2;
+  if (npair == 0 || nz == 0) return hipSuccess;
+  if (nz > 65535) return hipErrorInvalidValue;
+  const int g = red_group(nsplit);
+  const dim3 grid((unsigned)cdiv(npair, kRedThreads / g), (unsigned)nz);
+  if (g == 8) syrk_reduce_kernel<8><<<grid, kRedThreads, 0, s>>>(Kpart, nsplit, n, npair, K, accumulate);
+  else syrk_reduce_kernel<1><<<grid, kRedThreads, 0, s>>>(Kpart, nsplit, n, npair, K, accumulate);
   return hipGetLastError();
 }
 
@@ -2002,8 +2036,10 @@ hipError_t launch_coulomb(const double* B, int64_t naux, int64_t nao, const doub
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (pt) {
-      coulomb_reduce_kernel<<<dim3((unsigned)cdiv(npair, kRedW), (unsigned)nzc), kRedG * kRedW, 0, s>>>(
-          pt, ns, nao, npair, Jz, accumulate);
+      const int g = red_group(ns);
+      const dim3 rg((unsigned)cdiv(npair, kRedThreads / g), (unsigned)nzc);
+      if (g == 8) coulomb_reduce_kernel<8><<<rg, kRedThreads, 0, s>>>(pt, ns, nao, npair, Jz, accumulate);
+      else coulomb_reduce_kernel<1><<<rg, kRedThreads, 0, s>>>(pt, ns, nao, npair, Jz, accumulate);
       e = hipGetLastError();
       if (e != hipSuccess) return e;
     }
