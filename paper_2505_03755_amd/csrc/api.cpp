@@ -117,9 +117,39 @@ struct Plan {
 };
 
 // Offsets of the workspace pieces of each operation.
+// The active-space contractions (pu|vw) and (uv|wx): the operand [Cp | Cact], b^P over its rows
+// [naux][np + nac][nac], the packed pairs of b^P_uv [naux][nuv], and partial sums over P of the
+// products of the rows (pu) and (uv) with the packed pairs.
+struct ActivePlan {
+  size_t pcat, b, vp, part;
+};
+int64_t active_rows(int64_t np, int64_t nac) { return (np + nac) * nac; }
+// Rows of P per product: all of them unless their 32-bit offsets would not reach.
+int64_t active_block(int64_t naux, int64_t np, int64_t nac) {
+  return std::min(naux, std::max<int64_t>(1, ((int64_t(1) << 32) - 1) / std::max<int64_t>(active_rows(np, nac), 1) - 17));
+}
+int active_splits(int64_t naux, int64_t np, int64_t nac) {
+  return dfk::part_splits(active_rows(np, nac), nac * (nac + 1) / 2, (active_block(naux, np, nac) + 15) / 16);
+}
+int64_t active_part(int64_t naux, int64_t np, int64_t nac) {
+  if (nac == 0) return 0;
+  const int64_t pb = active_block(naux, np, nac), nblk = (naux + pb - 1) / pb;
+  return nblk * active_splits(naux, np, nac) * active_rows(np, nac) * (nac * (nac + 1) / 2);
+}
+// own_b: b in the workspace (else in a caller's buffer)
+ActivePlan plan_active(Plan& pl, int64_t naux, int64_t nao, int64_t np, int64_t nac, bool own_b, bool own_part) {
+  ActivePlan p{};
+  p.pcat = pl.take(np > 0 ? nao * (np + nac) : 0);
+  p.b = pl.take(own_b ? naux * active_rows(np, nac) : 0);
+  p.vp = pl.take(naux * (nac * (nac + 1) / 2));
+  p.part = pl.take(own_part ? active_part(naux, np, nac) : 0);
+  return p;
+}
+
 struct StepPlan {
-  size_t ccat, xo, xa, kpart, vtmp, vpart, bpu, buv;
-  int64_t kpart_n;   // doubles at kpart: the K partials, and before them the Coulomb build's
+  size_t ccat, xo, xa, kpart, vtmp, vpart;
+  ActivePlan act;    // its partial sums share kpart
+  int64_t kpart_n;   // doubles at kpart: the K partials, before them the Coulomb build's, after them the active ones
   int nsplit;
 };
 
@@ -198,12 +228,12 @@ StepPlan plan_step(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t na
   p.xo = pl.take(caller_x ? 0 : naux * nao * nocc);
   p.xa = pl.take(caller_x ? 0 : naux * nao * nac);
   p.nsplit = dfk::syrk_splits(nao, naux, nocc, 1);
-  p.kpart_n = std::max((int64_t)p.nsplit * nao * nao, dfk::coulomb_part(naux, nao, 1));
+  p.kpart_n = std::max({(int64_t)p.nsplit * nao * nao, dfk::coulomb_part(naux, nao, 1), active_part(naux, np, nac),
+                        active_part(naux, 0, nac)});
   p.kpart = pl.take(p.kpart_n);
   p.vtmp = pl.take(naux);
   p.vpart = pl.take(nocc > 0 ? naux * dfk::half_tiles(nao, ncol) : 0);
-  p.bpu = pl.take(naux * np * nac);
-  p.buv = pl.take(naux * nac * nac);
+  p.act = plan_active(pl, naux, nao, np, nac, true, false);
   return p;
 }
 
@@ -409,6 +439,7 @@ int64_t noalloc_jk_rows(int64_t naux, int64_t nao, int64_t ndm, int64_t nocc, bo
 // of Cact, of the rows (P, u) of X_act and of the rows uv of b_uv over P.
 struct ActPlan {
   size_t cpad, x, buv;
+  ActivePlan act;
   SplitBuf cas, xas, buvs;
 };
 ActPlan plan_act(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int flags, int nslice) {
@@ -417,6 +448,7 @@ ActPlan plan_act(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int flags, in
   p.cpad = pl.take(sp ? 0 : dfk::kpad16(nao) * nac);
   p.x = pl.take(naux * nao * nac);
   p.buv = pl.take(naux * nac * nac);
+  if (!sp) p.act = plan_active(pl, naux, nao, 0, nac, false, true);
   if (sp) {
     p.cas = take_split(pl, nac, nao, nslice);
     p.xas = take_split(pl, naux * nac, nao, nslice);
@@ -430,6 +462,7 @@ ActPlan plan_act(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int flags, in
 // over P.
 struct PapaPlan {
   size_t cpad, x, bpu, bvw, bqv;
+  ActivePlan act;   // the default form in FP64
   SplitBuf cas, cps, cqs, xas, bpus, bvws, bqvs;
 };
 PapaPlan plan_papa(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int64_t np, int64_t nq, int flags, int nslice) {
@@ -437,8 +470,10 @@ PapaPlan plan_papa(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int64_t np,
   const bool full = flags & DF_PAPA_FULL, sp = flags & DF_PREC_SPLIT;
   p.cpad = pl.take(sp ? 0 : dfk::kpad16(nao) * nac);
   p.x = pl.take(naux * nao * nac);
-  p.bpu = pl.take(naux * np * nac);
-  p.bvw = pl.take(full ? 0 : naux * nac * nac);
+  const bool packed = !full && !sp;
+  p.bpu = pl.take(packed ? 0 : naux * np * nac);
+  p.bvw = pl.take(full || packed ? 0 : naux * nac * nac);
+  if (packed) p.act = plan_active(pl, naux, nao, np, nac, true, true);
   p.bqv = pl.take(full ? naux * nq * nac : 0);
   if (sp) {
     p.xas = take_split(pl, naux * nac, nao, nslice);
@@ -521,7 +556,8 @@ BwdSplitPlan plan_backward_split(Plan& pl, int64_t naux, int64_t nao, int64_t no
 
 // ---- batched problems ----
 struct BatchedPiece {
-  size_t cpad, xo, xa, v, jp, kpart, buv, bpu, dfull, dw, vpart;
+  size_t cpad, xo, xa, v, jp, kpart, bpu, dfull, dw, vpart;
+  ActivePlan act;   // (uv|wx)
   int64_t jp_n;   // doubles at jp: packed J of many densities, or the Coulomb build's partial sums
   int nsplit, vsplit;
 };
@@ -758,7 +794,7 @@ std::vector<BatchedPiece> plan_batched(Plan& pl, const df_problem* probs, int n)
     b.jp = pl.take(b.jp_n);
     b.nsplit = ks[(size_t)i];
     b.kpart = pl.take(q.K && q.nocc > 0 ? (int64_t)b.nsplit * q.ndm * q.nao * q.nao : 0);
-    b.buv = pl.take(q.eri && q.nac > 0 ? q.naux * q.nac * q.nac : 0);
+    if (q.eri && q.nac > 0) b.act = plan_active(pl, q.naux, q.nao, 0, q.nac, true, true);
     b.bpu = pl.take(q.papa && q.nac > 0 && q.np > 0 ? q.naux * q.np * q.nac : 0);
   }
   return v;
@@ -997,6 +1033,44 @@ df_status run_pgemm(df_ctx* c, int kind, const double* L, int64_t M, const doubl
   dfk::OutMap O = dfk::out_plain(out, M, N, N);
   O.accumulate = accumulate;
   DF_LAUNCH(kind, dfk::launch_gemm(A, Bm, O, 1, c->stream), "aux contraction launch");
+  return DF_OK;
+}
+
+// (pu|vw) into papa [np][nac][nac][nac] and (uv|wx) into eri [nac]^4 (null: not formed) from Xa
+// AO-major [nao][naux][nac].  b^P over the rows of [Cp | Cact] (b: [naux][np + nac][nac]; np = 0 without
+// papa) comes from one product, whose last rows are b_uv.  The right factor is b_vw over the packed pairs
+// v >= w, half of the square, one product over P gives both outputs' rows, split over workgroups (with
+// 480 rows of P and 8 active orbitals the two products ran on 1 and 8 workgroups, 79 us each), and
+// the pairs are spread over the squares as the partial sums are added.
+df_status run_active(df_ctx* c, char* ws, const ActivePlan& p, double* b, double* part, const double* Cp, int64_t np,
+                     const double* Cact, int64_t nac, const double* Xa, int64_t naux, int64_t nao, double* papa,
+                     double* eri, int accumulate = 0) {
+  const int64_t rows = np + nac, nuv = nac * (nac + 1) / 2;
+  double* vp = (double*)(ws + p.vp);
+  const double* cl = Cact;
+  if (np > 0) {
+    double* pcat = (double*)(ws + p.pcat);
+    const ColBlock blks[2] = {{Cp, np, np, 0}, {Cact, nac, nac, np}};
+    if (df_status s = pad_operand_plain(c, pcat, nao, rows, blks, 2)) return s;
+    cl = pcat;
+  }
+  if (df_status s = run_mo(c, cl, rows, Xa, naux, nao, nac, b)) return s;
+  DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_pack_lower(b + np * nac, rows * nac, naux, nac, vp, c->stream), "pack launch");
+  const int64_t M = (papa ? np : 0) * nac + (eri ? nac * nac : 0), m0 = papa ? 0 : np * nac;
+  const int64_t pb = active_block(naux, np, nac);
+  const int ns = active_splits(naux, np, nac);
+  const int kind = papa ? DF_KERNEL_PAPA : DF_KERNEL_ERI;
+  int64_t nsum = 0;
+  for (int64_t p0 = 0; p0 < naux; p0 += pb, nsum += ns) {
+    const int64_t pn = std::min(pb, naux - p0);
+    const dfk::OpMap A = dfk::op_map(b + m0 + p0 * rows * nac, M, 1, pn, rows * nac);
+    const dfk::OpMap Bm = dfk::op_map(vp + p0 * nuv, nuv, 1, pn, nuv);
+    DF_LAUNCH(kind, dfk::launch_gemm_part(A, Bm, M, nuv, ns, part + nsum * M * nuv, c->stream),
+              "aux contraction launch");
+  }
+  DF_LAUNCH(kind,
+            dfk::launch_expand_pairs(part, (int)nsum, M, nac, papa, papa ? np * nac : 0, eri, accumulate, c->stream),
+            "pair expansion launch");
   return DF_OK;
 }
 
@@ -1619,8 +1693,9 @@ df_status df_active_eri(df_ctx* ctx, const double* B, int64_t naux, int64_t nao,
     const ColBlock blk{Cact, nac, nac, 0};
     if (df_status s = pad_operand(c, cpad, nao, nac, &blk, 1)) return s;
     if (df_status s = run_half(c, B, naux, nao, cpad, nac, out_split(nullptr, X, naux, nao, 0, nac))) return s;
-    if (df_status s = run_mo(c, Cact, nac, X, naux, nao, nac, bu)) return s;
-    if (df_status s = run_pgemm(c, DF_KERNEL_ERI, bu, n2, bu, n2, naux, eri, acc)) return s;
+    if (df_status s = run_active(c, ws, p.act, bu, (double*)(ws + p.act.part), nullptr, 0, Cact, nac, X, naux, nao,
+                                 nullptr, eri, acc))
+      return s;
   } else {
     const SplitOp cas = split_in(ws, p.cas), xas = split_in(ws, p.xas), bvs = split_in(ws, p.buvs);
     if (df_status s = split_xact(c, *reg, Cact, nac, X, cas, xas)) return s;
@@ -1686,6 +1761,9 @@ df_status df_papa(df_ctx* ctx, const double* B, int64_t naux, int64_t nao, const
     const ColBlock blk{Cact, nac, nac, 0};
     if (df_status s = pad_operand(c, cpad, nao, nac, &blk, 1)) return s;
     if (df_status s = run_half(c, B, naux, nao, cpad, nac, out_split(nullptr, X, naux, nao, 0, nac))) return s;
+    if (!full)
+      return run_active(c, ws, p.act, (double*)(ws + p.act.b), (double*)(ws + p.act.part), Cp, np, Cact, nac, X, naux,
+                        nao, out, nullptr, acc);
     if (df_status s = run_mo(c, Cp, np, X, naux, nao, nac, bpu)) return s;
     if (df_status s = run_mo(c, Cr, nr, X, naux, nao, nac, br)) return s;
     return run_pgemm(c, DF_KERNEL_PAPA, bpu, np * nac, br, nr * nac, naux, out, acc);
@@ -1721,7 +1799,7 @@ static df_status ppaa_run(df_ctx* c, char* ws, const PpaaPlan& p, const double* 
   if (df_status s = pad_operand(c, cpa, nao, nac, &ba, 1)) return s;
   if (df_status s = run_half(c, B, naux, nao, cpa, nac, out_split(nullptr, X, naux, nao, 0, nac))) return s;
   if (df_status s = run_mo(c, Cact, nac, X, naux, nao, nac, buv)) return s;
-  DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_pack_lower(buv, naux, nac, vp, c->stream), "pack launch");
+  DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_pack_lower(buv, nac * nac, naux, nac, vp, c->stream), "pack launch");
   const ColBlock bq{Cq, nq, nq, 0};
   if (df_status s = pad_operand(c, cpq, nao, nq, &bq, 1)) return s;
   // P ranges whose packed rows stay inside 31-bit offsets
@@ -1894,7 +1972,7 @@ df_status df_embed_cholesky(df_ctx* ctx, const double* B, int64_t naux, int64_t 
     if (df_status s = run_half(c, B + p0 * npair, pc, nao, mpad, nemb, out_pmajor(X, pc, nao, nemb, nemb)))
       return s;
     if (df_status s = run_mo_pmajor(c, M, nemb, X, pc, nao, nemb, Y)) return s;
-    DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_pack_lower(Y, pc, nemb, Be + p0 * npe, c->stream), "pack launch");
+    DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_pack_lower(Y, nemb * nemb, pc, nemb, Be + p0 * npe, c->stream), "pack launch");
   }
   return DF_OK;
 }
@@ -1963,16 +2041,10 @@ df_status df_step(df_ctx* ctx, const double* B, int64_t naux, int64_t nao, const
       if (df_status s = run_k(c, Xo, w, naux, nao, nocc, nocc, 1, p.nsplit, (double*)(c->ws + p.kpart), K))
         return s;
   }
-  if (nac > 0 && (eri || papa)) {
-    double* buv = (double*)(c->ws + p.buv);
-    if (df_status s = run_mo(c, Cact, nac, Xa, naux, nao, nac, buv)) return s;
-    if (eri)
-      if (df_status s = run_pgemm(c, DF_KERNEL_ERI, buv, nac * nac, buv, nac * nac, naux, eri)) return s;
-    if (papa && np > 0) {
-      double* bpu = (double*)(c->ws + p.bpu);
-      if (df_status s = run_mo(c, Cp, np, Xa, naux, nao, nac, bpu)) return s;
-      if (df_status s = run_pgemm(c, DF_KERNEL_PAPA, bpu, np * nac, buv, nac * nac, naux, papa)) return s;
-    }
+  if (nac > 0 && (eri || (papa && np > 0))) {
+    const bool dp = papa && np > 0;
+    return run_active(c, c->ws, p.act, (double*)(c->ws + p.act.b), (double*)(c->ws + p.kpart), dp ? Cp : nullptr,
+                      dp ? np : 0, Cact, nac, Xa, naux, nao, dp ? papa : nullptr, eri);
   }
   return DF_OK;
 }
@@ -2735,11 +2807,10 @@ df_status df_batched_step(df_ctx* ctx, const df_problem* probs, int nprob, int f
       if (df_status s = batched_coulomb(c, q, Xo, (double*)(ws + b.v), (double*)(ws + b.jp), b.jp_n, (double*)(ws + b.dfull),
                                         (double*)(ws + b.dw), b.vsplit, (double*)(ws + b.vpart)))
         return s;
-    if (q.eri && q.nac > 0) {
-      double* buv = (double*)(ws + b.buv);
-      if (df_status s = run_mo(c, q.Cact, q.nac, Xa, q.naux, q.nao, q.nac, buv)) return s;
-      if (df_status s = run_pgemm(c, DF_KERNEL_ERI, buv, q.nac * q.nac, buv, q.nac * q.nac, q.naux, q.eri)) return s;
-    }
+    if (q.eri && q.nac > 0)
+      if (df_status s = run_active(c, ws, b.act, (double*)(ws + b.act.b), (double*)(ws + b.act.part), nullptr, 0, q.Cact,
+                                   q.nac, Xa, q.naux, q.nao, nullptr, q.eri))
+        return s;
     if (q.papa && q.nac > 0 && q.np > 0) {
       double* bpu = (double*)(ws + b.bpu);
       if (df_status s = run_mo(c, q.Cp, q.np, Xa, q.naux, q.nao, q.nac, bpu)) return s;

@@ -77,6 +77,16 @@ int64_t gemm_slabs(const OpMap& A);
 hipError_t launch_gemm_split(const OpMap& A, const OpMap& Bm, const OutMap& C, int nsplit, double* part,
                              hipStream_t s);
 
+// The partial sums alone: part [nsplit][M][N], nsplit >= 1; part_splits() is the count to take.
+int part_splits(int64_t M, int64_t N, int64_t nslab);
+hipError_t launch_gemm_part(const OpMap& A, const OpMap& Bm, int64_t M, int64_t N, int nsplit, double* part,
+                            hipStream_t s);
+// From partial sums over the packed pairs of nac orbitals, part [nsplit][M][nac (nac + 1) / 2], rows
+// m < M1 to out1[m][nac][nac] and the others to out2[m - M1][nac][nac], both halves of each square
+// (null: not written; added to when `accumulate`).
+hipError_t launch_expand_pairs(const double* part, int nsplit, int64_t M, int64_t nac, double* out1, int64_t M1,
+                               double* out2, int accumulate, hipStream_t s);
+
 // C = alpha * sum_s part[s] (+ C), fixed order over s; part is [nsplit][O.M][O.N].
 hipError_t launch_split_reduce(const double* part, int nsplit, const OutMap& O, hipStream_t s);
 
@@ -155,8 +165,9 @@ hipError_t launch_chol_block(double* A, int64_t lda, int kb, double* Linv, int* 
                              hipStream_t s);
 // A[i][j] = 0 for j > i (n x n, row major)
 hipError_t launch_zero_upper(double* A, int64_t n, hipStream_t s);
-// Ap[z][pair(i, j)] = A[z][i][j] for i >= j: the lower triangles of nz n x n matrices, packed
-hipError_t launch_pack_lower(const double* A, int64_t nz, int64_t n, double* Ap, hipStream_t s);
+// Ap[z][pair(i, j)] = A[z][i][j] for i >= j: the lower triangles of nz n x n matrices (s_z doubles
+// from one to the next), packed
+hipError_t launch_pack_lower(const double* A, int64_t s_z, int64_t nz, int64_t n, double* Ap, hipStream_t s);
 // p[z*s_z + i] = 0 for z < nz, i < n
 hipError_t launch_fill_zero_strided(double* p, int64_t nz, int64_t s_z, int64_t n, hipStream_t s);
 

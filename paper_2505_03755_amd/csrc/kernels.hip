@@ -51,6 +51,8 @@ typedef Cfg<2, 2, 4, 4, true> CfgSq;
 // same per-wave work with a quarter fewer loads per MFMA
 typedef Cfg<4, 2, 4, 4, true> CfgTall;
 typedef Cfg<2, 2, 4, 4, true> CfgSyrk;
+// small products: 64 x 64 tiles, four workgroups per CU
+typedef Cfg<2, 2, 2, 2, true> CfgSmall;
 // small matrices (fragment sizes): 64 x 64 SYRK tiles pad the triangle less
 typedef Cfg<2, 2, 2, 2, true> CfgSyrk64;
 // half transform: {64, 128, 128} rows x {176, 96, 48} columns, 4 waves stacked along the rows
@@ -522,6 +524,31 @@ __global__ void __launch_bounds__(kRedThreads) split_reduce_kernel(const double*
     dst = O.p2 + m * O.s2_m + (n - O.nsplit);
   }
   *dst = O.accumulate ? *dst + O.alpha * s : O.alpha * s;
+}
+
+// Rows m of sums over packed pairs (u >= v of nac orbitals), spread over the full square:
+//   q(m, (u, v)) = q(m, (v, u)) = sum_s part[s][m][pair(max, min)],
+// rows m < M1 to out1[m][nac][nac], the rest to out2[m - M1][nac][nac] (either may be null); fixed
+// order over s.  A workgroup takes `rpb` rows; the reads of a row repeat within it and stay in L1.
+__global__ void __launch_bounds__(256) expand_pairs_kernel(const double* __restrict__ part, int nsplit, int64_t M,
+                                                           int nac, int rpb, double* __restrict__ out1, int64_t M1,
+                                                           double* __restrict__ out2, int accumulate) {
+  const int n2 = nac * nac, nuv = nac * (nac + 1) / 2;
+  const int64_t m0 = (int64_t)blockIdx.x * rpb, stride = M * nuv;
+  const int rows = (int)(M - m0 < rpb ? M - m0 : rpb);
+  for (int idx = threadIdx.x; idx < rows * n2; idx += 256) {
+    const int r = idx / n2, e = idx - r * n2, u = e / nac, v = e - u * nac;
+    const int64_t m = m0 + r;
+    double* dst = m < M1 ? out1 : out2;
+    if (!dst) continue;
+    dst += (m < M1 ? m : m - M1) * n2 + e;
+    const int i = u > v ? u : v, j = u > v ? v : u;
+    const double* q = part + m * nuv + i * (i + 1) / 2 + j;
+    double s = 0.0;
+#pragma unroll 4
+    for (int sp = 0; sp < nsplit; ++sp) s += q[sp * stride];
+    *dst = accumulate ? *dst + s : s;
+  }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1172,8 +1199,8 @@ __global__ void __launch_bounds__(256) unpack_sym_kernel(const double* __restric
   J[z * nao * nao + j * nao + i] = x;
 }
 
-__global__ void __launch_bounds__(256) pack_lower_kernel(const double* __restrict__ A, int64_t nz, int64_t n,
-                                                         int64_t npair, double* __restrict__ Ap) {
+__global__ void __launch_bounds__(256) pack_lower_kernel(const double* __restrict__ A, int64_t s_z, int64_t nz,
+                                                         int64_t n, int64_t npair, double* __restrict__ Ap) {
   const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (idx >= nz * npair) return;
   const int64_t z = idx / npair, p = idx % npair;
@@ -1181,7 +1208,7 @@ __global__ void __launch_bounds__(256) pack_lower_kernel(const double* __restric
   while (i * (i + 1) / 2 > p) --i;
   while ((i + 1) * (i + 2) / 2 <= p) ++i;
   const int64_t j = p - i * (i + 1) / 2;
-  Ap[idx] = A[z * n * n + i * n + j];
+  Ap[idx] = A[z * s_z + i * n + j];
 }
 
 // Cholesky factor of one kb x kb diagonal block (kb <= kCholNB) of the metric, in LDS, and the
@@ -1561,8 +1588,31 @@ static hipError_t gemm_launch_cfg(const OpMap& A, const OpMap& Bm, const OutMap&
   return hipGetLastError();
 }
 
+int64_t gemm_slabs(const OpMap& A) { return A.kb_n * cdiv(A.kc_n, 16); }
+
+// Estimated time (us) of W equal workgroups of `slabs` slabs each on 128 x 128 or (small) 64 x 64
+// tiles.  A slab takes 4.6 us with two 128-wide workgroups on a CU and 2.6 with one, where the
+// latency of its loads shows (one workgroup over 30 slabs: 79 us); 64-wide tiles issue a quarter
+// of the MFMAs, fit four to a CU and take 1.3 us alone, 2.7 with four.
+static double gemm_us(int64_t W, double slabs, bool small) {
+  const int64_t per = small ? 1024 : 512;
+  const int64_t rem = W % per;
+  const double full = small ? 2.7 : 4.6;
+  double last = 0.0;
+  if (rem > 0) last = small ? (rem <= 256 ? 1.3 : rem <= 512 ? 1.6 : rem <= 768 ? 2.1 : 2.7) : rem <= 256 ? 2.6 : 4.6;
+  return ((double)(W / per) * full + last) * (slabs + 4.0);
+}
+// 64 x 64 tiles where they are estimated faster: products of few 128-wide tiles, or that fill them badly
+// (b_uv and b_pu at 120 x 480 36 + 35 -> 18 us in one product, b_uv at 600 x 2400 185 -> 90 us).
+static bool gemm_small(int64_t M, int64_t N, int64_t nw, double slabs) {
+  return gemm_us(cdiv(M, CfgSmall::BM) * cdiv(N, CfgSmall::BN) * nw, slabs, true) <
+         gemm_us(cdiv(M, CfgSq::BM) * cdiv(N, CfgSq::BN) * nw, slabs, false);
+}
+
 static hipError_t gemm_launch(const OpMap& A, const OpMap& Bm, const OutMap& O, int64_t nz, int nsplit,
                               double* part, hipStream_t s) {
+  if (gemm_small(O.M, O.N, nz * nsplit, (double)gemm_slabs(A) / nsplit))
+    return gemm_launch_cfg<CfgSmall>(A, Bm, O, nz, nsplit, part, s);
   const int64_t rem = O.M % CfgSq::BM, tn = cdiv(O.N, CfgSq::BN);
   if (gemm_tall(O.M) && rem > 0 && rem <= CfgRowTail::BM && nz == 1 && nsplit == 1 && !part && O.alpha == 1.0 &&
       !O.accumulate && A.kc_n % 16 == 0 && (O.M / CfgSq::BM + 1) * tn <= 0x7fffffffLL && offsets_fit(A) &&
@@ -1583,8 +1633,6 @@ static hipError_t gemm_launch(const OpMap& A, const OpMap& Bm, const OutMap& O, 
 hipError_t launch_gemm(const OpMap& A, const OpMap& Bm, const OutMap& O, int64_t nz, hipStream_t s) {
   return gemm_launch(A, Bm, O, nz, 1, nullptr, s);
 }
-
-int64_t gemm_slabs(const OpMap& A) { return A.kb_n * cdiv(A.kc_n, 16); }
 
 // Workgroups resident at once for the MFMA kernels on MI355X: 256 CUs x 2 (each kernel is sized
 // for two workgroups per CU).  A launch of W equal workgroups takes ceil(W / kResident) rounds.
@@ -1643,6 +1691,42 @@ int gemm_splits(int64_t M, int64_t N, int64_t nslab) {
                            slab_us(CfgSq::BM, CfgSq::BN));
   return balanced_splits(cdiv(M, CfgSq::BM) * cdiv(N, CfgSq::BN), nslab / 4, nslab, M * N,
                          slab_us(CfgSq::BM, CfgSq::BN));
+}
+
+// Split count of a product whose partial sums are read by a kernel of their own in any case
+// (expand_pairs): the least estimated time over both tiles, at least two slabs per split, and at
+// most 64 MB of partials beyond the first.
+int part_splits(int64_t M, int64_t N, int64_t nslab) {
+  int best = 1;
+  double best_us = 0.0;
+  const int64_t most = std::max<int64_t>(1, std::min<int64_t>({nslab / 2, 64, 1 + (int64_t(8) << 20) / std::max<int64_t>(M * N, 1)}));
+  for (int ns = 1; ns <= most; ++ns) {
+    const double slabs = (double)cdiv(nslab, ns);
+    const double us = std::min(gemm_us(cdiv(M, CfgSmall::BM) * cdiv(N, CfgSmall::BN) * ns, slabs, true),
+                               gemm_us(cdiv(M, CfgSq::BM) * cdiv(N, CfgSq::BN) * ns, slabs, false)) +
+                      (double)ns * (double)(M * N) * 16.0 / 4.0e6;
+    if (ns == 1 || us < best_us) {
+      best_us = us;
+      best = ns;
+    }
+  }
+  return best;
+}
+
+hipError_t launch_gemm_part(const OpMap& A, const OpMap& Bm, int64_t M, int64_t N, int nsplit, double* part,
+                            hipStream_t s) {
+  return gemm_launch(A, Bm, out_plain(part, M, N, N), 1, nsplit, part, s);
+}
+
+hipError_t launch_expand_pairs(const double* part, int nsplit, int64_t M, int64_t nac, double* out1, int64_t M1,
+                               double* out2, int accumulate, hipStream_t s) {
+  if (M <= 0 || nac <= 0) return hipSuccess;
+  if (nac > 32768) return hipErrorInvalidValue;
+  const int rpb = (int)std::max<int64_t>(1, 256 / (nac * nac));
+  const int64_t nb = cdiv(M, rpb);
+  if (nb > 0x7fffffffLL) return hipErrorInvalidValue;
+  expand_pairs_kernel<<<(unsigned)nb, 256, 0, s>>>(part, nsplit, M, (int)nac, rpb, out1, M1, out2, accumulate);
+  return hipGetLastError();
 }
 
 hipError_t launch_split_reduce(const double* part, int nsplit, const OutMap& O, hipStream_t s) {
@@ -2094,10 +2178,10 @@ hipError_t launch_zero_upper(double* A, int64_t n, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_pack_lower(const double* A, int64_t nz, int64_t n, double* Ap, hipStream_t s) {
+hipError_t launch_pack_lower(const double* A, int64_t s_z, int64_t nz, int64_t n, double* Ap, hipStream_t s) {
   const int64_t npair = n * (n + 1) / 2, tot = nz * npair;
   if (tot <= 0) return hipSuccess;
-  pack_lower_kernel<<<(unsigned)cdiv(tot, 256), 256, 0, s>>>(A, nz, n, npair, Ap);
+  pack_lower_kernel<<<(unsigned)cdiv(tot, 256), 256, 0, s>>>(A, s_z, nz, n, npair, Ap);
   return hipGetLastError();
 }
 

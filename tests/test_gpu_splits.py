@@ -1,5 +1,6 @@
 """Launches whose contraction is split over workgroups, at the sizes where the split changes: the
-Coulomb build over P (none below 8 rows, at most 128 splits, pairs around its 1024-pair tile).
+Coulomb build over P (none below 8 rows, at most 128 splits, pairs around its 1024-pair tile) and the
+active-space contractions over packed pairs.
 
 Bar: 1e-10 normwise against the FP64 oracle, as in test_gpu_parity.py (reordering a sum of at most
 1e6 terms costs about 1e-13)."""
@@ -87,3 +88,34 @@ def test_adjoint_coulomb_under_scratch_limit(nao, naux):
             close(dCo, ref[0], f"dCocc limit {limit}")
             if cot[2] is not None:
                 close(dCa, ref[1], f"dCact limit {limit}")
+
+
+# naux 5: one split of less than a slab; 33: the fewest slabs with two splits; 700: many; nac 1 and 17:
+# one pair, and pairs past one and two 64-wide tiles; np 0 and 130: rows of (uv) alone, and past a tile
+@pytest.mark.parametrize("nao,naux,nac,nmo", [(19, 5, 3, 7), (40, 33, 8, 40), (37, 700, 1, 0), (60, 700, 17, 60), (130, 48, 12, 130)])
+def test_active_contractions_over_packed_pairs(nao, naux, nac, nmo):
+    rng = np.random.default_rng(nao * 1000 + naux)
+    B = rng.standard_normal((naux, O.npair(nao)))
+    C = np.linalg.qr(rng.standard_normal((nao, nao)))[0]
+    Cact, Cp, Cocc = C[:, :nac], C[:, :nmo], C[:, :max(1, nao // 4)]
+    gB, gA, gP, gO = dev(B), dev(Cact), dev(Cp), dev(Cocc)
+    eri, buv = O.active_eri(B, nao, Cact)
+    ge, gb = dfmi.active_eri(gB, nao, gA, return_buv=True)
+    close(ge, eri, "eri")
+    close(gb, buv, "b_uv")
+    oe, ob = torch.ones_like(ge), torch.ones_like(gb)
+    dfmi.active_eri(gB, nao, gA, return_buv=True, out=(oe, ob), accumulate=True)
+    close(oe, 1.0 + eri, "accumulated eri")
+    close(ob, 1.0 + buv, "accumulated b_uv")
+    out = dfmi.step(gB, nao, gO, gA, gP)
+    close(out["eri"], eri, "step eri")
+    if nmo:
+        papa = O.papa(B, nao, Cp, Cact)
+        gp = dfmi.papa(gB, nao, gP, gA)
+        close(gp, papa, "papa")
+        close(out["papa"], papa, "step papa")
+        acc = torch.ones_like(gp)
+        dfmi.papa(gB, nao, gP, gA, out=acc, accumulate=True)
+        close(acc, 1.0 + papa, "accumulated papa")
+        assert torch.equal(gp, gp.transpose(2, 3))
+    assert torch.equal(ge, ge.transpose(2, 3))
