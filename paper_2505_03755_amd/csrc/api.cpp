@@ -461,7 +461,8 @@ ActPlan plan_act(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int flags, in
 // rows of Cact, Cp (and Cq), of the rows (P, u) of X_act and of the rows of b_pu and b_vw / b_qv
 // over P.
 struct PapaPlan {
-  size_t cpad, x, bpu, bvw, bqv;
+  size_t cpad, x, bpu, bvw, bqv, gpart;
+  int64_t gpart_n;  // doubles at gpart: partial sums of the (pu|qv) block with Cq = Cp
   ActivePlan act;   // the default form in FP64
   SplitBuf cas, cps, cqs, xas, bpus, bvws, bqvs;
 };
@@ -475,6 +476,8 @@ PapaPlan plan_papa(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int64_t np,
   p.bvw = pl.take(full || packed ? 0 : naux * nac * nac);
   if (packed) p.act = plan_active(pl, naux, nao, np, nac, true, true);
   p.bqv = pl.take(full ? naux * nq * nac : 0);
+  p.gpart_n = full && !sp && np == nq ? dfk::gram_part(np * nac, (naux + 15) / 16) : 0;
+  p.gpart = pl.take(p.gpart_n);
   if (sp) {
     p.xas = take_split(pl, naux * nac, nao, nslice);
     p.cps = take_split(pl, np, nao, nslice);
@@ -556,7 +559,8 @@ BwdSplitPlan plan_backward_split(Plan& pl, int64_t naux, int64_t nao, int64_t no
 
 // ---- batched problems ----
 struct BatchedPiece {
-  size_t cpad, xo, xa, v, jp, kpart, bpu, dfull, dw, vpart;
+  size_t cpad, xo, xa, v, jp, kpart, bpu, gpart, dfull, dw, vpart;
+  int64_t gpart_n;  // doubles at gpart: partial sums of the (pu|qv) block
   ActivePlan act;   // (uv|wx)
   int64_t jp_n;   // doubles at jp: packed J of many densities, or the Coulomb build's partial sums
   int nsplit, vsplit;
@@ -795,7 +799,10 @@ std::vector<BatchedPiece> plan_batched(Plan& pl, const df_problem* probs, int n)
     b.nsplit = ks[(size_t)i];
     b.kpart = pl.take(q.K && q.nocc > 0 ? (int64_t)b.nsplit * q.ndm * q.nao * q.nao : 0);
     if (q.eri && q.nac > 0) b.act = plan_active(pl, q.naux, q.nao, 0, q.nac, true, true);
-    b.bpu = pl.take(q.papa && q.nac > 0 && q.np > 0 ? q.naux * q.np * q.nac : 0);
+    const bool dp = q.papa && q.nac > 0 && q.np > 0;
+    b.bpu = pl.take(dp ? q.naux * q.np * q.nac : 0);
+    b.gpart_n = dp ? dfk::gram_part(q.np * q.nac, (q.naux + 15) / 16) : 0;
+    b.gpart = pl.take(b.gpart_n);
   }
   return v;
 }
@@ -1033,6 +1040,15 @@ df_status run_pgemm(df_ctx* c, int kind, const double* L, int64_t M, const doubl
   dfk::OutMap O = dfk::out_plain(out, M, N, N);
   O.accumulate = accumulate;
   DF_LAUNCH(kind, dfk::launch_gemm(A, Bm, O, 1, c->stream), "aux contraction launch");
+  return DF_OK;
+}
+
+// out[m][n] = out[n][m] (+)= sum_P L[P][m] L[P][n]
+df_status run_gram(df_ctx* c, int kind, const double* L, int64_t M, int64_t naux, double* out, double* part,
+                   int64_t part_n, int accumulate = 0) {
+  if (M == 0) return DF_OK;
+  DF_LAUNCH(kind, dfk::launch_gram(dfk::op_map(L, M, 1, naux, M), out, part, part_n, accumulate, c->stream),
+            "aux contraction launch");
   return DF_OK;
 }
 
@@ -1765,6 +1781,8 @@ df_status df_papa(df_ctx* ctx, const double* B, int64_t naux, int64_t nao, const
       return run_active(c, ws, p.act, (double*)(ws + p.act.b), (double*)(ws + p.act.part), Cp, np, Cact, nac, X, naux,
                         nao, out, nullptr, acc);
     if (df_status s = run_mo(c, Cp, np, X, naux, nao, nac, bpu)) return s;
+    if (Cq == Cp && nq == np)   // one factor: half of a symmetric product
+      return run_gram(c, DF_KERNEL_PAPA, bpu, np * nac, naux, out, (double*)(ws + p.gpart), p.gpart_n, acc);
     if (df_status s = run_mo(c, Cr, nr, X, naux, nao, nac, br)) return s;
     return run_pgemm(c, DF_KERNEL_PAPA, bpu, np * nac, br, nr * nac, naux, out, acc);
   }
@@ -2814,7 +2832,8 @@ df_status df_batched_step(df_ctx* ctx, const df_problem* probs, int nprob, int f
     if (q.papa && q.nac > 0 && q.np > 0) {
       double* bpu = (double*)(ws + b.bpu);
       if (df_status s = run_mo(c, q.Cp, q.np, Xa, q.naux, q.nao, q.nac, bpu)) return s;
-      if (df_status s = run_pgemm(c, DF_KERNEL_PAPA, bpu, q.np * q.nac, bpu, q.np * q.nac, q.naux, q.papa)) return s;
+      if (df_status s = run_gram(c, DF_KERNEL_PAPA, bpu, q.np * q.nac, q.naux, q.papa, (double*)(ws + b.gpart), b.gpart_n))
+        return s;
     }
   }
   // (pq|uv) through the AO basis, problem after problem in one region

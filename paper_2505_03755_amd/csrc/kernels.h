@@ -130,6 +130,12 @@ hipError_t launch_syrk_partial(const OpMap& A, const OpMap& Bw, int64_t n, int64
 hipError_t launch_syrk_reduce(const double* Kpart, int nsplit, int64_t n, int64_t nz, double* K,
                               hipStream_t s, int accumulate = 0);
 
+// G(m, n) = sum_k A(m, k) A(n, k), M x M (M = A.rows), both triangles written (added to when
+// `accumulate`) from the lower tiles; A with its rows along lanes (s_rlo == 1).  part: scratch of
+// part_n doubles for a split contraction; gram_part() of them (it may be 0) let it split as it wants.
+int64_t gram_part(int64_t M, int64_t nslab);
+hipError_t launch_gram(const OpMap& A, double* G, double* part, int64_t part_n, int accumulate, hipStream_t s);
+
 // v[z][P] = sum_{m<nao, c<nocc} C[z][m][c] w[z][c] X[P][m][z*nocc + c]   (X row stride ldx; v row
 // stride ldv, naux when 0; added to v when `accumulate`)
 hipError_t launch_jvec(const double* X, int64_t naux, int64_t nao, int64_t ldx, const double* C,

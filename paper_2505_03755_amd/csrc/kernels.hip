@@ -454,6 +454,64 @@ __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2)))
   gemm_tile<C, AK, BK, GEN, CLAMP>(A, B, O, m0, n0, blockIdx.z, gridDim.y, blockIdx.y, part, smem);
 }
 
+// Row i and column j <= i of packed pair p = i(i+1)/2 + j.
+__device__ __forceinline__ void pair_ij(int64_t p, int64_t* i, int64_t* j) {
+  int64_t r = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
+  while (r * (r + 1) / 2 > p) --r;
+  while ((r + 1) * (r + 2) / 2 <= p) ++r;
+  *i = r;
+  *j = p - r * (r + 1) / 2;
+}
+
+// Gram matrix  G(m, n) = sum_k A(m, k) A(n, k): the tiles on and below the diagonal only (tile pair I >= J
+// of the triangle), lanes along the rows of A.  Without a split a tile is stored to G and, mirrored,
+// to the transposed place (accumulate adds to both); with one the partial sums go to part [split][M][M],
+// lower tiles only, for syrk_reduce.  Bound by the matrix cores; half the MFMAs of the full product.
+template <class C, bool CLAMP>
+__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) gram_kernel(OpMap A, double* G, int64_t npairs, int accumulate, double* part) {
+  static_assert(C::BM == C::BN, "square tiles");
+  __shared__ double smem[2 * C::STAGE];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int wm = wave % C::WM, wn = wave / C::WM;
+  int64_t I, J;
+  pair_ij(xcd_remap(blockIdx.x, npairs), &I, &J);
+  const int64_t m0 = I * C::BM, n0 = J * C::BN, M = A.rows;
+  const int nsplit = gridDim.y, split = blockIdx.y;
+  const int64_t S = A.kb_n * ((A.kc_n + C::BK - 1) / C::BK), s0 = S * split / nsplit, s1 = S * (split + 1) / nsplit;
+  d4 acc[C::TM][C::TN];
+  zero_acc<C>(acc);
+  if (s1 > s0) {
+    PairSrc<C, false, false, false, CLAMP> src;
+    src.A = &A;
+    src.B = &A;
+    src.t = t;
+    src.a.init(A, m0, 0, s0, s1, t);
+    src.b.init(A, n0, 0, s0, s1, t);
+    mainloop<C>(src, smem, s1 - s0, acc, wm, wn, lane);
+  }
+  if (part) {
+    store_tile<C, false>(out_plain(part + (int64_t)split * M * M, M, M, M), 0, m0, n0, acc, wm, wn, lane);
+    return;
+  }
+  // A lane's column index is lane % 16 and its rows come four apart, so the mirrored stores write runs
+  // of four doubles; the four of a block fill its 128-byte lines in L2.
+  const int lr = lane & 15, lg = lane >> 4;
+#pragma unroll
+  for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+    for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int64_t m = m0 + (wm * C::TM + i) * 16 + 4 * r + lg, n = n0 + (wn * C::TN + j) * 16 + lr;
+        if (m >= M || n > m) continue;   // each pair from its lower element
+        double *a = G + m * M + n, *b = G + n * M + m;
+        const double x = acc[i][j][r];
+        const double xa = accumulate ? *a + x : x, xb = accumulate ? *b + x : x;
+        *a = xa;
+        *b = xb;
+      }
+}
+
 // Rows in whole 128-row bands on 128 x 128 tiles and the rest (at most 64 rows) on 64 x 128 tiles
 // (4 waves of 64 x 32), in one launch: per column block the band tiles, then the tail tile.
 // Where the 256 x 128 or 128 x 128 tiles would pad the rows by more than 64 (1200 rows: 1280).
@@ -470,15 +528,6 @@ __global__ void __launch_bounds__(CfgSq::NT) __attribute__((amdgpu_waves_per_eu(
     gemm_tile<CfgSq, AK, BK, false, false>(A, B, O, i * CfgSq::BM, n0, 0, 1, 0, nullptr, smem);
   else
     gemm_tile<CfgRowTail, AK, BK, false, false>(A, B, O, nband * CfgSq::BM, n0, 0, 1, 0, nullptr, smem);
-}
-
-// Row i and column j <= i of packed pair p = i(i+1)/2 + j.
-__device__ __forceinline__ void pair_ij(int64_t p, int64_t* i, int64_t* j) {
-  int64_t r = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
-  while (r * (r + 1) / 2 > p) --r;
-  while ((r + 1) * (r + 2) / 2 <= p) ++r;
-  *i = r;
-  *j = p - r * (r + 1) / 2;
 }
 
 // Sum over s < nsplit of q[s * stride] by the G threads of a column (thread y takes s = y, y + G,
@@ -1856,6 +1905,60 @@ hipError_t launch_symmetrize(const double* in, int64_t n, int64_t nz, double* ou
 }
 
 
+
+// Gram products: tile and split count of least estimated time over the tiles of the triangle, the
+// partial sums (written, read, and the reduction's launch) included; at most 64 MB of partials
+// beyond the first.
+static int64_t gram_tiles(int64_t M, bool small) {
+  const int64_t T = cdiv(M, small ? CfgSmall::BM : CfgSq::BM);
+  return T * (T + 1) / 2;
+}
+static int gram_plan(int64_t M, int64_t nslab, int max_split, bool* small) {
+  int best = 1;
+  double best_us = 0.0;
+  const int64_t most = std::max<int64_t>(1, std::min<int64_t>({nslab / 4, max_split, 1 + (int64_t(8) << 20) / std::max<int64_t>(M * M, 1)}));
+  *small = false;
+  for (int ns = 1; ns <= most; ++ns)
+    for (int sm = 0; sm < 2; ++sm) {
+      const double us = gemm_us(gram_tiles(M, sm) * ns, (double)cdiv(nslab, ns), sm) +
+                        (ns > 1 ? 5.0 + (double)ns * (double)(M * M) * 8.0 / 4.0e6 : 0.0);
+      if ((ns == 1 && sm == 0) || us < best_us) {
+        best_us = us;
+        best = ns;
+        *small = sm;
+      }
+    }
+  return best;
+}
+int64_t gram_part(int64_t M, int64_t nslab) {
+  bool small;
+  const int ns = gram_plan(M, nslab, 64, &small);
+  return ns > 1 ? ns * M * M : 0;
+}
+
+template <class Cg>
+static void gram_go(const OpMap& A, double* G, int64_t npairs, int ns, int accumulate, double* part, hipStream_t s) {
+  const dim3 grid((unsigned)npairs, (unsigned)ns);
+  if (A.kc_n % 16 != 0) gram_kernel<Cg, true><<<grid, Cg::NT, 0, s>>>(A, G, npairs, accumulate, part);
+  else gram_kernel<Cg, false><<<grid, Cg::NT, 0, s>>>(A, G, npairs, accumulate, part);
+}
+
+hipError_t launch_gram(const OpMap& A, double* G, double* part, int64_t part_n, int accumulate, hipStream_t s) {
+  const int64_t M = A.rows;
+  if (M <= 0) return hipSuccess;
+  if (!offsets_fit(A)) return hipErrorInvalidValue;
+  bool small;
+  const int64_t room = part ? part_n / (M * M) : 0;
+  const int ns = gram_plan(M, gemm_slabs(A), (int)std::max<int64_t>(1, std::min<int64_t>(room, 64)), &small);
+  const int64_t npairs = gram_tiles(M, small);
+  if (npairs > 0x7fffffffLL) return hipErrorInvalidValue;
+  double* pt = ns > 1 ? part : nullptr;
+  if (small) gram_go<CfgSmall>(A, G, npairs, ns, accumulate, pt, s);
+  else gram_go<CfgSq>(A, G, npairs, ns, accumulate, pt, s);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess || !pt) return e;
+  return launch_syrk_reduce(pt, ns, M, 1, G, s, accumulate);
+}
 
 int syrk_tile_for(int64_t n) { return n <= 640 ? CfgSyrk64::BM : CfgSyrk::BM; }
 

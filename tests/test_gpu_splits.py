@@ -119,3 +119,25 @@ def test_active_contractions_over_packed_pairs(nao, naux, nac, nmo):
         close(acc, 1.0 + papa, "accumulated papa")
         assert torch.equal(gp, gp.transpose(2, 3))
     assert torch.equal(ge, ge.transpose(2, 3))
+
+
+# (pu|qv) with one factor on both sides: 1, 63 ... 65 and 390 rows (one 64-wide tile, past it, and with
+# 128-wide ones), a contraction of less than a slab and one that is split
+@pytest.mark.parametrize("nao,naux,nac,nmo", [(9, 5, 1, 1), (21, 40, 3, 21), (64, 130, 1, 64), (65, 300, 1, 65), (65, 700, 6, 65)])
+def test_papa_full_with_one_factor(nao, naux, nac, nmo):
+    rng = np.random.default_rng(nao * 1000 + naux)
+    B = rng.standard_normal((naux, O.npair(nao)))
+    C = np.linalg.qr(rng.standard_normal((nao, nao)))[0]
+    Cact, Cp = C[:, :nac], C[:, :nmo]
+    b = np.einsum("mp,Pmn,nu->Ppu", Cp, O.unpack(B, nao), Cact).reshape(naux, -1)
+    ref = (b.T @ b).reshape(nmo, nac, nmo, nac)
+    gB, gA, gP = dev(B), dev(Cact), dev(Cp)
+    one, two = dfmi.papa(gB, nao, gP, gA, Cq=gP), dfmi.papa(gB, nao, gP, gA, Cq=gP.clone())
+    acc = torch.ones_like(one)
+    dfmi.papa(gB, nao, gP, gA, Cq=gP, out=acc, accumulate=True)
+    pr = {"B": gB, "nao": nao, "Cocc": gP[None, :, :1].contiguous(), "Cact": gA, "Cp": gP}
+    batch = dfmi.batched_step([pr])[0]["papa"]
+    for name, got, r in (("one factor", one, ref), ("two", two, ref), ("batch", batch, ref), ("accumulated", acc, 1.0 + ref)):
+        close(got, r, name)
+    flat = one.reshape(nmo * nac, -1)
+    assert torch.equal(flat, flat.T)
