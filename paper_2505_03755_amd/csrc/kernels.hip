@@ -30,12 +30,11 @@ namespace dfk {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-// WM x WN waves, each TM x TN MFMA tiles of 16 x 16; IL selects the interleaved schedule
-// (loads and LDS stores spread between the MFMAs) over the bulk one.
-template <int WM_, int WN_, int TM_, int TN_, bool IL_ = false>
+// WM x WN waves, each TM x TN MFMA tiles of 16 x 16; WPE: waves per SIMD the half transform's kernels
+// are compiled for (at least).
+template <int WM_, int WN_, int TM_, int TN_, int WPE_ = 2>
 struct Cfg {
-  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_;
-  static constexpr bool IL = IL_;
+  static constexpr int WM = WM_, WN = WN_, TM = TM_, TN = TN_, WPE = WPE_;
   static constexpr int NT = 64 * WM * WN;
   static constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN, BK = 16;
   static constexpr int LD = BK + 1;
@@ -45,24 +44,37 @@ struct Cfg {
 
 // Every MFMA kernel is sized for two waves per SIMD (at most 256 registers per lane, two
 // workgroups' LDS per CU), so one wave's barrier and LDS latency hide behind the other's MFMAs.
-// generic products and the K SYRK: 128 x 128 tiles, 2 x 2 waves of 64 x 64, interleaved
-typedef Cfg<2, 2, 4, 4, true> CfgSq;
+// generic products and the K SYRK: 128 x 128 tiles, 2 x 2 waves of 64 x 64
+typedef Cfg<2, 2, 4, 4> CfgSq;
 // tall products (M >= 256): 256 x 128 tiles, 4 x 2 waves of 64 x 64, one workgroup per CU; the
 // same per-wave work with a quarter fewer loads per MFMA
-typedef Cfg<4, 2, 4, 4, true> CfgTall;
-typedef Cfg<2, 2, 4, 4, true> CfgSyrk;
+typedef Cfg<4, 2, 4, 4> CfgTall;
+typedef Cfg<2, 2, 4, 4> CfgSyrk;
 // small products: 64 x 64 tiles, four workgroups per CU
-typedef Cfg<2, 2, 2, 2, true> CfgSmall;
+typedef Cfg<2, 2, 2, 2> CfgSmall;
 // small matrices (fragment sizes): 64 x 64 SYRK tiles pad the triangle less
-typedef Cfg<2, 2, 2, 2, true> CfgSyrk64;
-// half transform: {64, 128, 128} rows x {176, 96, 48} columns, 4 waves stacked along the rows
-typedef Cfg<4, 1, 1, 11, true> CfgH176;
-typedef Cfg<4, 1, 2, 6> CfgH96;
-typedef Cfg<4, 1, 2, 3> CfgH48;
-// half transform on 2-D wave tiles: 128 rows x {128, 96, 64} columns, 2 x 2 waves of 4 x {4, 3, 2}
-typedef Cfg<2, 2, 4, 4, true> CfgQ128;
-typedef Cfg<2, 2, 4, 3, true> CfgQ96;
-typedef Cfg<2, 2, 4, 2, true> CfgQ64;
+typedef Cfg<2, 2, 2, 2> CfgSyrk64;
+// half transform: 64-row bands on tiles of 128 columns (three workgroups per CU), the columns past the
+// last whole one on one tile of 96, 64, 48, 32 or 16.  At N_ao = 512 (2048 rows of P, columns that fill
+// the tile) 128 columns run at 57.9 TF/s, as fast as 128 x 128 tiles (58.5) and with half the rows
+// to pad; 96: 54.6, 64: 49.6, 48: 45.6, 32: 39.5, 16: 24.3 (there bound by the latency of the loads of b^P,
+// so these take four waves per SIMD and more).  Where the rows past the last whole band fit 32, they take
+// 32 x 128 tiles, if the columns fill a tile of 128 at all.  176 columns on one row of waves: 48.6;
+// grouped launches may ask for it.
+typedef Cfg<2, 2, 2, 4, 3> CfgH128;
+typedef Cfg<2, 2, 2, 3, 3> CfgH96;
+typedef Cfg<2, 2, 2, 2, 4> CfgH64;
+typedef Cfg<4, 1, 1, 3, 4> CfgH48;
+typedef Cfg<4, 1, 1, 2, 4> CfgH32;
+typedef Cfg<4, 1, 1, 1, 4> CfgH16;
+typedef Cfg<1, 4, 2, 2, 3> CfgHTail;
+// The same with 128-row bands, for b^P larger than an XCD's L2 (see half_cols).  128 columns there: 61.6 TF/s.
+typedef Cfg<2, 2, 4, 4> CfgQ128;
+typedef Cfg<2, 2, 4, 3> CfgQ96;
+typedef Cfg<2, 2, 4, 2> CfgQ64;
+typedef Cfg<4, 1, 2, 3> CfgQ48;
+typedef Cfg<2, 2, 2, 4> CfgQTail;
+typedef Cfg<4, 1, 1, 11> CfgH176;
 
 // ---------------------------------------------------------------------------------------
 // Block index -> work item, keeping runs of consecutive work items on one XCD.  The
@@ -119,7 +131,7 @@ __device__ __forceinline__ void static_for(F&& f) {
 // zeroed: they only reach output rows and columns that are not stored.  Only contraction
 // indices past the end (a partial last slab) must contribute zero.
 
-// One slab of the software pipeline (interleaved schedule).  LDS stage `cur` holds the slab being
+// One slab of the software pipeline.  LDS stage `cur` holds the slab being
 // multiplied and F[0] already holds its first k-step of operands.  While its TM*TN*BK/4 MFMAs
 // issue one by one, the wave reads the operands of the next k-step, issues the global loads of
 // the next slab in the first half and writes those registers to the other LDS stage in the
@@ -163,32 +175,6 @@ __device__ __forceinline__ void slab_step(Src& src, double* smem, int cur, d4 (&
   read_frag<C>(An, Bn, 0, F[0], wm, wn, lane);
 }
 
-// Bulk schedule of one slab: all global loads of the next slab, then every MFMA of this one,
-// then the LDS stores of the loaded registers into the other stage and one barrier.
-template <class C, class Src>
-__device__ __forceinline__ void slab_step_bulk(Src& src, double* smem, int cur, d4 (&acc)[C::TM][C::TN], int wm,
-                                               int wn, int lane) {
-  const double* As = smem + cur * C::STAGE;
-  const double* Bs = As + C::LDS_A;
-  double* An = smem + (cur ^ 1) * C::STAGE;
-  src.begin();
-  static_for<Src::NL>([&](auto Q) { src.template load<decltype(Q)::value>(); });
-  src.finish();
-  __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-  for (int kk = 0; kk < C::BK; kk += 4) {
-    Frag<C> f;
-    read_frag<C>(As, Bs, kk, f, wm, wn, lane);
-#pragma unroll
-    for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < C::TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f64_16x16x4f64(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
-  }
-  __builtin_amdgcn_sched_barrier(0);
-  static_for<Src::NL>([&](auto Q) { src.template store<decltype(Q)::value>(An, An + C::LDS_A); });
-  __syncthreads();
-}
-
 // Runs nslab slabs through the pipeline (nslab >= 1).  The loads issued during the last slab
 // re-read it (the sources clamp) and land in the stage nobody reads any more.
 template <class C, class Src>
@@ -199,13 +185,9 @@ __device__ __forceinline__ void mainloop(Src& src, double* smem, int64_t nslab, 
   src.finish();
   static_for<Src::NL>([&](auto Q) { src.template store<decltype(Q)::value>(smem, smem + C::LDS_A); });
   __syncthreads();
-  if constexpr (C::IL) {
-    Frag<C> F[2];
-    read_frag<C>(smem, smem + C::LDS_A, 0, F[0], wm, wn, lane);
-    for (int64_t s = 0; s < nslab; ++s) slab_step<C>(src, smem, (int)(s & 1), acc, F, wm, wn, lane);
-  } else {
-    for (int64_t s = 0; s < nslab; ++s) slab_step_bulk<C>(src, smem, (int)(s & 1), acc, wm, wn, lane);
-  }
+  Frag<C> F[2];
+  read_frag<C>(smem, smem + C::LDS_A, 0, F[0], wm, wn, lane);
+  for (int64_t s = 0; s < nslab; ++s) slab_step<C>(src, smem, (int)(s & 1), acc, F, wm, wn, lane);
 }
 
 // Epilogue.  GEN = false stores the accumulators as they are (o.alpha must be 1 and
@@ -515,7 +497,7 @@ __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2)))
 // Rows in whole 128-row bands on 128 x 128 tiles and the rest (at most 64 rows) on 64 x 128 tiles
 // (4 waves of 64 x 32), in one launch: per column block the band tiles, then the tail tile.
 // Where the 256 x 128 or 128 x 128 tiles would pad the rows by more than 64 (1200 rows: 1280).
-typedef Cfg<1, 4, 4, 2, true> CfgRowTail;
+typedef Cfg<1, 4, 4, 2> CfgRowTail;
 template <bool AK, bool BK>
 __global__ void __launch_bounds__(CfgSq::NT) __attribute__((amdgpu_waves_per_eu(2))) gemm_tail_kernel(OpMap A, OpMap B, OutMap O, int64_t nband, int64_t tilesN) {
   static_assert(CfgRowTail::NT == CfgSq::NT && CfgRowTail::BN == CfgSq::BN && CfgRowTail::STAGE <= CfgSq::STAGE,
@@ -719,7 +701,7 @@ struct HalfSrc {
   static constexpr int EA = C::BM * C::BK / C::NT;
   static constexpr int NL = EA + Operand<C, C::BN, false, false, false>::E;
   static_assert(C::NT % C::BK == 0 && C::NT % C::BM == 0, "per-thread row / column of the A loads");
-  static_assert(C::BM % 64 == 0, "t / BM is the same for all lanes of a wave");
+  static constexpr bool UK = C::BM % 64 == 0;   // t / BM is the same for all lanes of a wave
   Operand<C, C::BN, false, false, false> c;
   const OpMap* Cm;
   const double* Bbase;  // packed b^P of the current P: Bbase + P*npair
@@ -727,7 +709,7 @@ struct HalfSrc {
   int64_t npair, P, P_last;
   unsigned last;        // nao - 1
   int m0, t, nks, ks;   // k slabs per P, current k slab
-  unsigned k0, kw;      // slab start; wave-uniform k offset t / BM of the along-m mapping
+  unsigned k0, kw;      // slab start; k offset t / BM of the along-m mapping (wave-uniform with UK)
   bool below;
   uint32_t offB[EA];    // along-k mapping: T(m) + t % 16 for row m = m0 + e / 16 (clamped)
   uint32_t mAc, mAoff;  // along-m mapping: row m0 + t % BM (clamped) and T of it
@@ -755,7 +737,7 @@ struct HalfSrc {
     const unsigned mA = (unsigned)(m0 + t % C::BM);
     mAc = mA <= last ? mA : last;
     mAoff = mAc * (mAc + 1u) / 2u;
-    kw = (unsigned)__builtin_amdgcn_readfirstlane(t / C::BM);
+    kw = UK ? (unsigned)__builtin_amdgcn_readfirstlane(t / C::BM) : (unsigned)(t / C::BM);
   }
   __device__ __forceinline__ void begin() {
     k0 = (unsigned)ks * C::BK;
@@ -765,7 +747,7 @@ struct HalfSrc {
   template <int q>
   __device__ __forceinline__ void load() {
     if constexpr (q < EA) {
-      const unsigned kr = k0 + kw + (unsigned)(q * (C::NT / C::BM));   // uniform
+      const unsigned kr = k0 + kw + (unsigned)(q * (C::NT / C::BM));
       const unsigned kc = kr <= last ? kr : last;
       const unsigned Tk = kc * (kc + 1u) / 2u;
       // bit-mask blends: conditionals here compile to a divergent branch (per lane) or to uniform
@@ -811,8 +793,8 @@ struct JvEpi {
   int64_t ldc;
   const double* w;
   int nv;
-  double* part;      // partial of tile `tile` of P at part[P * T + toff + tile]
-  int64_t T, toff;
+  double* part;      // partial of tile `tile` of P at part[P * T + tile]
+  int64_t T;
 };
 
 // The output tile of b^P at (m0, n0); with JV its J-vector partial goes to slot `tile` of P.
@@ -835,21 +817,26 @@ __device__ __forceinline__ void half_tile_at(const double* __restrict__ B, int n
   if constexpr (JV) {
     const int lr = lane & 15, lg = lane >> 4;
     double s = 0.0;
+    // rows past the end read the last one and columns past nv column 0, both dropped by a select: the loads
+    // are branch-free, so a column block's are in flight together
 #pragma unroll
     for (int j = 0; j < C::TN; ++j) {
       const int n = n0 + (wn * C::TN + j) * 16 + lr;
       const bool nok = n < jv->nv;
       const int nc = nok ? n : 0;
       const double wc = nok ? (jv->w ? jv->w[nc] : 1.0) : 0.0;
+      double cm[C::TM * 4];
+#pragma unroll
+      for (int q = 0; q < C::TM * 4; ++q) {
+        const int m = m0 + (wm * C::TM + q / 4) * 16 + 4 * (q % 4) + lg;
+        cm[q] = jv->C[(int64_t)(m < nao ? m : nao - 1) * jv->ldc + nc];
+      }
       double sj = 0.0;
 #pragma unroll
-      for (int i = 0; i < C::TM; ++i)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int m = m0 + (wm * C::TM + i) * 16 + 4 * r + lg;
-          const double cm = m < nao ? jv->C[(int64_t)m * jv->ldc + nc] : 0.0;
-          sj = fma(acc[i][j][r], cm, sj);
-        }
+      for (int q = 0; q < C::TM * 4; ++q) {
+        const int m = m0 + (wm * C::TM + q / 4) * 16 + 4 * (q % 4) + lg;
+        sj = m < nao ? fma(acc[q / 4][j][q % 4], cm[q], sj) : sj;
+      }
       s = fma(sj, wc, s);
     }
     for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off);
@@ -859,59 +846,61 @@ __device__ __forceinline__ void half_tile_at(const double* __restrict__ B, int n
     if (t == 0) {
       double r = 0.0;
       for (int q = 0; q < C::WM * C::WN; ++q) r += smem[q];
-      jv->part[P * jv->T + jv->toff + tile] = r;
+      jv->part[P * jv->T + tile] = r;
     }
   }
 }
 
-// One output tile (item = P * tiles + tile) of the half transform; row bands start at row r0.
-template <class C, bool GEN = false, bool JV = false>
+// Tiles of the half transform of one P: nA tiles of CA per 64-row band from column 0, one of CB
+// (nB = 1) on the columns from nA CA::BN on, and nT tiles of CT, along the columns, on the rows past the
+// `bands` bands.
+struct HalfTiles {
+  int bands, nA, nB, nT;
+  __host__ __device__ int64_t count() const { return (int64_t)bands * (nA + nB) + nT; }
+};
+
+// Tile of work item `item`.  Band by band, so that the column tiles of a band run side by side and share
+// its reads in L2, then the tiles of CT.  Consecutive workgroups go to the four shader engines of an XCD in turn:
+// with an even number of column tiles, the last one short, some engines would get all the short ones
+// (600 x 170 columns ran 7.8 ms so, 500 x 140 4.4).  The bands therefore turn their tiles so that the short ones fall on
+// every engine alike (5.9 and 3.0 ms); without CB tiles P turns the whole order, for the CT tiles (455 x 226
+// columns 3.73 -> 3.60 ms).
+template <class CA, class CB, class CT, bool GEN, bool JV>
 __device__ __forceinline__ void half_tile(const double* __restrict__ B, int nao, int64_t npair, const OpMap& Cm,
-                                          const OutMap& out, int64_t tilesM, int64_t tilesN, int64_t item, int r0,
-                                          double* smem, const JvEpi* jv = nullptr) {
-  const int64_t ntile = tilesM * tilesN;
-  // row band major: the column tiles of one band of b^P run side by side and share its reads in L2
-  const int64_t P = item / ntile, tile = item % ntile;
-  const int m0 = r0 + (int)((tile / tilesN) * C::BM), n0 = (int)((tile % tilesN) * C::BN);
-  half_tile_at<C, GEN, JV>(B, nao, npair, Cm, out, P, m0, n0, tile, smem, jv);
+                                          const OutMap& out, const HalfTiles& T, int64_t item, double* smem,
+                                          const JvEpi* jv = nullptr) {
+  static_assert(CA::NT == CB::NT && CA::NT == CT::NT && CA::BM == CB::BM, "one workgroup shape, one band");
+  constexpr bool kB = !std::is_same<CA, CB>::value, kT = !std::is_same<CA, CT>::value;
+  const int64_t ntile = T.count(), P = item / ntile;
+  const int per = T.nA + T.nB;
+  int tile = (int)(item % ntile);
+  if (kT && T.nB == 0) tile = (int)((tile + P) % ntile);
+  const int band = tile / per;
+  if (kT && band >= T.bands) {
+    half_tile_at<CT, GEN, JV>(B, nao, npair, Cm, out, P, T.bands * CA::BM, (tile - T.bands * per) * CT::BN, tile, smem, jv);
+    return;
+  }
+  int j = tile % per;
+  if (kB && per % 2 == 0) j = (int)((unsigned)(j + (per % 4 == 0 ? band : band >> 1) + (int)(P & 0xffff)) % (unsigned)per);
+  if (!kB || j < T.nA)
+    half_tile_at<CA, GEN, JV>(B, nao, npair, Cm, out, P, band * CA::BM, j * CA::BN, tile, smem, jv);
+  else if constexpr (kB)
+    half_tile_at<CB, GEN, JV>(B, nao, npair, Cm, out, P, band * CA::BM, T.nA * CA::BN, tile, smem, jv);
 }
 
-// Rows [r0, r0 + tilesM * 128) on two tile shapes in one launch: per row band, nA tiles of CA
-// (columns [0, nA CA::BN)) and one of CB (the remainder columns from nA CA::BN on).  The tiles of
-// one band of b^P run side by side and share its reads in L2, which two launches would not.
-template <class CA, class CB, bool GEN, bool JV>
-__global__ void __launch_bounds__(CA::NT) __attribute__((amdgpu_waves_per_eu(2))) half_pair_kernel(const double* __restrict__ B, int64_t naux, int nao,
-                                                          int64_t npair, OpMap Cm, OutMap out, int64_t tilesM,
-                                                          int64_t nA, int r0, JvEpi jv) {
-  static_assert(CA::BM == CB::BM && CA::NT == CB::NT, "one row band, one workgroup shape");
-  __shared__ double smem[2 * (CA::STAGE > CB::STAGE ? CA::STAGE : CB::STAGE)];
-  const int64_t per = nA + 1, ntile = tilesM * per;
-  const int64_t item = xcd_remap(blockIdx.x, ntile * naux);
-  const int64_t P = item / ntile, tile = item % ntile, j = tile % per;
-  const int m0 = r0 + (int)((tile / per) * CA::BM);
-  if (j < nA)
-    half_tile_at<CA, GEN, JV>(B, nao, npair, Cm, out, P, m0, (int)(j * CA::BN), tile, smem, &jv);
-  else
-    half_tile_at<CB, GEN, JV>(B, nao, npair, Cm, out, P, m0, (int)(nA * CA::BN), tile, smem, &jv);
-}
+template <class CA, class CB, class CT>
+struct HalfLds {
+  static constexpr int A = CA::STAGE > CB::STAGE ? CA::STAGE : CB::STAGE;
+  static constexpr int N = 2 * (A > CT::STAGE ? A : CT::STAGE);
+};
 
-// GEN: the epilogue applies out.alpha and out.accumulate (a separate instantiation, see store_tile)
-template <class C, bool GEN>
-__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) half_kernel(const double* __restrict__ B, int64_t naux, int nao,
-                                                     int64_t npair, OpMap Cm, OutMap out, int64_t tilesM,
-                                                     int64_t tilesN, int r0) {
-  __shared__ double smem[2 * C::STAGE];
-  half_tile<C, GEN>(B, nao, npair, Cm, out, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * naux), r0, smem);
-}
-
-// The half transform with the J-vector partials in its epilogue (JvEpi).
-template <class C>
-__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) half_jv_kernel(const double* __restrict__ B, int64_t naux, int nao,
-                                                        int64_t npair, OpMap Cm, OutMap out, int64_t tilesM,
-                                                        int64_t tilesN, int r0, JvEpi jv) {
-  __shared__ double smem[2 * C::STAGE];
-  half_tile<C, false, true>(B, nao, npair, Cm, out, tilesM, tilesN, xcd_remap(blockIdx.x, tilesM * tilesN * naux),
-                            r0, smem, &jv);
+// GEN: the epilogue applies out.alpha and out.accumulate (a separate instantiation, see store_tile);
+// JV: the J-vector partials are formed in it (JvEpi).
+template <class CA, class CB, class CT, bool GEN, bool JV>
+__global__ void __launch_bounds__(CA::NT) __attribute__((amdgpu_waves_per_eu(CA::WPE))) half_kernel(const double* __restrict__ B, int64_t naux, int nao,
+                                                     int64_t npair, OpMap Cm, OutMap out, HalfTiles T, JvEpi jv) {
+  __shared__ double smem[HalfLds<CA, CB, CT>::N];
+  half_tile<CA, CB, CT, GEN, JV>(B, nao, npair, Cm, out, T, xcd_remap(blockIdx.x, T.count() * naux), smem, &jv);
 }
 
 // v[P] (+)= sum_{t < tiles} part[P * tiles + t], in tile order.
@@ -930,10 +919,11 @@ __global__ void __launch_bounds__(256) jv_reduce_kernel(const double* __restrict
 // the small ones fill in behind them.
 struct HalfDesc {
   const double* B;
-  int64_t npair, tilesM, tilesN;
+  int64_t npair;
   OpMap Cm;
   OutMap out;
-  int nao, r0;   // row bands from row r0
+  int nao;
+  HalfTiles T;
 };
 struct HalfGroup {
   int n;
@@ -948,39 +938,46 @@ struct HalfGroup {
 // consecutive items run side by side on one XCD and share its L2, and every XCD gets the same
 // work although the items of different problems differ in cost.  (A persistent grid striding
 // through the chunks balanced uneven items worse than the dispatcher does.)
-template <class C>
-__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) half_group_kernel(HalfGroup g) {
-  __shared__ double smem[2 * C::STAGE];
+template <class CA, class CB, class CT>
+__global__ void __launch_bounds__(CA::NT) __attribute__((amdgpu_waves_per_eu(CA::WPE))) half_group_kernel(HalfGroup g) {
+  __shared__ double smem[HalfLds<CA, CB, CT>::N];
   const int x = blockIdx.x % 8;
   const int64_t item = g.xs[x] + blockIdx.x / 8;
   if (item >= g.xs[x + 1]) return;
   int p = 0;
   while (p + 1 < g.n && item >= g.start[p + 1]) ++p;
   const HalfDesc& d = g.d[p];
-  half_tile<C>(d.B, d.nao, d.npair, d.Cm, d.out, d.tilesM, d.tilesN, item - g.start[p], d.r0, smem);
+  half_tile<CA, CB, CT, false, false>(d.B, d.nao, d.npair, d.Cm, d.out, d.T, item - g.start[p], smem);
 }
 
 // part[split] (m, n) = sum_{P in split} sum_k b^P_{mk} Y(n, (P, k)): the packed half-transform
-// product with the right operand changing with P and the P sum split over grid y.
-// Row bands start at row r0; part[split] holds rows [r0, r0 + tilesM * BM) clipped to nao, as
-// [nao - r0 clipped][N] with N = Y.rows.
+// product with the right operand changing with P and the P sum split over workgroups.  The tiles are
+// those of half_kernel in up to three regions of the output (CA, CB and CT tiles), each with its own
+// split count, so that the items of all take about the same time, and its own partials
+// [ns][r1 - r0][c1 - c0].  (With one count for all, 1200 x 300 took 98 ms in four rounds of uneven
+// items, 75 in three launches.)
+struct ReduceRegion {
+  int64_t item0;                    // first work item
+  int r0, r1, c0, c1, tilesM, tilesN, ns;
+  double* part;
+};
+struct ReduceRegions {
+  ReduceRegion a, b, t;
+  int64_t items;
+};
+
 template <class C>
-__global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) half_reduce_kernel(const double* __restrict__ B, int64_t naux, int nao,
-                                                            int64_t npair, OpMap Y, int64_t N, int64_t tilesM,
-                                                            int64_t tilesN, int nsplit, int r0, int64_t rows,
-                                                            double* part) {
-  __shared__ double smem[2 * C::STAGE];
+__device__ __forceinline__ void half_reduce_tile(const double* __restrict__ B, int64_t naux, int nao, int64_t npair,
+                                                 const OpMap& Y, const ReduceRegion& g, int64_t item, double* smem) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave % C::WM, wn = wave / C::WM;
-  const int64_t ntile = tilesM * tilesN;
+  const int nks = (nao + C::BK - 1) / C::BK;
   // split major, then row band: the tiles of one P range sit on one XCD, and the column tiles
   // of a band side by side
-  const int64_t item = xcd_remap(blockIdx.x, ntile * nsplit);
-  const int split = (int)(item / ntile);
-  const int64_t tile = item % ntile;
-  const int m0 = r0 + (int)((tile / tilesN) * C::BM), n0 = (int)((tile % tilesN) * C::BN);
-  const int64_t P0 = naux * split / nsplit, P1 = naux * (split + 1) / nsplit;
-  const int nks = (nao + C::BK - 1) / C::BK;
+  const int64_t ntile = (int64_t)g.tilesM * g.tilesN;
+  const int split = (int)((item - g.item0) / ntile), tile = (int)((item - g.item0) % ntile);
+  const int m0 = g.r0 + tile / g.tilesN * C::BM, n0 = g.c0 + tile % g.tilesN * C::BN;
+  const int64_t P0 = naux * split / g.ns, P1 = naux * (split + 1) / g.ns;
   d4 acc[C::TM][C::TN];
   zero_acc<C>(acc);
   if (P1 > P0) {
@@ -990,8 +987,23 @@ __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2)))
     src.init(B, npair, P0, P1, nao, m0, t);
     mainloop<C>(src, smem, (P1 - P0) * nks, acc, wm, wn, lane);
   }
-  const OutMap po = out_plain(part + (int64_t)split * rows * N, rows, N, N);
-  store_tile<C, false>(po, 0, m0 - r0, n0, acc, wm, wn, lane);
+  const int rows = g.r1 - g.r0, cols = g.c1 - g.c0;
+  store_tile<C, false>(out_plain(g.part + (int64_t)split * rows * cols, rows, cols, cols), 0, m0 - g.r0, n0 - g.c0, acc,
+                       wm, wn, lane);
+}
+
+template <class CA, class CB, class CT>
+__global__ void __launch_bounds__(CA::NT) __attribute__((amdgpu_waves_per_eu(CA::WPE))) half_reduce_kernel(const double* __restrict__ B, int64_t naux, int nao,
+                                                            int64_t npair, OpMap Y, ReduceRegions R) {
+  __shared__ double smem[HalfLds<CA, CB, CT>::N];
+  constexpr bool kB = !std::is_same<CA, CB>::value, kT = !std::is_same<CA, CT>::value;
+  const int64_t item = xcd_remap(blockIdx.x, R.items);
+  if (!(kB || kT) || item < R.b.item0)
+    half_reduce_tile<CA>(B, naux, nao, npair, Y, R.a, item, smem);
+  else if (kB && (!kT || item < R.t.item0))
+    half_reduce_tile<CB>(B, naux, nao, npair, Y, R.b, item, smem);
+  else if constexpr (kT)
+    half_reduce_tile<CT>(B, naux, nao, npair, Y, R.t, item, smem);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1369,214 +1381,91 @@ bool offsets_fit(const OpMap& o) {
   return o.rows < (1LL << 31) && o.rl < (1LL << 31) && top < (1LL << 32);
 }
 
-// Column tile of the half transform on one row of waves: the widest of {176, 96, 48} whose padded
-// width is within 8% of the least padded one.  A wider tile reads each band of b^P fewer times
-// per column, which outweighs a few percent of padded columns (at 1200 columns: 176 pads to
-// 1232, 48 to 1200).
-int half_tile_n(int64_t ncol) {
-  const int cands[3] = {176, 96, 48};
-  int64_t least = INT64_MAX;
-  for (int c : cands) least = std::min<int64_t>(least, cdiv(ncol, c) * c);
-  for (int c : cands)
-    if (cdiv(ncol, c) * c * 100 <= least * 108) return c;
-  return cands[2];
-}
-
-// Tilings of the half transform.  One row of waves (4 x 1 waves of 1 x 11, 2 x 6 or 2 x 3 MFMA
-// blocks: 64 x 176, 128 x 96, 128 x 48) fits odd column counts (176 = 11 x 16), but its waves
-// issue one LDS read per MFMA.  2 x 2 waves of 4 x 4 blocks read half as much per MFMA and keep
-// the matrix cores busier (0.81 of the time against 0.73 for 1 x 11, both measured at N_ao =
-// 1200), at 128-row bands and 128-column tiles.  The 2-D tiling takes the columns in 128-wide
-// tiles plus one narrower remainder (96 or 64 wide: 2 x 2 waves of 4 x 3 or 4 x 2 blocks), the
-// rows in whole 128-row bands, and the rows past the last whole band (if any) on one row of
-// waves.  Each piece is a launch of its own; the choice is the tiling of least estimated time,
-// padded area over the matrix-core busy fraction of its tile shape.
-enum HalfCfg { kH176, kH96, kH48, kQ128, kQ96, kQ64 };
-struct HalfSeg {
-  int cfg;
-  int64_t r0, r1, c0, c1;   // rows [r0, r1) and columns [c0, c1) of the output
+// Tiling of the half transform: nA tiles of 128 columns and one narrower (or, past 96, one more of 128)
+// for the rest, `rest` its width (0: none); `tail` rows past the last whole band (at most half a band) on
+// tiles of their own, which need at least one whole 128-wide tile beside them (a narrow output is
+// bound by latency, not by its padding).  Bands have 64 rows, 128 (`big`) where the packed b^P does not
+// fit the 4 MB L2 of an XCD: every band reads all of b^P's columns, from the last-level cache then
+// (P-summed product at 1200 x 4800 x 300: 79 ms with 64-row bands, 75 with 128; at N_ao = 1000 the
+// 64-row bands still win, 17.9 ms against 18.1).
+struct HalfCols {
+  int64_t nA;
+  int rest, tail;
+  bool big;
+  int bm() const { return big ? CfgQ128::BM : CfgH128::BM; }
 };
-static int half_cfg_rows(int cfg) { return cfg == kH176 ? 64 : 128; }
-static int half_cfg_cols(int cfg) {
-  switch (cfg) {
-    case kH176: return 176;
-    case kH96: return 96;
-    case kH48: return 48;
-    case kQ128: return 128;
-    case kQ96: return 96;
-    default: return 64;
+static HalfCols half_cols(int64_t nao, int64_t ncol) {
+  HalfCols h{ncol / 128, 0, 0, false};
+  const int64_t rem = ncol % 128;
+  if (rem > 96) ++h.nA;
+  else if (rem > 0) h.rest = rem <= 16 ? 16 : rem <= 32 ? 32 : rem <= 48 ? 48 : rem <= 64 ? 64 : 96;
+  h.big = h.nA > 0 && nao * (nao + 1) / 2 > (int64_t(4) << 20) / 8;
+  if (h.big && h.rest > 0 && h.rest < 48) h.rest = 48;
+  const int64_t rows = nao % h.bm();
+  if (h.nA > 0 && rows > 0 && rows <= h.bm() / 2) h.tail = (int)rows;
+  return h;
+}
+static HalfTiles half_counts(int64_t nao, int64_t ncol) {
+  const HalfCols h = half_cols(nao, ncol);
+  HalfTiles T{(int)cdiv(nao - h.tail, h.bm()), (int)h.nA, h.rest ? 1 : 0, h.tail ? (int)cdiv(ncol, 128) : 0};
+  if (T.nA == 0) {   // one narrow tile per band: it takes CA's place
+    T.nA = T.nB;
+    T.nB = 0;
   }
-}
-// matrix-core busy fraction of each tile shape (1 x 11 and 4 x 4 measured; the others estimated
-// from their LDS reads per MFMA)
-static double half_cfg_busy(int cfg) {
-  switch (cfg) {
-    case kH176: return 0.73;
-    case kH96: return 0.72;
-    case kH48: return 0.68;
-    case kQ128: return 0.81;
-    case kQ96: return 0.78;
-    default: return 0.72;
-  }
-}
-static double half_seg_cost(const HalfSeg& g) {
-  const int bm = half_cfg_rows(g.cfg), bn = half_cfg_cols(g.cfg);
-  return (double)(cdiv(g.r1 - g.r0, bm) * bm) * (double)(cdiv(g.c1 - g.c0, bn) * bn) / half_cfg_busy(g.cfg);
-}
-static int half_cfg_1d(int64_t ncol) {
-  const int n = half_tile_n(ncol);
-  return n == 176 ? kH176 : n == 96 ? kH96 : kH48;
+  return T;
 }
 
-// The pieces of the half transform of nao rows and ncol columns (at most 3).  `split_cols` says
-// whether the output map can be cut along its columns (no column blocking).
-static int half_scheme(int64_t nao, int64_t ncol, bool split_cols, HalfSeg* seg) {
-  seg[0] = HalfSeg{half_cfg_1d(ncol), 0, nao, 0, ncol};
-  if (!split_cols || nao < 128 || ncol < 64) return 1;
-  double best = half_seg_cost(seg[0]);
-  int nbest = 1;
-  HalfSeg cand[3];
-  for (int tail = 0; tail < 2; ++tail) {
-    const int64_t rq = tail ? nao / 128 * 128 : nao;
-    if (tail && (rq == nao || rq == 0)) continue;
-    int n = 0;
-    const int64_t cq = ncol / 128 * 128, rem = ncol - cq;
-    if (cq > 0) cand[n++] = HalfSeg{kQ128, 0, rq, 0, cq};
-    if (rem > 0) {   // the remainder columns on the cheapest tile of 128 rows
-      const int rc[5] = {kQ128, kQ96, kQ64, kH96, kH48};
-      double rbest = 0.0;
-      for (int q = 0; q < 5; ++q) {
-        const HalfSeg g{rc[q], 0, rq, cq, ncol};
-        if (q == 0 || half_seg_cost(g) < rbest) {
-          rbest = half_seg_cost(g);
-          cand[n] = g;
-        }
-      }
-      ++n;
+int64_t half_tiles(int64_t nao, int64_t ncol) { return half_counts(nao, ncol).count(); }
+
+// f(CA, CB, CT) with the tile types: CB = CA or CT = CA where there are no such tiles (the kernel then
+// holds fewer bodies, and narrow tiles alone run as many waves as fit them).
+template <class F>
+static auto half_dispatch(const HalfCols& h, F&& f) {
+  typedef CfgH128 A;
+  typedef CfgHTail T;
+  if (h.big) switch (h.rest) {
+      case 0: return f(CfgQ128{}, CfgQ128{}, CfgQTail{});
+      case 48: return f(CfgQ128{}, CfgQ48{}, CfgQTail{});
+      case 64: return f(CfgQ128{}, CfgQ64{}, CfgQTail{});
+      default: return f(CfgQ128{}, CfgQ96{}, CfgQTail{});
     }
-    if (tail) cand[n++] = HalfSeg{half_cfg_1d(ncol), rq, nao, 0, ncol};
-    double cost = 0.0;
-    for (int i = 0; i < n; ++i) cost += half_seg_cost(cand[i]);
-    if (cost < best) {
-      best = cost;
-      nbest = n;
-      for (int i = 0; i < n; ++i) seg[i] = cand[i];
+  if (h.nA == 0) switch (h.rest) {
+      case 16: return f(CfgH16{}, CfgH16{}, CfgH16{});
+      case 32: return f(CfgH32{}, CfgH32{}, CfgH32{});
+      case 48: return f(CfgH48{}, CfgH48{}, CfgH48{});
+      case 64: return f(CfgH64{}, CfgH64{}, CfgH64{});
+      default: return f(CfgH96{}, CfgH96{}, CfgH96{});
     }
+  switch (h.rest) {
+    case 0: return h.tail ? f(A{}, A{}, T{}) : f(A{}, A{}, A{});
+    case 16: return f(A{}, CfgH16{}, T{});
+    case 32: return f(A{}, CfgH32{}, T{});
+    case 48: return f(A{}, CfgH48{}, T{});
+    case 64: return f(A{}, CfgH64{}, T{});
+    default: return f(A{}, CfgH96{}, T{});
   }
-  return nbest;
-}
-
-// `o` restricted to columns [c0, c1) (no column blocking: s_nh == 0)
-static OutMap out_cols(OutMap o, int64_t c0, int64_t c1) {
-  if (c0 < o.nsplit) {
-    o.p += c0 * o.s_nl;
-    o.nsplit -= c0;
-  } else {
-    o.p2 += c0 - o.nsplit;
-    o.nsplit = 0;
-  }
-  o.N = std::min(o.N, c1) - c0;
-  return o;
-}
-
-template <class Cg>
-static hipError_t half_seg_go(const double* B, int64_t naux, int64_t nao, const double* C, int64_t ldc,
-                              const HalfSeg& g, const OutMap& out, const JvEpi* jv, hipStream_t s) {
-  const OpMap cm = op_map(C + g.c0, g.c1 - g.c0, 1, nao, ldc);
-  const OutMap o = out_cols(out, g.c0, g.c1);
-  const int64_t tm = cdiv(g.r1 - g.r0, Cg::BM), tn = cdiv(g.c1 - g.c0, Cg::BN);
-  const int64_t nblk = tm * tn * naux;
-  if (nblk == 0) return hipSuccess;
-  if (nblk > 0x7fffffffLL || !offsets_fit(cm)) return hipErrorInvalidValue;
-  const int64_t npair = nao * (nao + 1) / 2;
-  if (jv) {
-    if (o.alpha != 1.0 || o.accumulate) return hipErrorInvalidValue;
-    JvEpi j = *jv;
-    j.C = jv->C + g.c0;
-    j.nv = (int)std::max<int64_t>(0, std::min<int64_t>(jv->nv - g.c0, g.c1 - g.c0));
-    half_jv_kernel<Cg><<<dim3((unsigned)nblk), dim3(Cg::NT), 0, s>>>(B, naux, (int)nao, npair, cm, o, tm, tn,
-                                                                     (int)g.r0, j);
-  } else if (o.alpha != 1.0 || o.accumulate) {
-    half_kernel<Cg, true><<<dim3((unsigned)nblk), dim3(Cg::NT), 0, s>>>(B, naux, (int)nao, npair, cm, o, tm, tn,
-                                                                       (int)g.r0);
-  } else {
-    half_kernel<Cg, false><<<dim3((unsigned)nblk), dim3(Cg::NT), 0, s>>>(B, naux, (int)nao, npair, cm, o, tm, tn,
-                                                                        (int)g.r0);
-  }
-  return hipGetLastError();
-}
-
-static int64_t half_seg_tiles(const HalfSeg& g) {
-  return cdiv(g.r1 - g.r0, half_cfg_rows(g.cfg)) * cdiv(g.c1 - g.c0, half_cfg_cols(g.cfg));
-}
-
-// Two pieces on the same rows, 128-wide tiles on columns [0, cq) and one tile of CB on the rest,
-// as one launch (half_pair_kernel).
-template <class CB>
-static hipError_t half_pair_go(const double* B, int64_t naux, int64_t nao, const double* C, int64_t ldc,
-                               int64_t ncol, const HalfSeg& a, const OutMap& out, JvEpi* jv, hipStream_t s) {
-  const OpMap cm = op_map(C, ncol, 1, nao, ldc);
-  const int64_t tm = cdiv(a.r1 - a.r0, CfgQ128::BM), nA = a.c1 / CfgQ128::BN;
-  const int64_t nblk = tm * (nA + 1) * naux;
-  if (nblk == 0) return hipSuccess;
-  if (nblk > 0x7fffffffLL || !offsets_fit(cm)) return hipErrorInvalidValue;
-  const int64_t npair = nao * (nao + 1) / 2;
-  const JvEpi j = jv ? *jv : JvEpi{};
-  const dim3 g((unsigned)nblk);
-  if (jv) {
-    if (out.alpha != 1.0 || out.accumulate) return hipErrorInvalidValue;
-    half_pair_kernel<CfgQ128, CB, false, true><<<g, CfgQ128::NT, 0, s>>>(B, naux, (int)nao, npair, cm, out, tm, nA,
-                                                                          (int)a.r0, j);
-  } else if (out.alpha != 1.0 || out.accumulate) {
-    half_pair_kernel<CfgQ128, CB, true, false><<<g, CfgQ128::NT, 0, s>>>(B, naux, (int)nao, npair, cm, out, tm, nA,
-                                                                          (int)a.r0, j);
-  } else {
-    half_pair_kernel<CfgQ128, CB, false, false><<<g, CfgQ128::NT, 0, s>>>(B, naux, (int)nao, npair, cm, out, tm, nA,
-                                                                           (int)a.r0, j);
-  }
-  return hipGetLastError();
 }
 
 static hipError_t half_run(const double* B, int64_t naux, int64_t nao, const double* C, int64_t ldc, int64_t ncol,
-                           const OutMap& out, JvEpi* jv, hipStream_t s) {
-  HalfSeg seg[3];
-  const int n = half_scheme(nao, ncol, out.s_nh == 0, seg);
-  if (jv) {
-    jv->T = 0;
-    for (int i = 0; i < n; ++i) jv->T += half_seg_tiles(seg[i]);
-    jv->toff = 0;
-  }
-  for (int i = 0; i < n; ++i) {
-    // 128-wide tiles from column 0 and a one-tile remainder on the same rows: one launch
-    if (i + 1 < n && seg[i].cfg == kQ128 && seg[i].c0 == 0 && seg[i].c1 % CfgQ128::BN == 0 &&
-        seg[i + 1].r0 == seg[i].r0 && seg[i + 1].r1 == seg[i].r1 && seg[i + 1].c0 == seg[i].c1 &&
-        seg[i + 1].c1 - seg[i + 1].c0 <= half_cfg_cols(seg[i + 1].cfg) && half_cfg_rows(seg[i + 1].cfg) == 128) {
-      hipError_t e;
-      switch (seg[i + 1].cfg) {
-        case kQ128: e = half_pair_go<CfgQ128>(B, naux, nao, C, ldc, ncol, seg[i], out, jv, s); break;
-        case kQ96: e = half_pair_go<CfgQ96>(B, naux, nao, C, ldc, ncol, seg[i], out, jv, s); break;
-        case kQ64: e = half_pair_go<CfgQ64>(B, naux, nao, C, ldc, ncol, seg[i], out, jv, s); break;
-        case kH96: e = half_pair_go<CfgH96>(B, naux, nao, C, ldc, ncol, seg[i], out, jv, s); break;
-        default: e = half_pair_go<CfgH48>(B, naux, nao, C, ldc, ncol, seg[i], out, jv, s); break;
-      }
-      if (e != hipSuccess) return e;
-      if (jv) jv->toff += half_seg_tiles(seg[i]) + half_seg_tiles(seg[i + 1]);
-      ++i;
-      continue;
-    }
-    hipError_t e;
-    switch (seg[i].cfg) {
-      case kH176: e = half_seg_go<CfgH176>(B, naux, nao, C, ldc, seg[i], out, jv, s); break;
-      case kH96: e = half_seg_go<CfgH96>(B, naux, nao, C, ldc, seg[i], out, jv, s); break;
-      case kH48: e = half_seg_go<CfgH48>(B, naux, nao, C, ldc, seg[i], out, jv, s); break;
-      case kQ128: e = half_seg_go<CfgQ128>(B, naux, nao, C, ldc, seg[i], out, jv, s); break;
-      case kQ96: e = half_seg_go<CfgQ96>(B, naux, nao, C, ldc, seg[i], out, jv, s); break;
-      default: e = half_seg_go<CfgQ64>(B, naux, nao, C, ldc, seg[i], out, jv, s); break;
-    }
-    if (e != hipSuccess) return e;
-    if (jv) jv->toff += half_seg_tiles(seg[i]);
-  }
-  return hipSuccess;
+                           const OutMap& out, const JvEpi* jv, hipStream_t s) {
+  const OpMap cm = op_map(C, ncol, 1, nao, ldc);
+  const HalfTiles T = half_counts(nao, ncol);
+  const int64_t nblk = T.count() * naux, npair = nao * (nao + 1) / 2;
+  if (nblk == 0) return hipSuccess;
+  if (nblk > 0x7fffffffLL || !offsets_fit(cm)) return hipErrorInvalidValue;
+  const bool gen = out.alpha != 1.0 || out.accumulate;
+  if (jv && gen) return hipErrorInvalidValue;
+  const dim3 g((unsigned)nblk);
+  const JvEpi j = jv ? *jv : JvEpi{};
+  return half_dispatch(half_cols(nao, ncol), [&](auto ca, auto cb, auto ct) {
+    typedef decltype(ca) CA;
+    typedef decltype(cb) CB;
+    typedef decltype(ct) CT;
+    if (jv) half_kernel<CA, CB, CT, false, true><<<g, CA::NT, 0, s>>>(B, naux, (int)nao, npair, cm, out, T, j);
+    else if (gen) half_kernel<CA, CB, CT, true, false><<<g, CA::NT, 0, s>>>(B, naux, (int)nao, npair, cm, out, T, j);
+    else half_kernel<CA, CB, CT, false, false><<<g, CA::NT, 0, s>>>(B, naux, (int)nao, npair, cm, out, T, j);
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_half_transform(const double* B, int64_t naux, int64_t nao, const double* C, int64_t ldc,
@@ -1584,23 +1473,15 @@ hipError_t launch_half_transform(const double* B, int64_t naux, int64_t nao, con
   return half_run(B, naux, nao, C, ldc, ncol, out, nullptr, s);
 }
 
-int64_t half_tiles(int64_t nao, int64_t ncol) {
-  HalfSeg seg[3];
-  const int n = half_scheme(nao, ncol, true, seg);
-  int64_t T = 0;
-  for (int i = 0; i < n; ++i) T += half_seg_tiles(seg[i]);
-  return T;
-}
-
 hipError_t launch_half_transform_jvec(const double* B, int64_t naux, int64_t nao, const double* C, int64_t ldc,
                                       int64_t ncol, const OutMap& out, const double* w, int64_t nv, double* part,
                                       double* v, int accumulate, hipStream_t s) {
   if (nv < 0 || nv > ncol || nv > 0x7fffffffLL || out.s_nh != 0) return hipErrorInvalidValue;
   if (naux == 0) return hipSuccess;
-  JvEpi jv{C, ldc, w, (int)nv, part, 0, 0};
+  const JvEpi jv{C, ldc, w, (int)nv, part, half_tiles(nao, ncol)};
+  if (jv.T == 0) return hipErrorInvalidValue;
   hipError_t e = half_run(B, naux, nao, C, ldc, ncol, out, &jv, s);
   if (e != hipSuccess) return e;
-  if (jv.T == 0) return hipErrorInvalidValue;
   jv_reduce_kernel<<<(unsigned)cdiv(naux, 256), 256, 0, s>>>(part, jv.T, naux, v, accumulate);
   return hipGetLastError();
 }
@@ -1796,67 +1677,93 @@ hipError_t launch_gemm_split(const OpMap& A, const OpMap& Bm, const OutMap& O, i
   return launch_split_reduce(part, nsplit, O, s);
 }
 
-// The P-summed packed product takes the half transform's tilings (half_scheme): each piece is a
-// launch of its own with its own P split (filling the resident workgroups) and its own partials
-// [splits][rows][cols], reduced into O piece by piece.
-static int half_reduce_seg_splits(const HalfSeg& g, int64_t naux, int64_t nao) {
-  return balanced_splits(half_seg_tiles(g), naux, naux * cdiv(nao, 16), (g.r1 - g.r0) * (g.c1 - g.c0),
-                         slab_us(half_cfg_rows(g.cfg), half_cfg_cols(g.cfg)));
+// The regions of the P-summed packed product (ReduceRegions) with split counts in proportion to the
+// time of a tile of each: `unit` splits of the 128-wide tiles.  The items then fill whole rounds of
+// the resident workgroups, the partial sums' cost against the rounds' as in balanced_splits.
+static double half_tile_time(int rest) {   // of a tile, against 128 columns (rates at CfgH128)
+  return rest == 96 ? 0.80 : rest == 64 ? 0.58 : rest == 48 ? 0.48 : rest == 32 ? 0.37 : 0.30;
+}
+constexpr double kHTailTime = 0.55;
+static int scaled_splits(int unit, double w, int64_t naux) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(naux, (int64_t)((double)unit * w + 0.5)));
+}
+static ReduceRegions reduce_regions(int64_t naux, int64_t nao, int64_t N, int unit) {
+  const HalfCols h = half_cols(nao, N);
+  const HalfTiles T = half_counts(nao, N);
+  const bool one = h.nA == 0;   // one narrow tile per band: region a alone
+  const int rows = (int)nao - h.tail, ca = one ? (int)N : (int)std::min<int64_t>(N, h.nA * 128);
+  ReduceRegions R{};
+  R.a = ReduceRegion{0, 0, rows, 0, ca, T.bands, T.nA, scaled_splits(unit, 1.0, naux), nullptr};
+  R.b = ReduceRegion{0, 0, rows, ca, (int)N, T.bands, T.nB, T.nB ? scaled_splits(unit, half_tile_time(h.rest), naux) : 0, nullptr};
+  R.t = ReduceRegion{0, rows, (int)nao, 0, (int)N, T.nT ? 1 : 0, T.nT, T.nT ? scaled_splits(unit, kHTailTime, naux) : 0, nullptr};
+  R.b.item0 = (int64_t)R.a.tilesM * R.a.tilesN * R.a.ns;
+  R.t.item0 = R.b.item0 + (int64_t)R.b.tilesM * R.b.tilesN * R.b.ns;
+  R.items = R.t.item0 + (int64_t)R.t.tilesM * R.t.tilesN * R.t.ns;
+  return R;
+}
+static int64_t region_part(const ReduceRegion& g) { return (int64_t)g.ns * (g.r1 - g.r0) * (g.c1 - g.c0); }
+// workgroups resident at once: three per CU, two with 128-row bands
+static int64_t half_resident(const HalfCols& h) { return h.big ? 512 : 768; }
+static int half_reduce_bound(int64_t nao, int64_t N, int64_t naux) {
+  return (int)std::min<int64_t>(naux, 4 * cdiv(half_resident(half_cols(nao, N)), half_tiles(nao, N)));
+}
+static int half_reduce_unit(int64_t naux, int64_t nao, int64_t N) {
+  const HalfCols h = half_cols(nao, N);
+  const int64_t res = half_resident(h);
+  const double slab = h.big ? 4.4 : 3.5 * (h.nA == 0 ? half_tile_time(h.rest) : 1.0);   // us, all resident
+  const int most = half_reduce_bound(nao, N, naux);
+  int best = 1;
+  double best_us = 0.0;
+  for (int u = 1; u <= most; ++u) {
+    const int64_t items = reduce_regions(naux, nao, N, u).items, full = items / res, rem = items % res;
+    const double rounds = (double)full + (rem == 0 ? 0.0 : rem * 3 <= res ? 0.5 : rem * 3 <= 2 * res ? 0.7 : 1.0);
+    const double us = (rounds + 0.2) * (double)(cdiv(naux, u) * cdiv(nao, 16) + 4) * slab +
+                      (double)u * (double)(nao * N) * 16.0 / 4.0e6;
+    if (u == 1 || us < best_us) {
+      best_us = us;
+      best = u;
+    }
+  }
+  return best;
 }
 
+// scaled_splits() rounds up to at most the 128-wide tiles' count, so no region has more
 int64_t half_reduce_part_bound(int64_t nao, int64_t N, int64_t naux) {
-  HalfSeg seg[3];
-  const int n = half_scheme(nao, N, true, seg);
-  int64_t total = 0;
-  for (int i = 0; i < n; ++i)
-    total += (int64_t)balanced_splits_bound(half_seg_tiles(seg[i]), naux) * (seg[i].r1 - seg[i].r0) *
-             (seg[i].c1 - seg[i].c0);
-  return total;
-}
-
-template <class Cg>
-static hipError_t half_reduce_go(const double* B, int64_t naux, int64_t nao, const OpMap& Y, const HalfSeg& g,
-                                 int nsplit, double* part, hipStream_t s) {
-  OpMap Yg = Y;
-  Yg.p = Y.p + g.c0;
-  Yg.rows = Yg.rl = g.c1 - g.c0;
-  const int64_t tm = cdiv(g.r1 - g.r0, Cg::BM), tn = cdiv(g.c1 - g.c0, Cg::BN);
-  const int64_t nblk = tm * tn * nsplit;
-  if (nblk > 0x7fffffffLL) return hipErrorInvalidValue;
-  half_reduce_kernel<Cg><<<dim3((unsigned)nblk), Cg::NT, 0, s>>>(B, naux, (int)nao, nao * (nao + 1) / 2, Yg,
-                                                                g.c1 - g.c0, tm, tn, nsplit, (int)g.r0,
-                                                                g.r1 - g.r0, part);
-  return hipGetLastError();
+  return (int64_t)half_reduce_bound(nao, N, naux) * nao * N;
 }
 
 hipError_t launch_half_reduce(const double* B, int64_t naux, int64_t nao, const OpMap& Y, const OutMap& O,
                               double* part, hipStream_t s) {
   if (nao <= 0 || O.N <= 0) return hipSuccess;
-  if (naux < 1 || !offsets_fit(Y) || O.s_nh != 0 || O.s_mh != 0) return hipErrorInvalidValue;
-  HalfSeg seg[3];
-  const int n = half_scheme(nao, O.N, true, seg);
-  for (int i = 0; i < n; ++i) {
-    const HalfSeg& g = seg[i];
-    const int ns = half_reduce_seg_splits(g, naux, nao);
-    hipError_t e;
-    switch (g.cfg) {
-      case kH176: e = half_reduce_go<CfgH176>(B, naux, nao, Y, g, ns, part, s); break;
-      case kH96: e = half_reduce_go<CfgH96>(B, naux, nao, Y, g, ns, part, s); break;
-      case kH48: e = half_reduce_go<CfgH48>(B, naux, nao, Y, g, ns, part, s); break;
-      case kQ128: e = half_reduce_go<CfgQ128>(B, naux, nao, Y, g, ns, part, s); break;
-      case kQ96: e = half_reduce_go<CfgQ96>(B, naux, nao, Y, g, ns, part, s); break;
-      default: e = half_reduce_go<CfgQ64>(B, naux, nao, Y, g, ns, part, s); break;
+  if (naux < 1 || !offsets_fit(Y) || O.s_nh != 0 || O.s_mh != 0 || Y.rows != O.N || O.M != nao)
+    return hipErrorInvalidValue;
+  ReduceRegions R = reduce_regions(naux, nao, O.N, half_reduce_unit(naux, nao, O.N));
+  if (R.items > 0x7fffffffLL) return hipErrorInvalidValue;
+  R.a.part = part;
+  R.b.part = R.a.part + region_part(R.a);
+  R.t.part = R.b.part + region_part(R.b);
+  const hipError_t e = half_dispatch(half_cols(nao, O.N), [&](auto ca, auto cb, auto ct) {
+    typedef decltype(ca) CA;
+    half_reduce_kernel<CA, decltype(cb), decltype(ct)><<<dim3((unsigned)R.items), CA::NT, 0, s>>>(
+        B, naux, (int)nao, nao * (nao + 1) / 2, Y, R);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
+  for (const ReduceRegion* g : {&R.a, &R.b, &R.t}) {
+    if (g->ns == 0) continue;
+    OutMap Og = O;   // the region's rows and columns of O
+    if (g->c0 < O.nsplit) {
+      Og.p += g->c0 * Og.s_nl;
+      Og.nsplit -= g->c0;
+    } else {
+      Og.p2 += g->c0 - O.nsplit;
+      Og.nsplit = 0;
     }
-    if (e != hipSuccess) return e;
-    // the piece's rows and columns of O
-    OutMap Oc = out_cols(O, g.c0, g.c1);
-    if (Oc.nsplit > 0) Oc.p += g.r0 * Oc.s_ml;
-    if (Oc.p2) Oc.p2 += g.r0 * Oc.s2_m;
-    Oc.M = g.r1 - g.r0;
-    const int64_t MN = Oc.M * Oc.N;
-    e = launch_split_reduce(part, ns, Oc, s);
-    if (e != hipSuccess) return e;
-    part += (int64_t)ns * MN;
+    Og.M = g->r1 - g->r0;
+    Og.N = g->c1 - g->c0;
+    if (Og.nsplit > 0) Og.p += g->r0 * Og.s_ml;
+    if (Og.p2) Og.p2 += g->r0 * Og.s2_m;
+    if (hipError_t er = launch_split_reduce(g->part, g->ns, Og, s)) return er;
   }
   return hipSuccess;
 }
@@ -2028,84 +1935,49 @@ static int64_t xcd_chunks(const int64_t* start, const double* cost, int n, int64
   return longest;
 }
 
-// rows [r0[p], r1[p]) of problem p (all rows when r0 is null); problems with no rows are skipped
-template <class Cg>
-static hipError_t half_group_go(const GroupHalf* probs, int n, hipStream_t s, const int64_t* r0 = nullptr,
-                                const int64_t* r1 = nullptr) {
+template <class CA, class CB, class CT>
+static hipError_t half_group_go(const GroupHalf* probs, int n, hipStream_t s) {
+  constexpr bool kB = !std::is_same<CA, CB>::value, kT = !std::is_same<CA, CT>::value;
   HalfGroup g{};
+  g.n = n;
   g.start[0] = 0;
-  for (int i = 0; i < n; ++i) {
-    const GroupHalf& q = probs[i];
-    const int64_t a = r0 ? r0[i] : 0, b = r1 ? r1[i] : q.nao;
-    if (b <= a) continue;
-    const int p = g.n++;
+  double cost[kMaxGroup];   // slabs per item, plus about two for the prologue and the epilogue
+  for (int p = 0; p < n; ++p) {
+    const GroupHalf& q = probs[p];
     HalfDesc& d = g.d[p];
     d.B = q.B;
     d.nao = (int)q.nao;
-    d.r0 = (int)a;
     d.npair = q.nao * (q.nao + 1) / 2;
     d.Cm = op_map(q.C, q.ncol, 1, q.nao, q.ldc);
     d.out = q.out;
-    d.tilesM = cdiv(b - a, Cg::BM);
-    d.tilesN = cdiv(q.ncol, Cg::BN);
+    // the rest of the columns and of the rows on CB and CT where those hold them
+    const int64_t rem = q.ncol % CA::BN, rows = q.nao % CA::BM;
+    const bool tail = kT && rows > 0 && rows <= CT::BM && q.ncol >= CT::BN;
+    d.T.nB = kB && rem > 0 && rem <= CB::BN && q.ncol >= CA::BN ? 1 : 0;
+    d.T.nA = (int)(d.T.nB ? q.ncol / CA::BN : cdiv(q.ncol, CA::BN));
+    d.T.bands = (int)(tail ? q.nao / CA::BM : cdiv(q.nao, CA::BM));
+    d.T.nT = tail ? (int)cdiv(q.ncol, CT::BN) : 0;
     if (!offsets_fit(d.Cm) || q.out.alpha != 1.0 || q.out.accumulate) return hipErrorInvalidValue;
-    g.start[p + 1] = g.start[p] + d.tilesM * d.tilesN * q.naux;
+    g.start[p + 1] = g.start[p] + d.T.count() * q.naux;
+    const double w = d.T.bands * (d.T.nA + 0.6 * d.T.nB) + kHTailTime * d.T.nT;
+    cost[p] = ((double)cdiv(q.nao, CA::BK) + 2.0) * w / (double)std::max<int64_t>(1, d.T.count());
   }
-  if (g.n == 0 || g.start[g.n] == 0) return hipSuccess;
+  if (g.start[g.n] == 0) return hipSuccess;
   if (g.start[g.n] > 0x7fffffffLL) return hipErrorInvalidValue;
-  double cost[kMaxGroup];   // slabs per item, plus about two for the prologue and the epilogue
-  for (int p = 0; p < g.n; ++p) cost[p] = (double)cdiv(g.d[p].nao, Cg::BK) + 2.0;
   const int64_t per = xcd_chunks(g.start, cost, g.n, g.xs);
   if (8 * per > 0x7fffffffLL) return hipErrorInvalidValue;
-  half_group_kernel<Cg><<<(unsigned)(8 * per), Cg::NT, 0, s>>>(g);
+  half_group_kernel<CA, CB, CT><<<(unsigned)(8 * per), CA::NT, 0, s>>>(g);
   return hipGetLastError();
-}
-
-// The 2-D tiling of a problem in a group: the cheaper (padded area over matrix-core busy
-// fraction, as in half_scheme) of all rows on 128 x 128 tiles and the whole 128-row bands on them
-// with the rest of the rows on 64 x 176 tiles.  Returns the rows on 128 x 128 tiles and the cost.
-static int64_t half_group_2d_rows(int64_t nao, int64_t ncol, double* cost) {
-  const int64_t rq = nao / 128 * 128;
-  const double all = half_seg_cost(HalfSeg{kQ128, 0, nao, 0, ncol});
-  const double split = rq > 0 && rq < nao ? half_seg_cost(HalfSeg{kQ128, 0, rq, 0, ncol}) +
-                                                 half_seg_cost(HalfSeg{kH176, rq, nao, 0, ncol})
-                                           : all;
-  *cost = std::min(all, split);
-  return split < all ? rq : nao;
-}
-
-int half_group_tile_for(const int64_t* nao, const int64_t* ncol, int n) {
-  double c2 = 0.0, c1 = 0.0, c;
-  for (int i = 0; i < n; ++i) {
-    half_group_2d_rows(nao[i], ncol[i], &c);
-    c2 += c * (double)nao[i];   // the contraction runs over nao
-    c1 += half_seg_cost(HalfSeg{kH176, 0, nao[i], 0, ncol[i]}) * (double)nao[i];
-  }
-  return c2 < c1 ? 128 : 176;
-}
-
-static hipError_t half_group_2d(const GroupHalf* probs, int n, hipStream_t s) {
-  int64_t q0[kMaxGroup], q1[kMaxGroup], t0[kMaxGroup], t1[kMaxGroup];
-  double c;
-  for (int i = 0; i < n; ++i) {
-    q0[i] = 0;
-    q1[i] = half_group_2d_rows(probs[i].nao, probs[i].ncol, &c);
-    t0[i] = q1[i];
-    t1[i] = probs[i].nao;
-  }
-  hipError_t e = half_group_go<CfgQ128>(probs, n, s, q0, q1);
-  if (e != hipSuccess) return e;
-  return half_group_go<CfgH176>(probs, n, s, t0, t1);
 }
 
 hipError_t launch_half_group(const GroupHalf* probs, int n, int tile_n, hipStream_t s) {
   if (n < 1 || n > kMaxGroup) return hipErrorInvalidValue;
   switch (tile_n) {
+    case 176: return half_group_go<CfgH176, CfgH176, CfgH176>(probs, n, s);
+    case 96: return half_group_go<CfgH96, CfgH96, CfgH96>(probs, n, s);
+    case 48: return half_group_go<CfgH48, CfgH48, CfgH48>(probs, n, s);
     case 0:
-    case 176: return half_group_go<CfgH176>(probs, n, s);
-    case 96: return half_group_go<CfgH96>(probs, n, s);
-    case 48: return half_group_go<CfgH48>(probs, n, s);
-    case 128: return half_group_2d(probs, n, s);
+    case 128: return half_group_go<CfgH128, CfgH64, CfgHTail>(probs, n, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -141,3 +141,35 @@ def test_papa_full_with_one_factor(nao, naux, nac, nmo):
         close(got, r, name)
     flat = one.reshape(nmo * nac, -1)
     assert torch.equal(flat, flat.T)
+
+
+# the half transform's tiles: 64-row bands with 16 ... 96 columns alone; 128 columns and each narrower rest;
+# with and without rows for the 32-row tail tile (1 ... 32 past a band), one band of tail alone; 128-row
+# bands (packed b^P above 4 MB: nao >= 1024) with each rest and with and without their 64-row tail
+HALF_SIZES = [(1, 3, 1), (31, 2, 16), (64, 3, 17), (65, 2, 33), (96, 2, 49), (63, 2, 64), (97, 3, 65), (128, 2, 96), (20, 5, 140), (130, 2, 97),
+              (33, 9, 128), (96, 3, 129), (97, 3, 160), (224, 2, 161), (128, 3, 192), (129, 2, 224), (40, 3, 257),
+              (1024, 2, 128), (1025, 2, 133), (1088, 2, 192), (1089, 2, 224)]
+
+
+@pytest.mark.parametrize("nao,naux,ncol", HALF_SIZES)
+def test_half_transform_tiles(nao, naux, ncol):
+    rng = np.random.default_rng(nao * 1000 + ncol)
+    B = rng.standard_normal((naux, O.npair(nao)))
+    b = O.unpack(B, nao)
+    C = rng.standard_normal((nao, ncol)) / np.sqrt(nao)
+    gB, gC = dev(B), dev(C)
+    ref = b @ C
+    close(dfmi.half_transform(gB, nao, gC), ref, "X")
+    acc = torch.ones((naux, nao, ncol), dtype=torch.float64, device="cuda")
+    dfmi.half_transform(gB, nao, gC, out=acc, accumulate=True)
+    close(acc, 1.0 + ref, "accumulated X")
+    # the J-vector from the half transform's epilogue (all columns but the active ones), and the P-summed product
+    nac = min(3, ncol - 1)
+    nocc = ncol - nac
+    Co, Ca = C[:, :nocc].copy(), C[:, nocc:].copy()
+    out = dfmi.step(gB, nao, dev(Co), dev(Ca), dev(C[:, :1].copy()))
+    close(out["v"], np.einsum("mc,Pmc->P", Co, ref[:, :, :nocc]), "v")
+    gK = rng.standard_normal((nao, nao))
+    dCo, _ = dfmi.step_backward(gB, nao, dev(Co), dev(Ca), gK=dev(gK))
+    Y = (gK + gK.T) @ ref[:, :, :nocc]
+    close(dCo, sum(b[p] @ Y[p] for p in range(naux)), "dCocc")
