@@ -618,7 +618,11 @@ std::vector<int> batched_k_splits_max(const df_problem* probs, int n) {
 }
 
 BatchedTune batched_default_tune(const df_problem* probs, int n) {
-  return BatchedTune{kHalfTiles[0], batched_default_k_tile(probs, n), kKRounds[0]};
+  // a group of so few workgroups that they run in one round either way keeps the widest column tile
+  int64_t few = 0;
+  for (int i = 0; i < n; ++i)
+    few += (probs[i].nao + 63) / 64 * ((batched_ncol(probs[i]) + 175) / 176) * probs[i].naux;
+  return BatchedTune{few <= 256 ? 176 : kHalfTiles[0], batched_default_k_tile(probs, n), kKRounds[0]};
 }
 
 // The shape of a problem group: what the work and hence the best configuration depend on.
@@ -1091,7 +1095,7 @@ df_status run_k(df_ctx* c, const double* X, const double* w, int64_t naux, int64
   Bw.ks = w;
   Bw.s_ksz = nocc;
   DF_LAUNCH(DF_KERNEL_K_SYRK, dfk::launch_syrk_partial(A, Bw, nao, nz, nsplit, kpart, c->stream), "K tiles launch");
-  DF_LAUNCH(DF_KERNEL_K_REDUCE, dfk::launch_syrk_reduce(kpart, nsplit, nao, nz, K, c->stream, accumulate),
+  DF_LAUNCH(DF_KERNEL_K_REDUCE, dfk::launch_syrk_partial_reduce(kpart, nsplit, naux, nao, nz, K, c->stream, accumulate),
             "K reduce launch");
   return DF_OK;
 }
@@ -2885,7 +2889,7 @@ static df_status split_problem_run(df_ctx* c, char* ws, const df_problem& q, con
     A.s_z = q.nocc;
     double* kpart = (double*)(ws + b.kpart);
     DF_LAUNCH(DF_KERNEL_K_SYRK, dfk::launch_syrk_partial(A, A, nao, q.ndm, b.nsk, kpart, c->stream), "K tiles launch");
-    DF_LAUNCH(DF_KERNEL_K_REDUCE, dfk::launch_syrk_reduce(kpart, b.nsk, nao, q.ndm, q.K, c->stream),
+    DF_LAUNCH(DF_KERNEL_K_REDUCE, dfk::launch_syrk_partial_reduce(kpart, b.nsk, naux, nao, q.ndm, q.K, c->stream),
               "K reduce launch");
   } else if (q.K && q.nocc > 0) {
     // rows m of each density's X_occ over (P, i), then K_z = sum_{P, i} X[P][m][z i] X[P][n][z i]

@@ -114,21 +114,24 @@ hipError_t launch_jvec_packed(const double* B, int64_t naux, int64_t nao, const 
 // out[z] = in[z] + in[z]^T for nz square n x n matrices (out may equal in)
 hipError_t launch_symmetrize(const double* in, int64_t n, int64_t nz, double* out, hipStream_t s);
 
-// Lower-tile SYRK with a split over kb: Kpart[split][z][i][j] = sum_{kb in split, kc} A(i,(kb,kc)) Bw(j,(kb,kc))
-// for tile(i) >= tile(j) (Bw = A with an optional per-kc weight).  Kpart is dense [nsplit][nz][n][n];
-// syrk_splits() gives the number of splits the workspace is planned for.
+// Lower-tile SYRK with a split of the contraction: Kpart[split][z][i][j] = sum_{kb in split, kc} A(i,(kb,kc)) Bw(j,(kb,kc))
+// for the tiles of the lower triangle (Bw = A with an optional per-kc weight).  Kpart is dense
+// [nsplit][nz][n][n]; syrk_splits() gives the number of splits the workspace is planned for (tiles
+// smaller than the largest take fewer).
 int syrk_splits(int64_t n, int64_t kb_n, int64_t kc_n, int64_t nz);
 // The most splits syrk_splits(n, k, kc_n, nz) gives for any k <= kb_n.
 int syrk_splits_bound(int64_t n, int64_t kb_n, int64_t nz);
-// SYRK tile edge for an n x n result (64 up to n = 640, else 128); a group uses the edge of its
-// largest member.
-int syrk_tile_for(int64_t n);
 hipError_t launch_syrk_partial(const OpMap& A, const OpMap& Bw, int64_t n, int64_t nz, int nsplit,
                                double* Kpart, hipStream_t s);
-// K[z][i][j] = sum_s Kpart[s][z][max(i,j)][min(i,j)]; both triangles written (added to K
-// when `accumulate`).
+// K[z][i][j] = sum_s Kpart[s][z][max(i,j)][min(i,j)] from launch_syrk_partial's partials of a contraction
+// over kb_n blocks; both triangles written (added to K when `accumulate`).
+hipError_t launch_syrk_partial_reduce(const double* Kpart, int nsplit, int64_t kb_n, int64_t n, int64_t nz, double* K,
+                                      hipStream_t s, int accumulate = 0);
+// The same where every tile has all nsplit partials.
 hipError_t launch_syrk_reduce(const double* Kpart, int nsplit, int64_t n, int64_t nz, double* K,
                               hipStream_t s, int accumulate = 0);
+// Tile edge of a grouped SYRK whose largest result is n x n (64 up to n = 640, else 128).
+int syrk_tile_for(int64_t n);
 
 // G(m, n) = sum_k A(m, k) A(n, k), M x M (M = A.rows), both triangles written (added to when
 // `accumulate`) from the lower tiles; A with its rows along lanes (s_rlo == 1).  part: scratch of
@@ -191,7 +194,7 @@ struct GroupHalf {
 // tile_n: column tile of the launch (64-row bands), 176, 96, 48 or 128 (0 = 128; the columns past the
 // last whole tile of 128 on one of 64 where it holds them).
 hipError_t launch_half_group(const GroupHalf* probs, int n, int tile_n, hipStream_t s);
-// Lower-tile SYRK partials of problem p: as launch_syrk_partial with (A, A, n, nz, nsplit, Kpart).
+// Lower-tile SYRK partials of problem p on square tiles, all with nsplit splits (for launch_syrk_reduce).
 struct GroupSyrk {
   OpMap A;
   int64_t n, nz;

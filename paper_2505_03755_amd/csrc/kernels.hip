@@ -52,8 +52,13 @@ typedef Cfg<4, 2, 4, 4> CfgTall;
 typedef Cfg<2, 2, 4, 4> CfgSyrk;
 // small products: 64 x 64 tiles, four workgroups per CU
 typedef Cfg<2, 2, 2, 2> CfgSmall;
-// small matrices (fragment sizes): 64 x 64 SYRK tiles pad the triangle less
+// small matrices (fragment sizes): 64 x 64 SYRK tiles pad the triangle less (grouped launches)
 typedef Cfg<2, 2, 2, 2> CfgSyrk64;
+// K SYRK of one call: 64-row bands on 64 x 128 tiles, 64 x 64 where a band's columns end half way, the last rows
+// (at most 32) on 32 x 128 (SyrkTiles); all three workgroups per CU
+typedef Cfg<2, 2, 2, 4, 3> CfgKA;
+typedef Cfg<2, 2, 2, 2, 3> CfgKD;
+typedef Cfg<1, 4, 2, 2, 3> CfgKT;
 // half transform: 64-row bands on tiles of 128 columns (three workgroups per CU), the columns past the
 // last whole one on one tile of 96, 64, 48, 32 or 16.  At N_ao = 512 (2048 rows of P, columns that fill
 // the tile) 128 columns run at 57.9 TF/s, as fast as 128 x 128 tiles (58.5) and with half the rows
@@ -583,26 +588,16 @@ __global__ void __launch_bounds__(256) expand_pairs_kernel(const double* __restr
 }
 
 // ---------------------------------------------------------------------------------------
-// Lower-triangle tile SYRK with the kb range split over workgroups:
-// Kpart[split][z] tile (I, J), I >= J, = sum_{kb in split} sum_kc A(i, kb, kc) Bw(j, kb, kc),
-// where Bw is A times an optional per-kc weight.
-// One (tile pair, split) item of density z.  FLAT: the contraction (kb, kc) runs as one flat
+// Lower-triangle tile SYRK with the contraction split over workgroups: one (tile, split) item of density z,
+//   Kpart[split][z] tile (m0, n0) = sum_{kb in split} sum_kc A(i, kb, kc) Bw(j, kb, kc),
+// where Bw is A times an optional per-kc weight.  FLAT: the contraction (kb, kc) runs as one flat
 // index in slabs of 16 (see Operand) and the flat slabs are split evenly, so no kb block is padded
 // to whole slabs; otherwise the kb range is split and each block padded.
-template <class C, bool SCALE, bool CLAMP, bool FLAT = false>
-__device__ __forceinline__ void syrk_tile(const OpMap& A, const OpMap& Bw, int64_t n, int64_t nz, int nsplit,
-                                          int64_t npairs, double* Kpart, int64_t item, int64_t z, double* smem) {
-  static_assert(C::BM == C::BN, "square tiles");
+template <class C, bool SCALE, bool CLAMP, bool FLAT>
+__device__ __forceinline__ void syrk_run(const OpMap& A, const OpMap& Bw, int64_t n, int64_t nz, int nsplit,
+                                         int split, int64_t m0, int64_t n0, double* Kpart, int64_t z, double* smem) {
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int wm = wave % C::WM, wn = wave / C::WM;
-  const int64_t pair = item % npairs;
-  const int split = (int)(item / npairs);
-  // triangular decode: pair = I(I+1)/2 + J, 0 <= J <= I
-  int64_t I = (int64_t)((sqrt(8.0 * (double)pair + 1.0) - 1.0) * 0.5);
-  while (I * (I + 1) / 2 > pair) --I;
-  while ((I + 1) * (I + 2) / 2 <= pair) ++I;
-  const int64_t J = pair - I * (I + 1) / 2;
-  const int64_t m0 = I * C::BM, n0 = J * C::BN;
   int64_t s_lo, s_hi;   // slabs of this split
   if constexpr (FLAT) {
     const int64_t S = (A.kb_n * A.kc_n + C::BK - 1) / C::BK;
@@ -630,16 +625,48 @@ __device__ __forceinline__ void syrk_tile(const OpMap& A, const OpMap& Bw, int64
   store_tile<C, false>(o, 0, m0, n0, acc, wm, wn, lane);
 }
 
-template <class C, bool SCALE, bool CLAMP, bool FLAT = false>
-__global__ void __launch_bounds__(C::NT) syrk_kernel(OpMap A, OpMap Bw, int64_t n, int64_t nz, int nsplit,
-                                                     int64_t npairs, double* Kpart) {
-  __shared__ double smem[2 * C::STAGE];
-  syrk_tile<C, SCALE, CLAMP, FLAT>(A, Bw, n, nz, nsplit, npairs, Kpart, xcd_remap(blockIdx.x, npairs * nsplit),
-                                   blockIdx.z, smem);
+// Tiles of the lower triangle of an n x n SYRK, and their splits of the contraction.  Band i of `bands` 64-row
+// bands needs columns 0 ... 64 (i + 1): (i + 1) / 2 tiles of 64 x 128 (A) and, in even bands, one of
+// 64 x 64 on the diagonal (D); the rows past the bands take tiles of 32 x 128 (T).  Each kind has its own split
+// count, in proportion to the time of its tiles, so that all work items take about as long.  Bound by the
+// matrix cores (0.7 busy) and the padding of the triangle.  Against square tiles of 64 (128 past n = 640): K at
+// 341 x 1365 x 85 0.41 -> 0.38 ms, 600 x 2400 x 150 3.30 -> 3.03, 700 x 1400 x 128 1.91 -> 1.52, 1200 x 1200 x 300
+// 10.5 -> 9.8.  (One split count for all kinds was faster at 600, 2.90, and slower at 240, 0.139 against 0.113,
+// and 1200, 10.9; 128 x 128 tiles with 64-row tails 2.98 at 600 and 1.69 at 700.)
+struct SyrkTiles {
+  int bands;              // 0: every element has na partials (launch_syrk_reduce)
+  int a, d, t;            // tiles of each kind
+  int na, nd, nt;         // splits of each kind
+  __host__ __device__ int64_t items() const { return (int64_t)a * na + (int64_t)d * nd + (int64_t)t * nt; }
+};
+
+// Items: the A tiles of split 0, of split 1, ..., then the D tiles so, then the T tiles.
+template <bool SCALE, bool CLAMP, bool FLAT>
+__global__ void __launch_bounds__(CfgKA::NT) __attribute__((amdgpu_waves_per_eu(CfgKA::WPE))) syrk_kernel(OpMap A, OpMap Bw, int64_t n, int64_t nz, SyrkTiles T,
+                                                     double* Kpart) {
+  static_assert(CfgKD::STAGE <= CfgKA::STAGE && CfgKT::STAGE <= CfgKA::STAGE, "the A tile's LDS holds the others");
+  __shared__ double smem[2 * CfgKA::STAGE];
+  const int64_t item = xcd_remap(blockIdx.x, T.items()), z = blockIdx.z;
+  const int64_t na = (int64_t)T.a * T.na, nad = na + (int64_t)T.d * T.nd;
+  if (item < na) {
+    const int q = (int)(item % T.a);
+    int i = (int)(2.0f * sqrtf((float)q));   // i^2 / 4 A tiles lie in the bands before band i
+    while (i * i / 4 > q) --i;
+    while ((i + 1) * (i + 1) / 4 <= q) ++i;
+    syrk_run<CfgKA, SCALE, CLAMP, FLAT>(A, Bw, n, nz, T.na, (int)(item / T.a), (int64_t)i * CfgKA::BM,
+                                        (int64_t)(q - i * i / 4) * CfgKA::BN, Kpart, z, smem);
+  } else if (item < nad) {
+    const int64_t m0 = (item - na) % T.d * 2 * CfgKD::BM;
+    syrk_run<CfgKD, SCALE, CLAMP, FLAT>(A, Bw, n, nz, T.nd, (int)((item - na) / T.d), m0, m0, Kpart, z, smem);
+  } else {
+    syrk_run<CfgKT, SCALE, CLAMP, FLAT>(A, Bw, n, nz, T.nt, (int)((item - nad) / T.t), (int64_t)T.bands * CfgKA::BM,
+                                        (item - nad) % T.t * CfgKT::BN, Kpart, z, smem);
+  }
 }
 
-// Grouped K SYRK: problem p owns items [start[p], start[p + 1]) = (density z, split, tile pair),
-// z outermost; unit weights.
+// Grouped K SYRK on square tiles (64 x 64 at fragment sizes: four workgroups per CU and a batch's X, much
+// larger than the caches, read once; 92.5 ms for the 64-density fragments against 97 on SyrkTiles):
+// problem p owns items [start[p], start[p + 1]) = (density z, split, tile pair), z outermost; unit weights.
 struct SyrkDesc {
   OpMap A;
   int64_t n, nz, npairs;
@@ -664,19 +691,29 @@ __global__ void __launch_bounds__(C::NT) syrk_group_kernel(SyrkGroup g) {
   while (p + 1 < g.n && it >= g.start[p + 1]) ++p;
   const SyrkDesc& d = g.d[p];
   const int64_t item = it - g.start[p], per_z = d.npairs * d.nsplit;
-  syrk_tile<C, false, CLAMP, FLAT>(d.A, d.A, d.n, d.nz, d.nsplit, d.npairs, d.Kpart, item % per_z, item / per_z,
-                                   smem);
+  const int64_t in_z = item % per_z;
+  int64_t I, J;
+  pair_ij(in_z % d.npairs, &I, &J);
+  syrk_run<C, false, CLAMP, FLAT>(d.A, d.A, d.n, d.nz, d.nsplit, (int)(in_z / d.npairs), I * C::BM, J * C::BN, d.Kpart,
+                                  item / per_z, smem);
 }
 
-// K[z][i][j] and K[z][j][i] (+)= sum_s Kpart[s][z][i][j] for the lower pairs i >= j, G threads each.
+// K[z][i][j] and K[z][j][i] (+)= sum_s Kpart[s][z][i][j] for the lower pairs i >= j, G threads each, over
+// the splits of the pair's tile (SyrkTiles).
 template <int G>
-__global__ void __launch_bounds__(kRedThreads) syrk_reduce_kernel(const double* __restrict__ Kpart, int nsplit,
+__global__ void __launch_bounds__(kRedThreads) syrk_reduce_kernel(const double* __restrict__ Kpart, SyrkTiles T,
                                                                   int64_t n, int64_t npair, double* __restrict__ K,
                                                                   int accumulate) {
   constexpr int W = kRedThreads / G;
   const int64_t p = (int64_t)blockIdx.x * W + threadIdx.x % W, z = blockIdx.y, nz = gridDim.y, nn = n * n;
   int64_t i = 0, j = 0;
   if (p < npair) pair_ij(p, &i, &j);
+  int nsplit = T.na;
+  if (T.bands > 0) {
+    const int band = (int)(i / CfgKA::BM);
+    if (band >= T.bands) nsplit = T.nt;
+    else if (band % 2 == 0 && j >= (int64_t)band * CfgKA::BM) nsplit = T.nd;
+  }
   const double s = split_sum<G>(Kpart + z * nn + i * n + j, nsplit, nz * nn, p < npair);
   if (threadIdx.x >= W || p >= npair) return;
   double* a = K + z * nn + i * n + j;
@@ -1869,42 +1906,62 @@ hipError_t launch_gram(const OpMap& A, double* G, double* part, int64_t part_n, 
 
 int syrk_tile_for(int64_t n) { return n <= 640 ? CfgSyrk64::BM : CfgSyrk::BM; }
 
+// Tiles of an n x n SYRK with `unit` splits of the 64 x 128 tiles; a 64 x 64 tile takes 0.58 and a 32 x 128
+// one 0.55 of their time (rates at CfgH128).
+static SyrkTiles syrk_tiles(int64_t n, int64_t kb_n, int unit) {
+  SyrkTiles T{};
+  const int64_t rows = n % CfgKA::BM, tail = n > CfgKA::BM && rows > 0 && rows <= CfgKT::BM ? rows : 0;
+  T.bands = (int)cdiv(n - tail, CfgKA::BM);
+  T.a = T.bands * T.bands / 4;
+  T.d = (T.bands + 1) / 2;
+  T.t = tail ? (int)cdiv(n, CfgKT::BN) : 0;
+  T.na = unit;
+  T.nd = scaled_splits(unit, 0.58, kb_n);
+  T.nt = T.t ? scaled_splits(unit, 0.55, kb_n) : 0;
+  return T;
+}
+
+static int64_t syrk_most(int64_t n, int64_t kb_n, int64_t nz) {
+  const int64_t tiles = syrk_tiles(n, 1, 1).items() * std::max<int64_t>(nz, 1);
+  return std::max<int64_t>(1, std::min<int64_t>({kb_n, 4096, 4 * cdiv(768, tiles)}));
+}
+int syrk_splits_bound(int64_t n, int64_t kb_n, int64_t nz) { return (int)syrk_most(n, kb_n, nz); }
+
+// Splits of least estimated time, as in half_reduce_unit: three workgroups per CU, 3.5 us a slab of a 64 x 128 tile
+// (two 2.4, one 1.6); partial sums of the triangle written and read.
 int syrk_splits(int64_t n, int64_t kb_n, int64_t kc_n, int64_t nz) {
-  const int64_t tile = syrk_tile_for(n), T = cdiv(n, tile);
   if (nz < 1) nz = 1;
-  return balanced_splits(T * (T + 1) / 2 * nz, kb_n, cdiv(kb_n * kc_n, 16), n * (n + 1) / 2 * nz, slab_us(tile, tile));
-}
-
-int syrk_splits_bound(int64_t n, int64_t kb_n, int64_t nz) {
-  const int64_t T = cdiv(n, syrk_tile_for(n));
-  return balanced_splits_bound(T * (T + 1) / 2 * (nz > 0 ? nz : 1), kb_n < 4096 ? kb_n : 4096);
-}
-
-template <class Cg>
-static hipError_t syrk_go(const OpMap& A, const OpMap& Bw, int64_t n, int64_t nz, int nsplit, double* Kpart,
-                          hipStream_t s) {
-  const int64_t T = cdiv(n, Cg::BM);
-  const int64_t npairs = T * (T + 1) / 2;
-  if (npairs == 0 || nz == 0) return hipSuccess;
-  if (nz > 65535 || !offsets_fit(A)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)(npairs * nsplit), 1, (unsigned)nz);
-  const bool clamp = A.kc_n % 16 != 0;
-  // contraction chunks that are not whole slabs: one flat contraction (no padded slabs) unless
-  // weighted or shorter than a slab
-  const bool flat = clamp && !Bw.ks && flat_pays(A) && flat_fits(A);
-  // weighted: the clamping loader in every case (without it the weighted 128-wide tiles need more
-  // than 256 registers per lane and run one wave per SIMD)
-  if (Bw.ks) syrk_kernel<Cg, true, true><<<grid, Cg::NT, 0, s>>>(A, Bw, n, nz, nsplit, npairs, Kpart);
-  else if (flat) syrk_kernel<Cg, false, false, true><<<grid, Cg::NT, 0, s>>>(A, Bw, n, nz, nsplit, npairs, Kpart);
-  else if (clamp) syrk_kernel<Cg, false, true><<<grid, Cg::NT, 0, s>>>(A, Bw, n, nz, nsplit, npairs, Kpart);
-  else syrk_kernel<Cg, false, false><<<grid, Cg::NT, 0, s>>>(A, Bw, n, nz, nsplit, npairs, Kpart);
-  return hipGetLastError();
+  const int64_t most = syrk_most(n, kb_n, nz), slabs = cdiv(kb_n * kc_n, 16);
+  int best = 1;
+  double best_us = 0.0;
+  for (int u = 1; u <= most; ++u) {
+    const int64_t w = syrk_tiles(n, kb_n, u).items() * nz, full = w / 768, rem = w % 768;
+    const double last = rem == 0 ? 0.0 : rem <= 256 ? 1.6 : rem <= 512 ? 2.4 : 3.5;
+    const double us = ((double)full * 3.5 + last + 0.7) * (double)(cdiv(slabs, u) + 4) +
+                      (double)u * (double)(n * (n + 1) / 2 * nz) * 16.0 / 4.0e6;
+    if (u == 1 || us < best_us * (1.0 - 1e-9)) {
+      best_us = us;
+      best = u;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_syrk_partial(const OpMap& A, const OpMap& Bw, int64_t n, int64_t nz, int nsplit, double* Kpart,
                                hipStream_t s) {
-  return syrk_tile_for(n) == CfgSyrk64::BM ? syrk_go<CfgSyrk64>(A, Bw, n, nz, nsplit, Kpart, s)
-                                           : syrk_go<CfgSyrk>(A, Bw, n, nz, nsplit, Kpart, s);
+  if (n == 0 || nz == 0) return hipSuccess;
+  const SyrkTiles T = syrk_tiles(n, A.kb_n, nsplit);
+  if (nz > 65535 || !offsets_fit(A) || T.items() > 0x7fffffffLL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)T.items(), 1, (unsigned)nz);
+  const bool clamp = A.kc_n % 16 != 0;
+  // contraction chunks that are not whole slabs: one flat contraction (no padded slabs) unless
+  // weighted or shorter than a slab
+  const bool flat = clamp && !Bw.ks && flat_pays(A) && flat_fits(A);
+  if (Bw.ks) syrk_kernel<true, true, false><<<grid, CfgKA::NT, 0, s>>>(A, Bw, n, nz, T, Kpart);
+  else if (flat) syrk_kernel<false, false, true><<<grid, CfgKA::NT, 0, s>>>(A, Bw, n, nz, T, Kpart);
+  else if (clamp) syrk_kernel<false, true, false><<<grid, CfgKA::NT, 0, s>>>(A, Bw, n, nz, T, Kpart);
+  else syrk_kernel<false, false, false><<<grid, CfgKA::NT, 0, s>>>(A, Bw, n, nz, T, Kpart);
+  return hipGetLastError();
 }
 
 // ---- grouped launches ----
@@ -2037,16 +2094,28 @@ hipError_t launch_syrk_group(const GroupSyrk* probs, int n, int tile, hipStream_
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_syrk_reduce(const double* Kpart, int nsplit, int64_t n, int64_t nz, double* K, hipStream_t s,
-                              int accumulate) {
+static hipError_t syrk_reduce_go(const double* Kpart, const SyrkTiles& T, int64_t n, int64_t nz, double* K,
+                                 hipStream_t s, int accumulate) {
   const int64_t npair = n * (n + 1) / 2;
   if (npair == 0 || nz == 0) return hipSuccess;
   if (nz > 65535) return hipErrorInvalidValue;
-  const int g = red_group(nsplit);
+  const int g = red_group(T.na);
   const dim3 grid((unsigned)cdiv(npair, kRedThreads / g), (unsigned)nz);
-  if (g == 8) syrk_reduce_kernel<8><<<grid, kRedThreads, 0, s>>>(Kpart, nsplit, n, npair, K, accumulate);
-  else syrk_reduce_kernel<1><<<grid, kRedThreads, 0, s>>>(Kpart, nsplit, n, npair, K, accumulate);
+  if (g == 8) syrk_reduce_kernel<8><<<grid, kRedThreads, 0, s>>>(Kpart, T, n, npair, K, accumulate);
+  else syrk_reduce_kernel<1><<<grid, kRedThreads, 0, s>>>(Kpart, T, n, npair, K, accumulate);
   return hipGetLastError();
+}
+
+hipError_t launch_syrk_reduce(const double* Kpart, int nsplit, int64_t n, int64_t nz, double* K, hipStream_t s,
+                              int accumulate) {
+  SyrkTiles T{};
+  T.na = nsplit;
+  return syrk_reduce_go(Kpart, T, n, nz, K, s, accumulate);
+}
+
+hipError_t launch_syrk_partial_reduce(const double* Kpart, int nsplit, int64_t kb_n, int64_t n, int64_t nz, double* K,
+                                      hipStream_t s, int accumulate) {
+  return syrk_reduce_go(Kpart, syrk_tiles(n, kb_n, nsplit), n, nz, K, s, accumulate);
 }
 
 hipError_t launch_jvec(const double* X, int64_t naux, int64_t nao, int64_t ldx, const double* C, const double* w,

@@ -173,3 +173,24 @@ def test_half_transform_tiles(nao, naux, ncol):
     dCo, _ = dfmi.step_backward(gB, nao, dev(Co), dev(Ca), gK=dev(gK))
     Y = (gK + gK.T) @ ref[:, :, :nocc]
     close(dCo, sum(b[p] @ Y[p] for p in range(naux)), "dCocc")
+
+
+# K's triangle: one diagonal tile; with 1, 13 and 32 rows of tail; two, three and four bands (the last one partial);
+# contractions of whole slabs, with a remainder (flat), and shorter than one; weighted and not
+@pytest.mark.parametrize("nao,nocc", [(1, 1), (64, 16), (65, 20), (77, 19), (96, 5), (97, 32), (128, 17), (160, 33), (191, 16), (200, 21), (256, 3), (290, 40)])
+def test_k_triangle_tiles(nao, nocc):
+    rng = np.random.default_rng(nao * 100 + nocc)
+    naux, ndm = 37, 2
+    B = rng.standard_normal((naux, O.npair(nao)))
+    C = rng.standard_normal((ndm, nao, nocc)) / np.sqrt(nao)
+    w = rng.standard_normal((ndm, nocc))
+    for wt in (None, w):
+        J, K, _ = dfmi.jk(dev(B), nao, dev(C), w=None if wt is None else dev(wt))
+        for z in range(ndm):
+            Jr, Kr, _ = O.jk(B, nao, C[z], None if wt is None else wt[z])
+            close(K[z], Kr, f"K[{z}]")
+            assert torch.equal(K[z], K[z].T)
+    pr = [{"B": dev(B), "nao": nao, "Cocc": dev(C), "Cact": dev(C[0, :, :1]), "Cp": dev(C[0, :, :1])}] * 2
+    for o in dfmi.batched_step(pr):
+        for z in range(ndm):
+            close(o["K"][z], O.jk(B, nao, C[z], None)[1], f"batched K[{z}]")
