@@ -175,19 +175,17 @@ PpaaPlan plan_ppaa(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int64_t nq)
   return p;
 }
 
-// Workspace of df_build_cholesky: the inverted diagonal blocks of L, a panel of the factorisation
-// and one block row of the substitution.
+// Workspace of df_build_cholesky: the inverted diagonal blocks of L and a panel of the factorisation.
 struct BuildPlan {
-  size_t linv, panel, t;
+  size_t linv, panel;
   int64_t nblk;
 };
-BuildPlan plan_build(Plan& pl, int64_t naux, int64_t nao) {
+BuildPlan plan_build(Plan& pl, int64_t naux) {
   BuildPlan p{};
-  const int64_t nb = dfk::kCholNB, npair = nao * (nao + 1) / 2;
+  const int64_t nb = dfk::kCholNB;
   p.nblk = (naux + nb - 1) / nb;
   p.linv = pl.take(p.nblk * nb * nb);
   p.panel = pl.take(naux * nb);
-  p.t = pl.take(nb * npair);
   return p;
 }
 
@@ -1282,7 +1280,7 @@ df_status workspace_bytes(df_op op, const df_dims* d, size_t limit, size_t* byte
       break;
     case DF_OP_ACTIVE_ERI: plan_act(pl, d->naux, d->nao, d->nac, d->flags, d->nslice); break;
     case DF_OP_PAPA: plan_papa(pl, d->naux, d->nao, d->nac, d->np, d->nq, d->flags, d->nslice); break;
-    case DF_OP_BUILD_CHOLESKY: plan_build(pl, d->naux, d->nao); break;
+    case DF_OP_BUILD_CHOLESKY: plan_build(pl, d->naux); break;
     case DF_OP_EMBED_CHOLESKY: plan_embed(pl, d->naux, d->nao, d->ncol); break;
     case DF_OP_PPAA:
       plan_ppaa(pl, d->naux, d->nao, d->nac, d->nq > 0 ? d->nq : d->np);
@@ -1885,7 +1883,7 @@ df_status df_build_cholesky(df_ctx* ctx, const double* metric, const double* eri
                            {B, dbytes(naux * npair), "B", true},
                            {info, sizeof(int), "info", true}};
   Plan pl;
-  const BuildPlan p = plan_build(pl, naux, nao);
+  const BuildPlan p = plan_build(pl, naux);
   if (!check_overlap(c, rs)) return DF_ERR_ARG;
   if (df_status s = need_ws(c, pl.total)) return s;
   rs.push_back({c->ws, pl.total, "workspace", true});
@@ -1893,7 +1891,6 @@ df_status df_build_cholesky(df_ctx* ctx, const double* metric, const double* eri
   if (df_status s = enter(c)) return s;
   double* linv = (double*)(c->ws + p.linv);
   double* panel = (double*)(c->ws + p.panel);
-  double* T = (double*)(c->ws + p.t);
   const int64_t n = naux;
   if (L != metric)
     DF_LAUNCH(DF_KERNEL_OTHER, hipMemcpyAsync(L, metric, dbytes(n * n), hipMemcpyDeviceToDevice, c->stream),
@@ -1927,27 +1924,9 @@ df_status df_build_cholesky(df_ctx* ctx, const double* metric, const double* eri
   // forward substitution by block rows: B_k = L_kk^-1 (E_k - L_{k,<k} B_{<k})
   for (int64_t k = 0; k < p.nblk; ++k) {
     const int64_t k0 = k * nb, kb = std::min(nb, n - k0);
-    DF_LAUNCH(DF_KERNEL_OTHER,
-              hipMemcpyAsync(T, eri3 + k0 * npair, dbytes(kb * npair), hipMemcpyDeviceToDevice, c->stream),
-              "block row copy");
-    if (k0 > 0) {
-      // the contraction over the k earlier (full) blocks, one 64-bit-strided slab per block
-      dfk::OpMap A = dfk::op_map(L + k0 * n, kb, n, nb, 1);
-      A.kb_n = k;
-      A.s_kb = nb;
-      dfk::OpMap Bm = dfk::op_map(B, npair, 1, nb, npair);
-      Bm.kb_n = k;
-      Bm.s_kb = nb * npair;
-      dfk::OutMap O = dfk::out_plain(T, kb, npair, npair);
-      O.alpha = -1.0;
-      O.accumulate = 1;
-      DF_LAUNCH(DF_KERNEL_BUILD, dfk::launch_gemm(A, Bm, O, 1, c->stream), "substitution update launch");
-    }
-    const dfk::OpMap A = dfk::op_map(linv + k * nb * nb, kb, nb, kb, 1);
-    const dfk::OpMap Bm = dfk::op_map(T, npair, 1, kb, npair);
     DF_LAUNCH(DF_KERNEL_BUILD,
-              dfk::launch_gemm(A, Bm, dfk::out_plain(B + k0 * npair, kb, npair, npair), 1, c->stream),
-              "block solve launch");
+              dfk::launch_subst_row(L + k0 * n, n, k, eri3 + k0 * npair, linv + k * nb * nb, (int)kb, npair, B, c->stream),
+              "substitution launch");
   }
   return DF_OK;
 }

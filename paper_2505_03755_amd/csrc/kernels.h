@@ -172,6 +172,11 @@ constexpr int kCholNB = 128;
 // unless an earlier one is recorded.  One workgroup.
 hipError_t launch_chol_block(double* A, int64_t lda, int kb, double* Linv, int* info, int64_t k0, bool first,
                              hipStream_t s);
+// Rows [128 k, 128 k + kb) of B (row length npair) by forward substitution: Linv (E - sum_{j < k} L_j B_j) with L the
+// kb rows of the factor (row stride ldl), E the same rows of the right side (they may be B's own) and Linv
+// from launch_chol_block; rows [0, 128 k) of B are there.
+hipError_t launch_subst_row(const double* L, int64_t ldl, int64_t k, const double* E, const double* Linv, int kb,
+                            int64_t npair, double* B, hipStream_t s);
 // A[i][j] = 0 for j > i (n x n, row major)
 hipError_t launch_zero_upper(double* A, int64_t n, hipStream_t s);
 // Ap[z][pair(i, j)] = A[z][i][j] for i >= j: the lower triangles of nz n x n matrices (s_z doubles

@@ -1311,66 +1311,213 @@ __global__ void __launch_bounds__(256) pack_lower_kernel(const double* __restric
 
 // Cholesky factor of one kb x kb diagonal block (kb <= kCholNB) of the metric, in LDS, and the
 // inverse of that factor.  A (row stride lda) holds the block with the earlier blocks' updates
-// already subtracted; its lower triangle is read.  Right-looking elimination: column j is scaled
-// by 1 / sqrt(pivot), then the trailing lower triangle takes the rank-1 update.  The inverse is
-// then found one column per thread by forward substitution: thread c keeps column c of L^-1 in
-// row c of the LDS array (the upper triangle, which the factor does not use), and reads the
-// factor from the strictly lower triangle and the diagonal from dg.  Outputs: the factor back to
+// already subtracted; its lower triangle is read (rows past kb are those of the identity).
+// Right-looking over 16-wide blocks: one wave factors the diagonal block and inverts it, a row
+// (a column of the inverse) per lane, the other lanes' values by readlane; the blocks below take its
+// inverse and the trailing blocks their update on the matrix cores.  The inverse follows by block columns, two
+// per wave, no barrier between: X_ij = -Linv_ii sum_{k=j}^{i-1} L_ik X_kj, kept in the upper blocks of S; the sum
+// leaves the matrix cores in the very layout in which the product with Linv_ii reads its right
+// operand.  One workgroup, so bound by latency: a column at a time (128 columns, three barriers each, and a
+// serial substitution for the inverse) took 331 us, so 81.  Outputs: the factor back to
 // A (lower, the block's strictly upper part zeroed) and L^-1 to Linv [kCholNB][kCholNB] (lower,
 // upper zeroed).  info: the first block (first != 0) writes 0; a block that meets a pivot that
 // is not positive writes k0 + j + 1 unless info already holds an earlier one.  After such a
 // pivot the block goes on with pivot 1 so that every wave finishes.
+__device__ __forceinline__ double lane_value(double x, int lane) {   // lane: uniform
+  const long long b = __double_as_longlong(x);
+  const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)b, lane);
+  const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
 __global__ void __launch_bounds__(256) chol_block_kernel(double* __restrict__ A, int64_t lda, int kb,
                                                          double* __restrict__ Linv, int* info, int64_t k0,
                                                          int first) {
-  __shared__ double S[kCholNB][kCholNB + 1];
-  __shared__ double dg[kCholNB];
+  constexpr int N = kCholNB, NB = N / 16, LS = N + 1;
+  __shared__ double S[N][LS];
+  __shared__ double D[NB][16][17];   // inverses of the diagonal blocks
   __shared__ int bad;
-  const int t = threadIdx.x;
-  for (int idx = t; idx < kb * kb; idx += 256) {
-    const int i = idx / kb, j = idx % kb;
-    S[i][j] = j <= i ? A[i * lda + j] : 0.0;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, lr = lane & 15, lk = lane >> 4;
+  for (int idx = t; idx < N * N; idx += 256) {
+    const int i = idx / N, j = idx % N;
+    S[i][j] = i < kb ? (j <= i ? A[i * lda + j] : 0.0) : (i == j ? 1.0 : 0.0);
   }
   if (t == 0) bad = -1;
   __syncthreads();
-  for (int j = 0; j < kb; ++j) {
-    const double d = S[j][j];
-    const double sd = d > 0.0 ? sqrt(d) : 1.0;
-    const double r = 1.0 / sd;
-    __syncthreads();
-    if (t == 0) {
-      if (!(d > 0.0) && bad < 0) bad = j;
-      dg[j] = sd;
+  for (int p = 0; p < NB; ++p) {
+    const int o = p * 16;
+    if (wave == 0) {
+      // lane l < 16 holds row l of the block (the other lanes copies, never stored)
+      double a[16], x[16], rd[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) a[c] = S[o + lr][o + c];
+      int b = -1;
+#pragma unroll
+      for (int j = 0; j < 16; ++j) {
+        const double d = lane_value(a[j], j);
+        const bool ok = d > 0.0;
+        if (!ok && b < 0) b = o + j;
+        const double sd = ok ? sqrt(d) : 1.0;
+        rd[j] = 1.0 / sd;
+        a[j] = lr == j ? sd : a[j] * rd[j];
+#pragma unroll
+        for (int c = j + 1; c < 16; ++c) a[c] -= a[j] * lane_value(a[j], c);
+      }
+      // column lr of the inverse: L x = e_lr
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        double v = i == lr ? 1.0 : 0.0;
+#pragma unroll
+        for (int j = 0; j < i; ++j) v -= lane_value(a[j], i) * x[j];
+        x[i] = v * rd[i];
+      }
+      if (lane < 16) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c) {
+          S[o + lr][o + c] = c <= lr ? a[c] : 0.0;
+          D[p][c][lr] = c >= lr ? x[c] : 0.0;
+        }
+        if (lane == 0 && b >= 0 && bad < 0) bad = b;
+      }
     }
-    for (int i = j + 1 + t; i < kb; i += 256) S[i][j] *= r;
     __syncthreads();
-    // trailing lower triangle: lane t % 64 takes columns c = j + 1 + (t % 64) + 64 q, the four
-    // wave-groups t / 64 take every fourth row i >= c
-    for (int c = j + 1 + (t & 63); c < kb; c += 64) {
-      const double lc = S[c][j];
-      for (int i = c + (t >> 6); i < kb; i += 4) S[i][c] -= S[i][j] * lc;
+    // the blocks below: L_rp = A_rp Linv_pp^T
+    for (int r = p + 1 + wave; r < NB; r += 4) {
+      d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kk = 0; kk < 16; kk += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(S[r * 16 + lr][o + kk + lk], D[p][lr][kk + lk], acc, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[r * 16 + 4 * q + lk][o + lr] = acc[q];
+    }
+    __syncthreads();
+    // trailing blocks (r >= c > p): A_rc -= L_rp L_cp^T
+    const int m = NB - 1 - p;
+    for (int w = wave; w < m * (m + 1) / 2; w += 4) {
+      int r = 0;
+      while ((r + 1) * (r + 2) / 2 <= w) ++r;
+      const int rb = (p + 1 + r) * 16, cb = (p + 1 + w - r * (r + 1) / 2) * 16;
+      d4 acc;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) acc[q] = S[rb + 4 * q + lk][cb + lr];
+#pragma unroll
+      for (int kk = 0; kk < 16; kk += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(-S[rb + lr][o + kk + lk], S[cb + lr][o + kk + lk], acc, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[rb + 4 * q + lk][cb + lr] = acc[q];
     }
     __syncthreads();
   }
-  if (t < kb) {
-    const int c = t;
-    S[c][c] = 1.0 / dg[c];
-    for (int i = c + 1; i < kb; ++i) {
-      double acc = 0.0;
-      for (int j = c; j < i; ++j) acc += S[i][j] * S[c][j];
-      S[c][i] = -acc / dg[i];
+  // block columns wave and NB - 1 - wave of the inverse; X_ij (i > j) at rows 16 j, columns 16 i of S, which the
+  // factor does not use and no other wave reads
+  for (int h = 0; h < 2; ++h) {
+    const int j = h == 0 ? wave : NB - 1 - wave;
+    for (int i = j + 1; i < NB; ++i) {
+      d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int kk = 0; kk < 16; kk += 4)
+        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(S[i * 16 + lr][j * 16 + kk + lk], D[j][kk + lk][lr], acc, 0, 0, 0);
+      for (int k = j + 1; k < i; ++k)
+#pragma unroll
+        for (int kk = 0; kk < 16; kk += 4)
+          acc = __builtin_amdgcn_mfma_f64_16x16x4f64(S[i * 16 + lr][k * 16 + kk + lk], S[j * 16 + kk + lk][k * 16 + lr],
+                                                     acc, 0, 0, 0);
+      d4 x = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        x = __builtin_amdgcn_mfma_f64_16x16x4f64(-D[i][lr][4 * q + lk], acc[q], x, 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) S[j * 16 + 4 * q + lk][i * 16 + lr] = x[q];
     }
   }
   __syncthreads();
   for (int idx = t; idx < kb * kb; idx += 256) {
-    const int i = idx / kb, j = idx % kb;
-    A[i * lda + j] = j < i ? S[i][j] : (j == i ? dg[i] : 0.0);
-    Linv[i * kCholNB + j] = j <= i ? S[j][i] : 0.0;
+    const int i = idx / kb, j = idx % kb, bi = i / 16, bj = j / 16;
+    A[i * lda + j] = j <= i ? S[i][j] : 0.0;
+    Linv[i * N + j] = j > i ? 0.0 : bi == bj ? D[bi][i % 16][j % 16] : S[bj * 16 + i % 16][bi * 16 + j % 16];
   }
   if (t == 0) {
     int cur = first ? 0 : *info;
     if (cur == 0 && bad >= 0) cur = (int)(k0 + bad + 1);
     *info = cur;
+  }
+}
+
+// One block row of the forward substitution:  B_k = Linv_k (E_k - sum_{j < k} L_kj B_j)  for 128 columns per
+// workgroup.  Waves side by side (1 x 4), so that a wave holds all kb <= 128 rows of its 32 columns of
+// T = E_k - sum: the accumulators then have the layout in which the product with Linv_k reads
+// its right operand, and T never leaves the registers.  Linv_k goes through LDS in two halves
+// of 64 rows; its zero upper part is skipped.  Bound by the matrix cores (49 TF/s; 1409 workgroups a block row
+// at 2400 x 180300 fill 2.75 rounds).  As a copy of E_k, a product that subtracts from it and a product with
+// Linv_k the substitution took 25.7 ms there, so 22.0.
+typedef Cfg<1, 4, 8, 2> CfgSub;
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) subst_row_kernel(OpMap A, OpMap B, int64_t nslab, const double* E,
+                                                          const double* __restrict__ Linv, int kb, int64_t npair,
+                                                          double* out) {
+  typedef CfgSub C;
+  static_assert(C::BM == kCholNB && C::TM == 8, "a wave holds every row");
+  constexpr int LS = kCholNB + 1;
+  static_assert(64 * LS <= 2 * C::STAGE, "half of Linv in the LDS of the main loop");
+  __shared__ double smem[2 * C::STAGE];
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, lr = lane & 15, lk = lane >> 4;
+  const int64_t n0 = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * C::BN;
+  d4 acc[C::TM][C::TN];
+  zero_acc<C>(acc);
+  if (nslab > 0) {
+    PairSrc<C, true, false, false, false> src;
+    src.A = &A;
+    src.B = &B;
+    src.t = t;
+    src.a.init(A, 0, 0, 0, nslab, t);
+    src.b.init(B, n0, 0, 0, nslab, t);
+    mainloop<C>(src, smem, nslab, acc, 0, wave, lane);
+  }
+  int64_t col[C::TN], colc[C::TN];
+#pragma unroll
+  for (int j = 0; j < C::TN; ++j) {
+    col[j] = n0 + (wave * C::TN + j) * 16 + lr;
+    colc[j] = col[j] < npair ? col[j] : npair - 1;
+  }
+#pragma unroll
+  for (int i = 0; i < C::TM; ++i)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int m = i * 16 + 4 * q + lk;
+#pragma unroll
+      for (int j = 0; j < C::TN; ++j) {
+        const double e = E[(int64_t)(m < kb ? m : kb - 1) * npair + colc[j]];
+        acc[i][j][q] = m < kb ? e - acc[i][j][q] : 0.0;
+      }
+    }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    __syncthreads();   // the last reads of what is overwritten are done
+    for (int idx = t; idx < 64 * kCholNB; idx += 256) {
+      const int r = 64 * h + idx / kCholNB, k = idx % kCholNB;
+      smem[(idx / kCholNB) * LS + k] = r < kb && k < kb ? Linv[r * kCholNB + k] : 0.0;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i4 = 0; i4 < 4; ++i4) {
+      const int i = 4 * h + i4;
+      d4 x[C::TN];
+#pragma unroll
+      for (int j = 0; j < C::TN; ++j) x[j] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int k = 0; k <= i; ++k)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const double a = smem[(i4 * 16 + lr) * LS + k * 16 + 4 * q + lk];
+#pragma unroll
+          for (int j = 0; j < C::TN; ++j) x[j] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, acc[k][j][q], x[j], 0, 0, 0);
+        }
+#pragma unroll
+      for (int j = 0; j < C::TN; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int m = i * 16 + 4 * q + lk;
+          if (m < kb && col[j] < npair) out[(int64_t)m * npair + col[j]] = x[j][q];
+        }
+    }
   }
 }
 
@@ -2213,6 +2360,23 @@ hipError_t launch_chol_block(double* A, int64_t lda, int kb, double* Linv, int* 
                              hipStream_t s) {
   if (kb < 1 || kb > kCholNB) return hipErrorInvalidValue;
   chol_block_kernel<<<1, 256, 0, s>>>(A, lda, kb, Linv, info, k0, first ? 1 : 0);
+  return hipGetLastError();
+}
+
+hipError_t launch_subst_row(const double* L, int64_t ldl, int64_t k, const double* E, const double* Linv, int kb,
+                            int64_t npair, double* B, hipStream_t s) {
+  if (kb < 1 || kb > kCholNB || npair < 1) return hipErrorInvalidValue;
+  // the contraction over the k earlier (full) blocks, one 64-bit-strided block of B each
+  OpMap A = op_map(L, kb, ldl, kCholNB, 1);
+  A.kb_n = k;
+  A.s_kb = kCholNB;
+  OpMap Bm = op_map(B, npair, 1, kCholNB, npair);
+  Bm.kb_n = k;
+  Bm.s_kb = kCholNB * npair;
+  const int64_t nblk = cdiv(npair, CfgSub::BN);
+  if (nblk > 0x7fffffffLL || !offsets_fit(A) || !offsets_fit(Bm)) return hipErrorInvalidValue;
+  subst_row_kernel<<<(unsigned)nblk, CfgSub::NT, 0, s>>>(A, Bm, k * (kCholNB / CfgSub::BK), E, Linv, kb, npair,
+                                                         B + k * kCholNB * npair);
   return hipGetLastError();
 }
 

@@ -124,3 +124,28 @@ def test_build_paper_scale_sampled_pairs():
     assert rel(B[:, cols], OB.cholesky_vectors(metric, Es)) <= TOL
     del L, B, E
     torch.cuda.empty_cache()
+
+
+# 16-wide blocks of the diagonal factor (15 ... 17, 113), a last block of 1 and of 16 rows, columns of B around
+# the 128-wide tile (120, 136, 253 pairs); in place too
+@pytest.mark.parametrize("naux,nao", [(15, 15), (16, 16), (17, 22), (113, 15), (144, 16), (257, 22), (273, 1)])
+def test_build_block_edges(naux, nao):
+    metric = synth.coulomb_metric(naux, 1e4, seed=naux)
+    E = synth.cholesky_vectors(naux, nao, 10.0, seed=naux + 1)
+    m2, e2 = dev(metric), dev(E)
+    for L, B, info in (dfmi.build_cholesky(dev(metric), dev(E), nao), dfmi.build_cholesky(m2, e2, nao, in_place=True)):
+        assert int(info.item()) == 0
+        assert rel(L, OB.metric_cholesky(metric)) <= TOL
+        assert rel(B, OB.cholesky_vectors(metric, E)) <= TOL
+        assert not torch.triu(L, 1).any()
+
+
+@pytest.mark.parametrize("pivot", [0, 15, 16, 37, 127, 128, 150])
+def test_first_bad_pivot_in_each_block(pivot):
+    naux = 151
+    metric = np.eye(naux)
+    metric[pivot, pivot] = -1.0
+    if pivot + 1 < naux:
+        metric[naux - 1, naux - 1] = 0.0
+    _, _, info = dfmi.build_cholesky(dev(metric), dev(np.ones((naux, 1))), 1, check=False)
+    assert int(info.item()) == pivot + 1
