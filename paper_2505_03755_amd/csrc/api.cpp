@@ -918,39 +918,20 @@ size_t dbytes(int64_t n) { return (size_t)std::max<int64_t>(n, 0) * sizeof(doubl
 // ---- building blocks on the device ----
 
 // T_P = b^P C (ncol columns of C, row stride ldc), written through `out` with z = P
-// A block of columns of the dense half-transform operand: src [nao][ncols] (row stride ld) goes to
-// columns [col0, col0 + ncols).
-struct ColBlock {
-  const double* src;
-  int64_t ld, ncols, col0;
-};
+// One block of columns, or two side by side.
+dfk::ColBlocks cols(const double* a, int64_t na, const double* b = nullptr, int64_t nb = 0) {
+  return dfk::ColBlocks{a, na, nullptr, 0, 0, b, nb};
+}
 
-// cpad [kpad16(nao)][ncol] = the blocks side by side, rows nao.. zero.
-df_status pad_operand(df_ctx* c, double* cpad, int64_t nao, int64_t ncol, const ColBlock* blocks, int nb) {
-  for (int i = 0; i < nb; ++i) {
-    const ColBlock& b = blocks[i];
-    if (b.ncols == 0) continue;
-    DF_LAUNCH(DF_KERNEL_OTHER,
-              hipMemcpy2DAsync(cpad + b.col0, ncol * sizeof(double), b.src, b.ld * sizeof(double),
-                               b.ncols * sizeof(double), nao, hipMemcpyDeviceToDevice, c->stream),
-              "operand gather");
-  }
-  const int64_t kp = dfk::kpad16(nao);
-  if (kp > nao)
-    DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_fill_zero(cpad + nao * ncol, (kp - nao) * ncol, c->stream), "fill");
+// cpad [kpad16(nao)][columns] = the blocks side by side, rows nao.. zero.
+df_status pad_operand(df_ctx* c, double* cpad, int64_t nao, const dfk::ColBlocks& k) {
+  DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_gather_cols(k, nao, dfk::kpad16(nao), cpad, c->stream), "operand gather");
   return DF_OK;
 }
 
-// cc [nao][ncol] = the blocks side by side (no padding)
-df_status pad_operand_plain(df_ctx* c, double* cc, int64_t nao, int64_t ncol, const ColBlock* blocks, int nb) {
-  for (int i = 0; i < nb; ++i) {
-    const ColBlock& b = blocks[i];
-    if (b.ncols == 0) continue;
-    DF_LAUNCH(DF_KERNEL_OTHER,
-              hipMemcpy2DAsync(cc + b.col0, ncol * sizeof(double), b.src, b.ld * sizeof(double),
-                               b.ncols * sizeof(double), nao, hipMemcpyDeviceToDevice, c->stream),
-              "operand gather");
-  }
+// cc [nao][columns] = the blocks side by side (no padding)
+df_status pad_operand_plain(df_ctx* c, double* cc, int64_t nao, const dfk::ColBlocks& k) {
+  DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_gather_cols(k, nao, nao, cc, c->stream), "operand gather");
   return DF_OK;
 }
 
@@ -1058,8 +1039,7 @@ df_status run_active(df_ctx* c, char* ws, const ActivePlan& p, double* b, double
   const double* cl = Cact;
   if (np > 0) {
     double* pcat = (double*)(ws + p.pcat);
-    const ColBlock blks[2] = {{Cp, np, np, 0}, {Cact, nac, nac, np}};
-    if (df_status s = pad_operand_plain(c, pcat, nao, rows, blks, 2)) return s;
+    if (df_status s = pad_operand_plain(c, pcat, nao, cols(Cp, np, Cact, nac))) return s;
     cl = pcat;
   }
   if (df_status s = run_mo(c, cl, rows, Xa, naux, nao, nac, b)) return s;
@@ -1415,8 +1395,7 @@ df_status df_half_transform(df_ctx* ctx, const double* B, int64_t naux, int64_t 
   const int xacc = acc && !C2;
   if (!sp) {
     double* cpad = (double*)(ws + p.cpad);
-    const ColBlock blk{C, ncol, ncol, 0};
-    if (df_status s = pad_operand(c, cpad, nao, ncol, &blk, 1)) return s;
+    if (df_status s = pad_operand(c, cpad, nao, cols(C, ncol))) return s;
     dfk::OutMap OX = out_pmajor(Xd, naux, nao, ncol, ncol);
     OX.accumulate = xacc;
     if (df_status s = run_half(c, B, naux, nao, cpad, ncol, OX)) return s;
@@ -1459,9 +1438,7 @@ static df_status jk_run(df_ctx* c, char* ws, const JkPlan& p, const double* B, i
   double* X = (double*)(ws + p.x);
   if (!sp) {
     double* cc = (double*)(ws + p.ccat);
-    std::vector<ColBlock> blks((size_t)ndm);
-    for (int64_t z = 0; z < ndm; ++z) blks[(size_t)z] = ColBlock{Cocc + z * nao * nocc, nocc, nocc, z * nocc};
-    if (df_status s = pad_operand(c, cc, nao, ncol, blks.data(), (int)ndm)) return s;
+    if (df_status s = pad_operand(c, cc, nao, dfk::ColBlocks{nullptr, 0, Cocc, nocc, ndm, nullptr, 0})) return s;
     if (df_status s = run_half(c, B, naux, nao, cc, ncol, out_pmajor(X, naux, nao, ncol, ncol))) return s;
   } else {
     // the rows (z, c) of the factors over mu, then X[P][mu][(z, c)] from the planes of b^P
@@ -1698,8 +1675,7 @@ df_status df_active_eri(df_ctx* ctx, const double* B, int64_t naux, int64_t nao,
   double* bu = buv && !acc ? buv : (double*)(ws + p.buv);   // b_uv of this call
   if (!sp) {
     double* cpad = (double*)(ws + p.cpad);
-    const ColBlock blk{Cact, nac, nac, 0};
-    if (df_status s = pad_operand(c, cpad, nao, nac, &blk, 1)) return s;
+    if (df_status s = pad_operand(c, cpad, nao, cols(Cact, nac))) return s;
     if (df_status s = run_half(c, B, naux, nao, cpad, nac, out_split(nullptr, X, naux, nao, 0, nac))) return s;
     if (df_status s = run_active(c, ws, p.act, bu, (double*)(ws + p.act.part), nullptr, 0, Cact, nac, X, naux, nao,
                                  nullptr, eri, acc))
@@ -1766,8 +1742,7 @@ df_status df_papa(df_ctx* ctx, const double* B, int64_t naux, int64_t nao, const
   double* br = (double*)(ws + (full ? p.bqv : p.bvw));
   if (!sp) {
     double* cpad = (double*)(ws + p.cpad);
-    const ColBlock blk{Cact, nac, nac, 0};
-    if (df_status s = pad_operand(c, cpad, nao, nac, &blk, 1)) return s;
+    if (df_status s = pad_operand(c, cpad, nao, cols(Cact, nac))) return s;
     if (df_status s = run_half(c, B, naux, nao, cpad, nac, out_split(nullptr, X, naux, nao, 0, nac))) return s;
     if (!full)
       return run_active(c, ws, p.act, (double*)(ws + p.act.b), (double*)(ws + p.act.part), Cp, np, Cact, nac, X, naux,
@@ -1805,13 +1780,11 @@ static df_status ppaa_run(df_ctx* c, char* ws, const PpaaPlan& p, const double* 
   double* cpa = (double*)(ws + p.cpa);
   double* cpq = (double*)(ws + p.cpq);
   // b^P_uv for every P, its lower triangle packed: vp [naux][nuv]
-  const ColBlock ba{Cact, nac, nac, 0};
-  if (df_status s = pad_operand(c, cpa, nao, nac, &ba, 1)) return s;
+  if (df_status s = pad_operand(c, cpa, nao, cols(Cact, nac))) return s;
   if (df_status s = run_half(c, B, naux, nao, cpa, nac, out_split(nullptr, X, naux, nao, 0, nac))) return s;
   if (df_status s = run_mo(c, Cact, nac, X, naux, nao, nac, buv)) return s;
   DF_LAUNCH(DF_KERNEL_OTHER, dfk::launch_pack_lower(buv, nac * nac, naux, nac, vp, c->stream), "pack launch");
-  const ColBlock bq{Cq, nq, nq, 0};
-  if (df_status s = pad_operand(c, cpq, nao, nq, &bq, 1)) return s;
+  if (df_status s = pad_operand(c, cpq, nao, cols(Cq, nq))) return s;
   // P ranges whose packed rows stay inside 31-bit offsets
   const int64_t pb = std::max<int64_t>(1, ((int64_t(1) << 31) - 1) / npair);
   for (int64_t u0 = 0; u0 < nuv; u0 += p.chunk) {
@@ -1956,8 +1929,7 @@ df_status df_embed_cholesky(df_ctx* ctx, const double* B, int64_t naux, int64_t 
   double* mpad = (double*)(c->ws + p.mpad);
   double* X = (double*)(c->ws + p.x);
   double* Y = (double*)(c->ws + p.y);
-  const ColBlock blk{M, nemb, nemb, 0};
-  if (df_status s = pad_operand(c, mpad, nao, nemb, &blk, 1)) return s;
+  if (df_status s = pad_operand(c, mpad, nao, cols(M, nemb))) return s;
   for (int64_t p0 = 0; p0 < naux; p0 += p.chunk) {
     const int64_t pc = std::min(p.chunk, naux - p0);
     if (df_status s = run_half(c, B + p0 * npair, pc, nao, mpad, nemb, out_pmajor(X, pc, nao, nemb, nemb)))
@@ -2012,8 +1984,7 @@ df_status df_step(df_ctx* ctx, const double* B, int64_t naux, int64_t nao, const
   }
   if (ncol == 0) return DF_OK;
   double* cc = (double*)(c->ws + p.ccat);
-  const ColBlock blks[2] = {{Cocc, nocc, nocc, 0}, {Cact, nac, nac, nocc}};
-  if (df_status s = pad_operand(c, cc, nao, ncol, blks, 2)) return s;
+  if (df_status s = pad_operand(c, cc, nao, cols(Cocc, nocc, Cact, nac))) return s;
   double* Xo = caller_x ? Xocc : (double*)(c->ws + p.xo);
   double* Xa = caller_x ? Xact : (double*)(c->ws + p.xa);
   const dfk::OutMap ox = out_split(Xo, Xa, naux, nao, nocc, nac);
@@ -2147,8 +2118,7 @@ df_status df_step_backward(df_ctx* ctx, const double* B, int64_t naux, int64_t n
   const int64_t no = do_k ? nocc : 0, na = do_e ? nac : 0;
   double* cc = (double*)(ws + p.ccat);
   if (recompute) {
-    const ColBlock blks[2] = {{Cocc, nocc, no, 0}, {Cact, nac, na, no}};
-    if (df_status s = pad_operand(c, cc, nao, no + na, blks, 2)) return s;
+    if (df_status s = pad_operand(c, cc, nao, cols(Cocc, no, Cact, na))) return s;
   }
   const int64_t kp = dfk::kpad16(nao);
   // auxiliary rows in chunks of p.chunk; each chunk's share of dCocc and dCact is added in order
@@ -2313,8 +2283,7 @@ df_status df_step_split(df_ctx* ctx, const double* B, const int8_t* Bs, const in
   // a2: X[(P, m)][c] = sum_k b^P_{mk} [Cact | Cocc][k][c], against the pre-split rows of b^P;
   // X_act goes out AO-major [m][P][u], X_occ P-major [P][m][i] (the layouts of df_step)
   double* cc = (double*)(ws + p.ccat);
-  const ColBlock blks[2] = {{Cact, nac, nac, 0}, {Cocc, nocc, nocc, nac}};
-  if (df_status s = pad_operand_plain(c, cc, nao, ncol, blks, 2)) return s;
+  if (df_status s = pad_operand_plain(c, cc, nao, cols(Cact, nac, Cocc, nocc))) return s;
   int8_t* cs = (int8_t*)(ws + p.cs.planes);
   int* ce = (int*)(ws + p.cs.ex);
   DF_LAUNCH(DF_KERNEL_SPLIT, dfk::launch_split_rows(dfk::op_map(cc, ncol, 1, nao, ncol), nao, nslice, cs, ce, c->stream),
@@ -2669,10 +2638,7 @@ df_status df_batched_step(df_ctx* ctx, const df_problem* probs, int nprob, int f
     const int64_t ncol = batched_ncol(q);
     if (ncol == 0 || !(q.J || q.K || q.eri || q.papa)) continue;
     double* cp = (double*)(ws + b.cpad);
-    std::vector<ColBlock> blks;
-    for (int64_t z = 0; z < q.ndm; ++z) blks.push_back({q.Cocc + z * q.nao * q.nocc, q.nocc, q.nocc, z * q.nocc});
-    blks.push_back({q.Cact, q.nac, q.nac, q.ndm * q.nocc});
-    if (df_status s = pad_operand(c, cp, q.nao, ncol, blks.data(), (int)blks.size())) return s;
+    if (df_status s = pad_operand(c, cp, q.nao, dfk::ColBlocks{nullptr, 0, q.Cocc, q.nocc, q.ndm, q.Cact, q.nac})) return s;
     double* Xo = (double*)(ws + b.xo);
     double* Xa = (double*)(ws + b.xa);
     gh.push_back({q.B, q.naux, q.nao, cp, ncol, ncol, out_split(Xo, Xa, q.naux, q.nao, q.ndm * q.nocc, q.nac)});
@@ -2838,9 +2804,7 @@ static df_status split_problem_run(df_ctx* c, char* ws, const df_problem& q, con
   const int64_t kpo = dfk::kpad64(nao);
   // half transform against the split b^P: [Cact | C_1 .. C_ndm] -> X_act AO-major, X_occ P-major
   double* cc = (double*)(ws + b.cc);
-  std::vector<ColBlock> blks = {{q.Cact, nac, nac, 0}};
-  for (int64_t z = 0; z < q.ndm; ++z) blks.push_back({q.Cocc + z * nao * q.nocc, q.nocc, q.nocc, nac + z * q.nocc});
-  if (df_status s = pad_operand_plain(c, cc, nao, ncol, blks.data(), (int)blks.size())) return s;
+  if (df_status s = pad_operand_plain(c, cc, nao, dfk::ColBlocks{q.Cact, nac, q.Cocc, q.nocc, q.ndm, nullptr, 0})) return s;
   DF_LAUNCH(DF_KERNEL_SPLIT,
             dfk::launch_split_rows(dfk::op_map(cc, ncol, 1, nao, ncol), nao, nslice, planes(b.cs), exps(b.cs), c->stream),
             "split launch");

@@ -155,6 +155,18 @@ hipError_t launch_coulomb(const double* B, int64_t naux, int64_t nao, const doub
 hipError_t launch_copy_rows(const double* x, int64_t rows, int64_t cols, double* y, int64_t ldy, int accumulate,
                             hipStream_t s);
 
+// Columns of a dense operand: one block of n0, nz of n1 (block z at s1 + z nao n1) and one of n2, side by side, each
+// stored [nao][columns].
+struct ColBlocks {
+  const double* s0;
+  int64_t n0;
+  const double* s1;
+  int64_t n1, nz;
+  const double* s2;
+  int64_t n2;
+};
+// dst [rows][n0 + nz n1 + n2] = the blocks, rows nao.. zero (rows >= nao); a block that is not empty must not be null
+hipError_t launch_gather_cols(const ColBlocks& k, int64_t nao, int64_t rows, double* dst, hipStream_t s);
 // y[i] += x[i], i < n
 hipError_t launch_add(const double* x, int64_t n, double* y, hipStream_t s);
 // Xw[i] = X[i] * w[i % ncol], i < n (columns of a row-major [n / ncol][ncol] matrix scaled)

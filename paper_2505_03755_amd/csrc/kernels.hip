@@ -1183,6 +1183,29 @@ __global__ void __launch_bounds__(kRedThreads) coulomb_reduce_kernel(const doubl
   Jz[j * nao + i] = x;
 }
 
+// Column blocks side by side (ColBlocks): dst[m][c], rows past nao zero.  One launch instead of a 2-D copy per
+// block and a fill: a copy's launch alone takes 10 to 20 us of a small call, and 64 densities
+// of eight fragments were 520 copies.
+__global__ void __launch_bounds__(256) gather_cols_kernel(ColBlocks k, int64_t nao, int64_t total,
+                                                          double* __restrict__ dst) {
+  const int64_t n = k.nz * k.n1, ncol = k.n0 + n + k.n2;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
+    const int64_t m = i / ncol, c = i - m * ncol - k.n0;
+    double x = 0.0;
+    if (m < nao) {
+      if (c < 0) {
+        x = k.s0[m * k.n0 + c + k.n0];
+      } else if (c < n) {
+        const int64_t z = c / k.n1;
+        x = k.s1[(z * nao + m) * k.n1 + c - z * k.n1];
+      } else {
+        x = k.s2[m * k.n2 + c - n];
+      }
+    }
+    dst[i] = x;
+  }
+}
+
 __global__ void __launch_bounds__(256) add_kernel(const double* __restrict__ x, int64_t n, double* __restrict__ y) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i < n) y[i] += x[i];
@@ -2320,6 +2343,14 @@ hipError_t launch_coulomb(const double* B, int64_t naux, int64_t nao, const doub
     }
   }
   return hipSuccess;
+}
+
+hipError_t launch_gather_cols(const ColBlocks& k, int64_t nao, int64_t rows, double* dst, hipStream_t s) {
+  const int64_t total = rows * (k.n0 + k.nz * k.n1 + k.n2);
+  if (total <= 0) return hipSuccess;
+  if ((k.n0 > 0 && !k.s0) || (k.nz * k.n1 > 0 && !k.s1) || (k.n2 > 0 && !k.s2)) return hipErrorInvalidValue;
+  gather_cols_kernel<<<(unsigned)std::min<int64_t>(cdiv(total, 256), 16384), 256, 0, s>>>(k, nao, total, dst);
+  return hipGetLastError();
 }
 
 hipError_t launch_add(const double* x, int64_t n, double* y, hipStream_t s) {
