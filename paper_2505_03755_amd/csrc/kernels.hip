@@ -441,6 +441,27 @@ __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2)))
   gemm_tile<C, AK, BK, GEN, CLAMP>(A, B, O, m0, n0, blockIdx.z, gridDim.y, blockIdx.y, part, smem);
 }
 
+// Rows in whole 64-row bands on 64 x 128 tiles and the rest (at most 32 rows) on 32 x 128 tiles, in one launch: per
+// column block the band tiles, then the tail tile, the column block turning their order so that the short
+// tiles do not all fall on the same shader engines (see half_tile).  Where the larger tiles would pad the
+// rows by much more (see gemm_launch): 800 rows 896 -> 800 (the adjoint's S X at 800 x 3200 x 200 15.9 -> 14.8 ms),
+// 210 rows 256 -> 224 (W of (pq|uv) at 600 x 2400 3.85 -> 3.57 ms).
+typedef Cfg<2, 2, 2, 4, 3> CfgBand;
+typedef Cfg<1, 4, 2, 2, 3> CfgBandTail;
+template <bool AK, bool BK, bool CLAMP>
+__global__ void __launch_bounds__(CfgBand::NT) __attribute__((amdgpu_waves_per_eu(CfgBand::WPE))) gemm_band_kernel(OpMap A, OpMap B, OutMap O, int64_t nband, int64_t per,
+                                                          int64_t tilesN, double* part) {
+  static_assert(CfgBandTail::NT == CfgBand::NT && CfgBandTail::BN == CfgBand::BN && CfgBandTail::STAGE <= CfgBand::STAGE,
+                "one workgroup shape and column block");
+  __shared__ double smem[2 * CfgBand::STAGE];
+  const int64_t tile = xcd_remap(blockIdx.x, per * tilesN);
+  const int64_t c = tile / per, i = (tile + c) % per, n0 = c * CfgBand::BN;
+  if (i < nband)
+    gemm_tile<CfgBand, AK, BK, false, CLAMP>(A, B, O, i * CfgBand::BM, n0, blockIdx.z, gridDim.y, blockIdx.y, part, smem);
+  else
+    gemm_tile<CfgBandTail, AK, BK, false, CLAMP>(A, B, O, nband * CfgBand::BM, n0, blockIdx.z, gridDim.y, blockIdx.y, part, smem);
+}
+
 // Row i and column j <= i of packed pair p = i(i+1)/2 + j.
 __device__ __forceinline__ void pair_ij(int64_t p, int64_t* i, int64_t* j) {
   int64_t r = (int64_t)((sqrt(8.0 * (double)p + 1.0) - 1.0) * 0.5);
@@ -1751,16 +1772,41 @@ static hipError_t gemm_launch(const OpMap& A, const OpMap& Bm, const OutMap& O, 
   if (gemm_small(O.M, O.N, nz * nsplit, (double)gemm_slabs(A) / nsplit))
     return gemm_launch_cfg<CfgSmall>(A, Bm, O, nz, nsplit, part, s);
   const int64_t rem = O.M % CfgSq::BM, tn = cdiv(O.N, CfgSq::BN);
+  // rows that the larger tiles pad by over 8% more than 64-row bands with a 32-row tail (the bands read more per
+  // MFMA: 600 rows, 5% less padding, ran 2.05 ms on 128-row tiles and 2.17 so; 210 rows, 14%, 3.85 and 3.57)
+  const int64_t large = rem > 0 && rem <= CfgRowTail::BM && gemm_tall(O.M) ? O.M - rem + CfgRowTail::BM
+                        : gemm_tall(O.M) ? cdiv(O.M, CfgTall::BM) * CfgTall::BM : cdiv(O.M, CfgSq::BM) * CfgSq::BM;
+  const int64_t brem = O.M % CfgBand::BM, tail = brem > 0 && brem <= CfgBandTail::BM ? 1 : 0;
+  const int64_t nband = tail ? O.M / CfgBand::BM : cdiv(O.M, CfgBand::BM);
+  if ((nband * CfgBand::BM + tail * CfgBandTail::BM) * 108 < large * 100 && (part || (O.alpha == 1.0 && !O.accumulate)) &&
+      (nband + tail) * tn <= 0x7fffffffLL && tn > 0 && nz > 0 && nz <= 65535 && nsplit >= 1 && nsplit <= 65535 &&
+      offsets_fit(A) && offsets_fit(Bm) && A.kc_n == Bm.kc_n && A.kb_n == Bm.kb_n) {
+    const dim3 grid((unsigned)((nband + tail) * tn), (unsigned)nsplit, (unsigned)nz);
+    const bool ak = A.s_kc == 1, bk = Bm.s_kc == 1;
+    auto go = [&](auto k, auto l, auto cl) {
+      gemm_band_kernel<decltype(k)::value, decltype(l)::value, decltype(cl)::value>
+          <<<grid, CfgBand::NT, 0, s>>>(A, Bm, O, nband, nband + tail, tn, part);
+    };
+    auto pick = [&](auto cl) {
+      if (ak && bk) go(std::true_type{}, std::true_type{}, cl);
+      else if (ak) go(std::true_type{}, std::false_type{}, cl);
+      else if (bk) go(std::false_type{}, std::true_type{}, cl);
+      else go(std::false_type{}, std::false_type{}, cl);
+    };
+    if (A.kc_n % 16 != 0) pick(std::true_type{});
+    else pick(std::false_type{});
+    return hipGetLastError();
+  }
   if (gemm_tall(O.M) && rem > 0 && rem <= CfgRowTail::BM && nz == 1 && nsplit == 1 && !part && O.alpha == 1.0 &&
       !O.accumulate && A.kc_n % 16 == 0 && (O.M / CfgSq::BM + 1) * tn <= 0x7fffffffLL && offsets_fit(A) &&
       offsets_fit(Bm) && A.kc_n == Bm.kc_n && A.kb_n == Bm.kb_n) {
-    const int64_t nband = O.M / CfgSq::BM;
-    const dim3 grid((unsigned)((nband + 1) * tn));
+    const int64_t nb = O.M / CfgSq::BM;
+    const dim3 grid((unsigned)((nb + 1) * tn));
     const bool ak = A.s_kc == 1, bk = Bm.s_kc == 1;
-    if (ak && bk) gemm_tail_kernel<true, true><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nband, tn);
-    else if (ak) gemm_tail_kernel<true, false><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nband, tn);
-    else if (bk) gemm_tail_kernel<false, true><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nband, tn);
-    else gemm_tail_kernel<false, false><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nband, tn);
+    if (ak && bk) gemm_tail_kernel<true, true><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nb, tn);
+    else if (ak) gemm_tail_kernel<true, false><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nb, tn);
+    else if (bk) gemm_tail_kernel<false, true><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nb, tn);
+    else gemm_tail_kernel<false, false><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nb, tn);
     return hipGetLastError();
   }
   return gemm_tall(O.M) ? gemm_launch_cfg<CfgTall>(A, Bm, O, nz, nsplit, part, s)

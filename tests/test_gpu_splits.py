@@ -194,3 +194,18 @@ def test_k_triangle_tiles(nao, nocc):
     for o in dfmi.batched_step(pr):
         for z in range(ndm):
             close(o["K"][z], O.jk(B, nao, C[z], None)[1], f"batched K[{z}]")
+
+
+# W of (pq|uv) with 91, 190 and 210 rows (pairs uv): 64-row bands with and without a 32-row tail, contractions of
+# whole slabs and not
+@pytest.mark.parametrize("naux,nac", [(33, 13), (32, 19), (17, 20)])
+def test_ppaa_rows_on_bands(naux, nac):
+    nao, nmo = 300, 3
+    rng = np.random.default_rng(naux)
+    B = rng.standard_normal((naux, O.npair(nao)))
+    C = np.linalg.qr(rng.standard_normal((nao, nao)))[0]
+    Cact, Cp = C[:, :nac], C[:, :nmo]
+    b = O.unpack(B, nao)
+    buv, bpq = Cact.T @ b @ Cact, Cp.T @ b @ Cp
+    u, v = np.tril_indices(nac)
+    close(dfmi.ppaa(dev(B), nao, dev(Cp), dev(Cact)), np.tensordot(buv[:, u, v], bpq, axes=(0, 0)), "ppaa")
