@@ -444,8 +444,7 @@ __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2)))
 // Rows in whole 64-row bands on 64 x 128 tiles and the rest (at most 32 rows) on 32 x 128 tiles, in one launch: per
 // column block the band tiles, then the tail tile, the column block turning their order so that the short
 // tiles do not all fall on the same shader engines (see half_tile).  Where the larger tiles would pad the
-// rows by much more (see gemm_launch): 800 rows 896 -> 800 (the adjoint's S X at 800 x 3200 x 200 15.9 -> 14.8 ms),
-// 210 rows 256 -> 224 (W of (pq|uv) at 600 x 2400 3.85 -> 3.57 ms).
+// rows by much more (see gemm_launch): 800 rows 896 -> 800 (the adjoint's S X at 800 x 3200 x 200 15.9 -> 14.5 ms).
 typedef Cfg<2, 2, 2, 4, 3> CfgBand;
 typedef Cfg<1, 4, 2, 2, 3> CfgBandTail;
 template <bool AK, bool BK, bool CLAMP>
@@ -1772,13 +1771,15 @@ static hipError_t gemm_launch(const OpMap& A, const OpMap& Bm, const OutMap& O, 
   if (gemm_small(O.M, O.N, nz * nsplit, (double)gemm_slabs(A) / nsplit))
     return gemm_launch_cfg<CfgSmall>(A, Bm, O, nz, nsplit, part, s);
   const int64_t rem = O.M % CfgSq::BM, tn = cdiv(O.N, CfgSq::BN);
-  // rows that the larger tiles pad by over 8% more than 64-row bands with a 32-row tail (the bands read more per
-  // MFMA: 600 rows, 5% less padding, ran 2.05 ms on 128-row tiles and 2.17 so; 210 rows, 14%, 3.85 and 3.57)
+  // at least 512 rows that the larger tiles pad by over 8% more than 64-row bands with a 32-row tail.  The bands read
+  // more per MFMA: 600 rows, 5% less padding, ran 2.05 ms on 128-row tiles and 2.17 so; with 210 rows, 14%, W
+  // of (pq|uv) at 600 x 2400 took 3.65 ms instead of 3.85, but the whole call 9.25 instead of 8.89 (the kernels after
+  // it ran slower: the card is at its power limit here)
   const int64_t large = rem > 0 && rem <= CfgRowTail::BM && gemm_tall(O.M) ? O.M - rem + CfgRowTail::BM
                         : gemm_tall(O.M) ? cdiv(O.M, CfgTall::BM) * CfgTall::BM : cdiv(O.M, CfgSq::BM) * CfgSq::BM;
   const int64_t brem = O.M % CfgBand::BM, tail = brem > 0 && brem <= CfgBandTail::BM ? 1 : 0;
   const int64_t nband = tail ? O.M / CfgBand::BM : cdiv(O.M, CfgBand::BM);
-  if ((nband * CfgBand::BM + tail * CfgBandTail::BM) * 108 < large * 100 && (part || (O.alpha == 1.0 && !O.accumulate)) &&
+  if (O.M >= 512 && (nband * CfgBand::BM + tail * CfgBandTail::BM) * 108 < large * 100 && (part || (O.alpha == 1.0 && !O.accumulate)) &&
       (nband + tail) * tn <= 0x7fffffffLL && tn > 0 && nz > 0 && nz <= 65535 && nsplit >= 1 && nsplit <= 65535 &&
       offsets_fit(A) && offsets_fit(Bm) && A.kc_n == Bm.kc_n && A.kb_n == Bm.kb_n) {
     const dim3 grid((unsigned)((nband + tail) * tn), (unsigned)nsplit, (unsigned)nz);

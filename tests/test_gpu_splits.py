@@ -196,16 +196,19 @@ def test_k_triangle_tiles(nao, nocc):
             close(o["K"][z], O.jk(B, nao, C[z], None)[1], f"batched K[{z}]")
 
 
-# W of (pq|uv) with 91, 190 and 210 rows (pairs uv): 64-row bands with and without a 32-row tail, contractions of
-# whole slabs and not
-@pytest.mark.parametrize("naux,nac", [(33, 13), (32, 19), (17, 20)])
-def test_ppaa_rows_on_bands(naux, nac):
-    nao, nmo = 300, 3
-    rng = np.random.default_rng(naux)
+# the adjoint's S X on 530 and 545 rows: 64-row bands with and without a 32-row tail (128-row tiles would pad to 640),
+# contractions that are not whole slabs
+@pytest.mark.parametrize("nao", [530, 545])
+def test_adjoint_product_on_bands(nao):
+    naux, nocc = 130, 100
+    rng = np.random.default_rng(nao)
     B = rng.standard_normal((naux, O.npair(nao)))
-    C = np.linalg.qr(rng.standard_normal((nao, nao)))[0]
-    Cact, Cp = C[:, :nac], C[:, :nmo]
-    b = O.unpack(B, nao)
-    buv, bpq = Cact.T @ b @ Cact, Cp.T @ b @ Cp
-    u, v = np.tril_indices(nac)
-    close(dfmi.ppaa(dev(B), nao, dev(Cp), dev(Cact)), np.tensordot(buv[:, u, v], bpq, axes=(0, 0)), "ppaa")
+    C = np.linalg.qr(rng.standard_normal((nao, nocc + 1)))[0]
+    Co, Ca = C[:, :nocc].copy(), C[:, nocc:].copy()
+    gK = rng.standard_normal((nao, nao))
+    dCo, _ = dfmi.step_backward(dev(B), nao, dev(Co), dev(Ca), gK=dev(gK))
+    ref = np.zeros((nao, nocc))
+    for P in range(naux):
+        b = O.unpack(B[P:P + 1], nao)[0]
+        ref += b @ ((gK + gK.T) @ (b @ Co))
+    close(dCo, ref, "dCocc")
