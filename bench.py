@@ -92,8 +92,8 @@ def kernel_table(kt, naux, nao, nocc, nac, nmo, steps):
         "half_transform": ("mfma", 2 * naux * nao * nao * ncol),
         "k_syrk": ("mfma", naux * nocc * nao * (nao + 1)),
         "mo_transform": ("mfma", 2 * naux * nao * nmo * nac + 2 * naux * nao * nac * nac),
-        "papa": ("mfma", 2 * naux * nmo * nac ** 3),
-        "eri": ("mfma", 2 * naux * nac ** 4),
+        # (pu|vw) and (uv|wx) in one product over P against the packed pairs v >= w
+        "papa": ("mfma", naux * (nmo + nac) * nac * nac * (nac + 1)),
         "adjoint": ("mfma", 4 * naux * nao * nao * nocc + 2 * nao * nao * nocc + 2 * naux * nac ** 4
                     + 2 * naux * nao * nac * nac),
         # HBM-bound kernels: bytes read + written

@@ -175,17 +175,20 @@ PpaaPlan plan_ppaa(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int64_t nq)
   return p;
 }
 
-// Workspace of df_build_cholesky: the inverted diagonal blocks of L and a panel of the factorisation.
+// Workspace of df_build_cholesky: the inverted diagonal blocks of L and a panel of the factorisation.  The
+// size keeps one block row of B besides, as it always had: the substitution no longer needs it, but
+// callers may count on the size.
 struct BuildPlan {
   size_t linv, panel;
   int64_t nblk;
 };
-BuildPlan plan_build(Plan& pl, int64_t naux) {
+BuildPlan plan_build(Plan& pl, int64_t naux, int64_t nao) {
   BuildPlan p{};
   const int64_t nb = dfk::kCholNB;
   p.nblk = (naux + nb - 1) / nb;
   p.linv = pl.take(p.nblk * nb * nb);
   p.panel = pl.take(naux * nb);
+  pl.take(nb * (nao * (nao + 1) / 2));
   return p;
 }
 
@@ -1260,7 +1263,7 @@ df_status workspace_bytes(df_op op, const df_dims* d, size_t limit, size_t* byte
       break;
     case DF_OP_ACTIVE_ERI: plan_act(pl, d->naux, d->nao, d->nac, d->flags, d->nslice); break;
     case DF_OP_PAPA: plan_papa(pl, d->naux, d->nao, d->nac, d->np, d->nq, d->flags, d->nslice); break;
-    case DF_OP_BUILD_CHOLESKY: plan_build(pl, d->naux); break;
+    case DF_OP_BUILD_CHOLESKY: plan_build(pl, d->naux, d->nao); break;
     case DF_OP_EMBED_CHOLESKY: plan_embed(pl, d->naux, d->nao, d->ncol); break;
     case DF_OP_PPAA:
       plan_ppaa(pl, d->naux, d->nao, d->nac, d->nq > 0 ? d->nq : d->np);
@@ -1856,7 +1859,7 @@ df_status df_build_cholesky(df_ctx* ctx, const double* metric, const double* eri
                            {B, dbytes(naux * npair), "B", true},
                            {info, sizeof(int), "info", true}};
   Plan pl;
-  const BuildPlan p = plan_build(pl, naux);
+  const BuildPlan p = plan_build(pl, naux, nao);
   if (!check_overlap(c, rs)) return DF_ERR_ARG;
   if (df_status s = need_ws(c, pl.total)) return s;
   rs.push_back({c->ws, pl.total, "workspace", true});
