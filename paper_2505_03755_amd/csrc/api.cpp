@@ -229,7 +229,7 @@ StepPlan plan_step(Plan& pl, int64_t naux, int64_t nao, int64_t nocc, int64_t na
   p.xo = pl.take(caller_x ? 0 : naux * nao * nocc);
   p.xa = pl.take(caller_x ? 0 : naux * nao * nac);
   p.nsplit = dfk::syrk_splits(nao, naux, nocc, 1);
-  p.kpart_n = std::max({(int64_t)p.nsplit * nao * nao, dfk::coulomb_part(naux, nao, 1), active_part(naux, np, nac),
+  p.kpart_n = std::max({dfk::syrk_parts(naux, p.nsplit) * nao * nao, dfk::coulomb_part(naux, nao, 1), active_part(naux, np, nac),
                         active_part(naux, 0, nac)});
   p.kpart = pl.take(p.kpart_n);
   p.vtmp = pl.take(naux);
@@ -395,7 +395,7 @@ JkPlan plan_jk(Plan& pl, int64_t naux, int64_t nao, int64_t ndm, int64_t nocc, b
                                        dfk::slice_gemm_steps(dfk::kpad64(naux * nocc)))
                         : 1;
   }
-  p.kpart_n = (int64_t)p.nsplit * ndm * nao * nao;
+  p.kpart_n = (sp ? p.nsplit : dfk::syrk_parts(naux, p.nsplit)) * ndm * nao * nao;
   if (nsplit_fp64 == 0) p.kpart_n = std::max(p.kpart_n, dfk::coulomb_part(naux, nao, ndm));
   p.kpart = pl.take(p.kpart_n);
   return p;
@@ -836,7 +836,7 @@ SplitPiece plan_split_piece(Plan& pl, const df_problem& q, int nslice, bool k_fp
           : dks ? slice_splits(dfk::slice_gemm_tiles(q.nao, q.nao, true) * q.ndm,
                                dfk::slice_gemm_steps(dfk::kpad64(q.naux * q.nocc)))
                 : dfk::syrk_splits(q.nao, q.naux, q.nocc, q.ndm);
-  b.kpart = pl.take(dk ? (int64_t)b.nsk * q.ndm * q.nao * q.nao : 0);
+  b.kpart = pl.take(dk ? (dks ? b.nsk : dfk::syrk_parts(q.naux, b.nsk)) * q.ndm * q.nao * q.nao : 0);
   b.xas = take_split(pl, de || dp ? q.naux * q.nac : 0, q.nao, nslice);
   b.cas = take_split(pl, de ? q.nac : 0, q.nao, nslice);
   b.buv = pl.take(de ? q.naux * q.nac * q.nac : 0);
@@ -1076,7 +1076,7 @@ df_status run_k(df_ctx* c, const double* X, const double* w, int64_t naux, int64
   Bw.ks = w;
   Bw.s_ksz = nocc;
   DF_LAUNCH(DF_KERNEL_K_SYRK, dfk::launch_syrk_partial(A, Bw, nao, nz, nsplit, kpart, c->stream), "K tiles launch");
-  DF_LAUNCH(DF_KERNEL_K_REDUCE, dfk::launch_syrk_partial_reduce(kpart, nsplit, naux, nao, nz, K, c->stream, accumulate),
+  DF_LAUNCH(DF_KERNEL_K_REDUCE, dfk::launch_syrk_partial_reduce(kpart, A, nsplit, nao, nz, K, c->stream, accumulate),
             "K reduce launch");
   return DF_OK;
 }
@@ -2835,7 +2835,7 @@ static df_status split_problem_run(df_ctx* c, char* ws, const df_problem& q, con
     A.s_z = q.nocc;
     double* kpart = (double*)(ws + b.kpart);
     DF_LAUNCH(DF_KERNEL_K_SYRK, dfk::launch_syrk_partial(A, A, nao, q.ndm, b.nsk, kpart, c->stream), "K tiles launch");
-    DF_LAUNCH(DF_KERNEL_K_REDUCE, dfk::launch_syrk_partial_reduce(kpart, b.nsk, naux, nao, q.ndm, q.K, c->stream),
+    DF_LAUNCH(DF_KERNEL_K_REDUCE, dfk::launch_syrk_partial_reduce(kpart, A, b.nsk, nao, q.ndm, q.K, c->stream),
               "K reduce launch");
   } else if (q.K && q.nocc > 0) {
     // rows m of each density's X_occ over (P, i), then K_z = sum_{P, i} X[P][m][z i] X[P][n][z i]

@@ -115,17 +115,19 @@ hipError_t launch_jvec_packed(const double* B, int64_t naux, int64_t nao, const 
 hipError_t launch_symmetrize(const double* in, int64_t n, int64_t nz, double* out, hipStream_t s);
 
 // Lower-tile SYRK with a split of the contraction: Kpart[split][z][i][j] = sum_{kb in split, kc} A(i,(kb,kc)) Bw(j,(kb,kc))
-// for the tiles of the lower triangle (Bw = A with an optional per-kc weight).  Kpart is dense
-// [nsplit][nz][n][n]; syrk_splits() gives the number of splits the workspace is planned for (tiles
-// smaller than the largest take fewer).
+// for the tiles of the lower triangle (Bw = A with an optional per-kc weight).  syrk_splits() gives the number
+// of splits of the largest tiles (the others take fewer, or up to 1.2 times as many); Kpart is dense
+// [syrk_parts()][nz][n][n].
 int syrk_splits(int64_t n, int64_t kb_n, int64_t kc_n, int64_t nz);
 // The most splits syrk_splits(n, k, kc_n, nz) gives for any k <= kb_n.
 int syrk_splits_bound(int64_t n, int64_t kb_n, int64_t nz);
+// Partials of nsplit splits over at most kb_n blocks, non-decreasing in both.
+int64_t syrk_parts(int64_t kb_n, int nsplit);
 hipError_t launch_syrk_partial(const OpMap& A, const OpMap& Bw, int64_t n, int64_t nz, int nsplit,
                                double* Kpart, hipStream_t s);
-// K[z][i][j] = sum_s Kpart[s][z][max(i,j)][min(i,j)] from launch_syrk_partial's partials of a contraction
-// over kb_n blocks; both triangles written (added to K when `accumulate`).
-hipError_t launch_syrk_partial_reduce(const double* Kpart, int nsplit, int64_t kb_n, int64_t n, int64_t nz, double* K,
+// K[z][i][j] = sum_s Kpart[s][z][max(i,j)][min(i,j)] from launch_syrk_partial's partials of the same A and nsplit;
+// both triangles written (added to K when `accumulate`).
+hipError_t launch_syrk_partial_reduce(const double* Kpart, const OpMap& A, int nsplit, int64_t n, int64_t nz, double* K,
                                       hipStream_t s, int accumulate = 0);
 // The same where every tile has all nsplit partials.
 hipError_t launch_syrk_reduce(const double* Kpart, int nsplit, int64_t n, int64_t nz, double* K,

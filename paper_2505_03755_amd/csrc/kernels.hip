@@ -648,11 +648,13 @@ __device__ __forceinline__ void syrk_run(const OpMap& A, const OpMap& Bw, int64_
 // Tiles of the lower triangle of an n x n SYRK, and their splits of the contraction.  Band i of `bands` 64-row
 // bands needs columns 0 ... 64 (i + 1): (i + 1) / 2 tiles of 64 x 128 (A) and, in even bands, one of
 // 64 x 64 on the diagonal (D); the rows past the bands take tiles of 32 x 128 (T).  Each kind has its own split
-// count, in proportion to the time of its tiles, so that all work items take about as long.  Bound by the
+// count, in proportion to the time of its tiles, so that all work items take about as long, or twice that for D and
+// T where the items are long: the chain of sums of a D item would be 1.7 times an A item's, and the diagonal is
+// the largest part of K.  (Relative error of K at 1200 x 4800 x 300 1.6e-15 so, 8.3e-16 with 37 equal chains,
+// 7.7e-16 now; at 800 6.9e-16, 4.0e-16, 3.1e-16.)  Bound by the
 // matrix cores (0.7 busy) and the padding of the triangle.  Against square tiles of 64 (128 past n = 640): K at
 // 341 x 1365 x 85 0.41 -> 0.38 ms, 600 x 2400 x 150 3.30 -> 3.03, 700 x 1400 x 128 1.91 -> 1.52, 1200 x 1200 x 300
-// 10.5 -> 9.8.  (One split count for all kinds was faster at 600, 2.90, and slower at 240, 0.139 against 0.113,
-// and 1200, 10.9; 128 x 128 tiles with 64-row tails 2.98 at 600 and 1.69 at 700.)
+// 10.5 -> 9.8.  128 x 128 tiles with 64-row tails: 2.98 at 600, 1.69 at 700.
 struct SyrkTiles {
   int bands;              // 0: every element has na partials (launch_syrk_reduce)
   int a, d, t;            // tiles of each kind
@@ -660,27 +662,30 @@ struct SyrkTiles {
   __host__ __device__ int64_t items() const { return (int64_t)a * na + (int64_t)d * nd + (int64_t)t * nt; }
 };
 
-// Items: the A tiles of split 0, of split 1, ..., then the D tiles so, then the T tiles.
+// Items: the A tiles of split 0, of split 1, ..., then the D tiles so, then the T tiles; the items of each kind are dealt
+// to the XCDs by themselves (all in one row, the last XCDs got the D and T items alone).
 template <bool SCALE, bool CLAMP, bool FLAT>
 __global__ void __launch_bounds__(CfgKA::NT) __attribute__((amdgpu_waves_per_eu(CfgKA::WPE))) syrk_kernel(OpMap A, OpMap Bw, int64_t n, int64_t nz, SyrkTiles T,
                                                      double* Kpart) {
   static_assert(CfgKD::STAGE <= CfgKA::STAGE && CfgKT::STAGE <= CfgKA::STAGE, "the A tile's LDS holds the others");
   __shared__ double smem[2 * CfgKA::STAGE];
-  const int64_t item = xcd_remap(blockIdx.x, T.items()), z = blockIdx.z;
-  const int64_t na = (int64_t)T.a * T.na, nad = na + (int64_t)T.d * T.nd;
-  if (item < na) {
+  const int64_t id = blockIdx.x, z = blockIdx.z;
+  const int64_t na = (int64_t)T.a * T.na, nd = (int64_t)T.d * T.nd, nad = na + nd;
+  if (id < na) {
+    const int64_t item = xcd_remap(id, na);
     const int q = (int)(item % T.a);
     int i = (int)(2.0f * sqrtf((float)q));   // i^2 / 4 A tiles lie in the bands before band i
     while (i * i / 4 > q) --i;
     while ((i + 1) * (i + 1) / 4 <= q) ++i;
     syrk_run<CfgKA, SCALE, CLAMP, FLAT>(A, Bw, n, nz, T.na, (int)(item / T.a), (int64_t)i * CfgKA::BM,
                                         (int64_t)(q - i * i / 4) * CfgKA::BN, Kpart, z, smem);
-  } else if (item < nad) {
-    const int64_t m0 = (item - na) % T.d * 2 * CfgKD::BM;
-    syrk_run<CfgKD, SCALE, CLAMP, FLAT>(A, Bw, n, nz, T.nd, (int)((item - na) / T.d), m0, m0, Kpart, z, smem);
+  } else if (id < nad) {
+    const int64_t item = xcd_remap(id - na, nd), m0 = item % T.d * 2 * CfgKD::BM;
+    syrk_run<CfgKD, SCALE, CLAMP, FLAT>(A, Bw, n, nz, T.nd, (int)(item / T.d), m0, m0, Kpart, z, smem);
   } else {
-    syrk_run<CfgKT, SCALE, CLAMP, FLAT>(A, Bw, n, nz, T.nt, (int)((item - nad) / T.t), (int64_t)T.bands * CfgKA::BM,
-                                        (item - nad) % T.t * CfgKT::BN, Kpart, z, smem);
+    const int64_t item = xcd_remap(id - nad, (int64_t)T.t * T.nt);
+    syrk_run<CfgKT, SCALE, CLAMP, FLAT>(A, Bw, n, nz, T.nt, (int)(item / T.t), (int64_t)T.bands * CfgKA::BM,
+                                        item % T.t * CfgKT::BN, Kpart, z, smem);
   }
 }
 
@@ -2123,9 +2128,9 @@ hipError_t launch_gram(const OpMap& A, double* G, double* part, int64_t part_n, 
 
 int syrk_tile_for(int64_t n) { return n <= 640 ? CfgSyrk64::BM : CfgSyrk::BM; }
 
-// Tiles of an n x n SYRK with `unit` splits of the 64 x 128 tiles; a 64 x 64 tile takes 0.58 and a 32 x 128
-// one 0.55 of their time (rates at CfgH128).
-static SyrkTiles syrk_tiles(int64_t n, int64_t kb_n, int unit) {
+// Tiles of an n x n SYRK with `unit` splits of the 64 x 128 tiles over `slabs` slabs in kb_n blocks; a 64 x 64 tile
+// takes 0.58 and a 32 x 128 one 0.55 of their time (rates at CfgH128).
+static SyrkTiles syrk_tiles(int64_t n, int64_t kb_n, int64_t slabs, int unit) {
   SyrkTiles T{};
   const int64_t rows = n % CfgKA::BM, tail = n > CfgKA::BM && rows > 0 && rows <= CfgKT::BM ? rows : 0;
   T.bands = (int)cdiv(n - tail, CfgKA::BM);
@@ -2135,39 +2140,55 @@ static SyrkTiles syrk_tiles(int64_t n, int64_t kb_n, int unit) {
   T.na = unit;
   T.nd = scaled_splits(unit, 0.58, kb_n);
   T.nt = T.t ? scaled_splits(unit, 0.55, kb_n) : 0;
+  // halves of 64 slabs at least: an item's prologue and epilogue take about four
+  if (T.nd < unit && slabs >= (int64_t)128 * T.nd) {
+    T.nd = (int)std::min<int64_t>(2 * T.nd, kb_n);
+    T.nt = (int)std::min<int64_t>(2 * T.nt, kb_n);
+  }
   return T;
 }
+static SyrkTiles syrk_tiles(const OpMap& A, int64_t n, int unit) {
+  return syrk_tiles(n, A.kb_n, cdiv(A.kb_n * A.kc_n, 16), unit);
+}
 
+// The most units: four rounds of resident workgroups, or five where that leaves fewer than 64.  With four, N_ao = 1200
+// had 32, chains of 45000 products.
 static int64_t syrk_most(int64_t n, int64_t kb_n, int64_t nz) {
-  const int64_t tiles = syrk_tiles(n, 1, 1).items() * std::max<int64_t>(nz, 1);
-  return std::max<int64_t>(1, std::min<int64_t>({kb_n, 4096, 4 * cdiv(768, tiles)}));
+  const SyrkTiles T = syrk_tiles(n, 1, 0, 1);
+  const int64_t per = cdiv(768, (T.a + T.d + T.t) * std::max<int64_t>(nz, 1));
+  return std::max<int64_t>(1, std::min<int64_t>({kb_n, 4096, std::max(4 * per, std::min<int64_t>(5 * per, 64))}));
 }
 int syrk_splits_bound(int64_t n, int64_t kb_n, int64_t nz) { return (int)syrk_most(n, kb_n, nz); }
 
-// Splits of least estimated time, as in half_reduce_unit: three workgroups per CU, 3.5 us a slab of a 64 x 128 tile
-// (two 2.4, one 1.6); partial sums of the triangle written and read.
+// Units of least estimated time, as in half_reduce_unit (halved D and T items count as whole ones): three workgroups per
+// CU, 3.5 us a slab of a 64 x 128 tile (two 2.4, one 1.6); partial sums of the triangle written and read.
+// At least one unit per 640 slabs, as far as there may be so many: the rounding error grows with the length of a chain.
 int syrk_splits(int64_t n, int64_t kb_n, int64_t kc_n, int64_t nz) {
   if (nz < 1) nz = 1;
   const int64_t most = syrk_most(n, kb_n, nz), slabs = cdiv(kb_n * kc_n, 16);
-  int best = 1;
+  const int least = (int)std::max<int64_t>(1, std::min(most, cdiv(slabs, 640)));
+  int best = least;
   double best_us = 0.0;
-  for (int u = 1; u <= most; ++u) {
-    const int64_t w = syrk_tiles(n, kb_n, u).items() * nz, full = w / 768, rem = w % 768;
+  for (int u = least; u <= most; ++u) {
+    const int64_t w = syrk_tiles(n, kb_n, 0, u).items() * nz, full = w / 768, rem = w % 768;
     const double last = rem == 0 ? 0.0 : rem <= 256 ? 1.6 : rem <= 512 ? 2.4 : 3.5;
     const double us = ((double)full * 3.5 + last + 0.7) * (double)(cdiv(slabs, u) + 4) +
                       (double)u * (double)(n * (n + 1) / 2 * nz) * 16.0 / 4.0e6;
-    if (u == 1 || us < best_us * (1.0 - 1e-9)) {
+    if (u == least || us < best_us * (1.0 - 1e-9)) {
       best_us = us;
       best = u;
     }
   }
   return best;
 }
+int64_t syrk_parts(int64_t kb_n, int unit) {
+  return std::max<int64_t>(unit, std::min<int64_t>(kb_n, 2 * scaled_splits(unit, 0.58, kb_n)));
+}
 
 hipError_t launch_syrk_partial(const OpMap& A, const OpMap& Bw, int64_t n, int64_t nz, int nsplit, double* Kpart,
                                hipStream_t s) {
   if (n == 0 || nz == 0) return hipSuccess;
-  const SyrkTiles T = syrk_tiles(n, A.kb_n, nsplit);
+  const SyrkTiles T = syrk_tiles(A, n, nsplit);
   if (nz > 65535 || !offsets_fit(A) || T.items() > 0x7fffffffLL) return hipErrorInvalidValue;
   const dim3 grid((unsigned)T.items(), 1, (unsigned)nz);
   const bool clamp = A.kc_n % 16 != 0;
@@ -2330,9 +2351,9 @@ hipError_t launch_syrk_reduce(const double* Kpart, int nsplit, int64_t n, int64_
   return syrk_reduce_go(Kpart, T, n, nz, K, s, accumulate);
 }
 
-hipError_t launch_syrk_partial_reduce(const double* Kpart, int nsplit, int64_t kb_n, int64_t n, int64_t nz, double* K,
+hipError_t launch_syrk_partial_reduce(const double* Kpart, const OpMap& A, int nsplit, int64_t n, int64_t nz, double* K,
                                       hipStream_t s, int accumulate) {
-  return syrk_reduce_go(Kpart, syrk_tiles(n, kb_n, nsplit), n, nz, K, s, accumulate);
+  return syrk_reduce_go(Kpart, syrk_tiles(A, n, nsplit), n, nz, K, s, accumulate);
 }
 
 hipError_t launch_jvec(const double* X, int64_t naux, int64_t nao, int64_t ldx, const double* C, const double* w,

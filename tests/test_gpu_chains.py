@@ -1,0 +1,43 @@
+"""How many products the library adds up one after the other: the rounding error of K and of the
+adjoint grows with the length of such a chain.
+
+The first product of a sum is 2^56, all others are 1.  A partial sum that holds the first one loses
+every 1 added to it (they are under half of its last place, four of them together still are), the
+other partial sums are whole numbers and exact, so the sum falls short by the length of the first
+chain.  Adding the partial sums up rounds each to a multiple of 16, at most 8 off per addition."""
+import pytest
+
+torch = pytest.importorskip("torch")
+
+from paper_2505_03755_amd import dfmi
+
+pytestmark = pytest.mark.gpu
+BIG = 2.0 ** 28   # its square is the first product
+
+
+def ones_with_big_column(naux, nao):
+    """Packed b^P_ij = 1, but 2^28 where P = 0 and i or j is 0."""
+    B = torch.ones((naux, nao * (nao + 1) // 2), dtype=torch.float64, device="cuda")
+    i = torch.arange(nao, device="cuda")
+    B[0, i * (i + 1) // 2] = BIG
+    return B
+
+
+def unit_columns(nao, n):
+    return torch.eye(nao, dtype=torch.float64, device="cuda")[:, :n].contiguous()
+
+
+# 640 slabs of 16 products a chain; 12000 products where 40 chains are more than that needs.  The contraction is in whole
+# slabs, runs on across the auxiliary rows, or is weighted.
+@pytest.mark.parametrize("nao,naux,nocc,weighted,limit", [
+    (800, 800, 800, False, 10240), (800, 801, 799, False, 10240), (800, 800, 800, True, 10240),
+    (1200, 400, 1200, False, 12000)])
+def test_k_chains(nao, naux, nocc, weighted, limit):
+    B = ones_with_big_column(naux, nao)
+    w = torch.ones((1, nocc), dtype=torch.float64, device="cuda") if weighted else None
+    _, K, _ = dfmi.jk(B, nao, unit_columns(nao, nocc)[None].contiguous(), w=w, want_j=False, want_v=False)
+    # K_ij = sum_{P, c} b^P_ic b^P_jc for i, j >= 1
+    lost = (BIG * BIG - K[0, 1:, 1:]) + float(naux * nocc - 1)
+    assert lost.min().item() >= -8 * 128
+    worst = lost.max().item()
+    assert worst <= limit + 8 * 128, worst
