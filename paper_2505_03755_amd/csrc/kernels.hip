@@ -1037,7 +1037,7 @@ __device__ __forceinline__ void half_reduce_tile(const double* __restrict__ B, i
   // split major, then row band: the tiles of one P range sit on one XCD, and the column tiles
   // of a band side by side
   const int64_t ntile = (int64_t)g.tilesM * g.tilesN;
-  const int split = (int)((item - g.item0) / ntile), tile = (int)((item - g.item0) % ntile);
+  const int split = (int)(item / ntile), tile = (int)(item % ntile);
   const int m0 = g.r0 + tile / g.tilesN * C::BM, n0 = g.c0 + tile % g.tilesN * C::BN;
   const int64_t P0 = naux * split / g.ns, P1 = naux * (split + 1) / g.ns;
   d4 acc[C::TM][C::TN];
@@ -1059,13 +1059,14 @@ __global__ void __launch_bounds__(CA::NT) __attribute__((amdgpu_waves_per_eu(CA:
                                                             int64_t npair, OpMap Y, ReduceRegions R) {
   __shared__ double smem[HalfLds<CA, CB, CT>::N];
   constexpr bool kB = !std::is_same<CA, CB>::value, kT = !std::is_same<CA, CT>::value;
-  const int64_t item = xcd_remap(blockIdx.x, R.items);
-  if (!(kB || kT) || item < R.b.item0)
-    half_reduce_tile<CA>(B, naux, nao, npair, Y, R.a, item, smem);
-  else if (kB && (!kT || item < R.t.item0))
-    half_reduce_tile<CB>(B, naux, nao, npair, Y, R.b, item, smem);
+  // each region dealt to the XCDs by itself: in one row, the last XCDs would get the short items alone
+  const int64_t id = blockIdx.x;
+  if (!(kB || kT) || id < R.b.item0)
+    half_reduce_tile<CA>(B, naux, nao, npair, Y, R.a, xcd_remap(id, kB || kT ? R.b.item0 : R.items), smem);
+  else if (kB && (!kT || id < R.t.item0))
+    half_reduce_tile<CB>(B, naux, nao, npair, Y, R.b, xcd_remap(id - R.b.item0, R.t.item0 - R.b.item0), smem);
   else if constexpr (kT)
-    half_reduce_tile<CT>(B, naux, nao, npair, Y, R.t, item, smem);
+    half_reduce_tile<CT>(B, naux, nao, npair, Y, R.t, xcd_remap(id - R.t.item0, R.items - R.t.item0), smem);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1936,25 +1937,28 @@ hipError_t launch_gemm_split(const OpMap& A, const OpMap& Bm, const OutMap& O, i
   return launch_split_reduce(part, nsplit, O, s);
 }
 
-// The regions of the P-summed packed product (ReduceRegions) with split counts in proportion to the
-// time of a tile of each: `unit` splits of the 128-wide tiles.  The items then fill whole rounds of
-// the resident workgroups, the partial sums' cost against the rounds' as in balanced_splits.
+// The regions of the P-summed packed product (ReduceRegions): `unit` splits of the 128-wide tiles, and as many
+// of the others or, where those take less than 0.7 of the time, up to twice as many as their time is worth, so
+// that their items last half as long and no chain of sums is longer than the 128-wide tiles'.  (In proportion to
+// the time, the chains of a 48-wide rest were 2.1 times as long; the rounding error of dCocc at 1200 x 4800 x 300
+// 1.45e-15 so, 9.8e-16 with chains of 68000 products at most, 6.8e-16 now.)
 static double half_tile_time(int rest) {   // of a tile, against 128 columns (rates at CfgH128)
   return rest == 96 ? 0.80 : rest == 64 ? 0.58 : rest == 48 ? 0.48 : rest == 32 ? 0.37 : 0.30;
 }
 constexpr double kHTailTime = 0.55;
-static int scaled_splits(int unit, double w, int64_t naux) {
-  return (int)std::max<int64_t>(1, std::min<int64_t>(naux, (int64_t)((double)unit * w + 0.5)));
+static int64_t region_splits(int64_t unit, double w, int64_t naux) {
+  const double f = w < 0.7 ? std::max(1.0, 2.0 * w) : 1.0;
+  return std::min<int64_t>(naux, (int64_t)((double)unit * f));
 }
-static ReduceRegions reduce_regions(int64_t naux, int64_t nao, int64_t N, int unit) {
+static ReduceRegions reduce_regions(int64_t naux, int64_t nao, int64_t N, int64_t unit) {
   const HalfCols h = half_cols(nao, N);
   const HalfTiles T = half_counts(nao, N);
   const bool one = h.nA == 0;   // one narrow tile per band: region a alone
   const int rows = (int)nao - h.tail, ca = one ? (int)N : (int)std::min<int64_t>(N, h.nA * 128);
   ReduceRegions R{};
-  R.a = ReduceRegion{0, 0, rows, 0, ca, T.bands, T.nA, scaled_splits(unit, 1.0, naux), nullptr};
-  R.b = ReduceRegion{0, 0, rows, ca, (int)N, T.bands, T.nB, T.nB ? scaled_splits(unit, half_tile_time(h.rest), naux) : 0, nullptr};
-  R.t = ReduceRegion{0, rows, (int)nao, 0, (int)N, T.nT ? 1 : 0, T.nT, T.nT ? scaled_splits(unit, kHTailTime, naux) : 0, nullptr};
+  R.a = ReduceRegion{0, 0, rows, 0, ca, T.bands, T.nA, (int)std::min(unit, naux), nullptr};
+  R.b = ReduceRegion{0, 0, rows, ca, (int)N, T.bands, T.nB, T.nB ? (int)region_splits(unit, half_tile_time(h.rest), naux) : 0, nullptr};
+  R.t = ReduceRegion{0, rows, (int)nao, 0, (int)N, T.nT ? 1 : 0, T.nT, T.nT ? (int)region_splits(unit, kHTailTime, naux) : 0, nullptr};
   R.b.item0 = (int64_t)R.a.tilesM * R.a.tilesN * R.a.ns;
   R.t.item0 = R.b.item0 + (int64_t)R.b.tilesM * R.b.tilesN * R.b.ns;
   R.items = R.t.item0 + (int64_t)R.t.tilesM * R.t.tilesN * R.t.ns;
@@ -1963,22 +1967,35 @@ static ReduceRegions reduce_regions(int64_t naux, int64_t nao, int64_t N, int un
 static int64_t region_part(const ReduceRegion& g) { return (int64_t)g.ns * (g.r1 - g.r0) * (g.c1 - g.c0); }
 // workgroups resident at once: three per CU, two with 128-row bands
 static int64_t half_resident(const HalfCols& h) { return h.big ? 512 : 768; }
-static int half_reduce_bound(int64_t nao, int64_t N, int64_t naux) {
-  return (int)std::min<int64_t>(naux, 4 * cdiv(half_resident(half_cols(nao, N)), half_tiles(nao, N)));
+// A chain of sums of the 128-wide tiles has at most this many 16-deep slabs (as far as naux goes): the rounding error
+// grows with its length.  At 1200 x 4800 x 300, with 64 such chains, the product was 0.7 per cent faster.
+constexpr int64_t kReduceChain = 2048;
+static int64_t half_reduce_least(int64_t nao, int64_t naux) {
+  return std::max<int64_t>(1, std::min(naux, cdiv(naux * cdiv(nao, 16), kReduceChain)));
 }
-static int half_reduce_unit(int64_t naux, int64_t nao, int64_t N) {
+static int64_t half_reduce_bound(int64_t nao, int64_t N, int64_t naux) {
+  // a quarter past the least, to choose one that fills its last round
+  return std::min<int64_t>(naux, std::max(half_reduce_least(nao, naux) * 5 / 4,
+                                          4 * cdiv(half_resident(half_cols(nao, N)), half_tiles(nao, N))));
+}
+static int64_t half_reduce_unit(int64_t naux, int64_t nao, int64_t N) {
   const HalfCols h = half_cols(nao, N);
   const int64_t res = half_resident(h);
   const double slab = h.big ? 4.4 : 3.5 * (h.nA == 0 ? half_tile_time(h.rest) : 1.0);   // us, all resident
-  const int most = half_reduce_bound(nao, N, naux);
-  int best = 1;
+  const int64_t most = half_reduce_bound(nao, N, naux);
+  int64_t best = 0;
   double best_us = 0.0;
-  for (int u = 1; u <= most; ++u) {
-    const int64_t items = reduce_regions(naux, nao, N, u).items, full = items / res, rem = items % res;
-    const double rounds = (double)full + (rem == 0 ? 0.0 : rem * 3 <= res ? 0.5 : rem * 3 <= 2 * res ? 0.7 : 1.0);
+  for (int64_t u = half_reduce_least(nao, naux); u <= most; u += 1 + u / 64) {
+    const ReduceRegions R = reduce_regions(naux, nao, N, u);
+    // in items of region a: the others' last 0.8 of its, or half and then fill the last round
+    const int64_t ia = (int64_t)R.a.tilesM * R.a.tilesN * R.a.ns, ib = R.t.item0 - R.b.item0, it = R.items - R.t.item0;
+    const double items = (double)ia + (h.rest == 96 ? 0.8 : 0.5) * (double)ib + 0.5 * (double)it;
+    const int64_t w = (int64_t)ceil(items), full = w / res, rem = w % res;
+    const double rounds = it > 0 || (ib > 0 && h.rest != 96) ? items / (double)res + 0.25
+                          : (double)full + (rem == 0 ? 0.0 : rem * 3 <= res ? 0.5 : rem * 3 <= 2 * res ? 0.7 : 1.0);
     const double us = (rounds + 0.2) * (double)(cdiv(naux, u) * cdiv(nao, 16) + 4) * slab +
                       (double)u * (double)(nao * N) * 16.0 / 4.0e6;
-    if (u == 1 || us < best_us) {
+    if (best == 0 || us < best_us) {
       best_us = us;
       best = u;
     }
@@ -1986,9 +2003,10 @@ static int half_reduce_unit(int64_t naux, int64_t nao, int64_t N) {
   return best;
 }
 
-// scaled_splits() rounds up to at most the 128-wide tiles' count, so no region has more
+// the partial sums grow with the unit and with naux
 int64_t half_reduce_part_bound(int64_t nao, int64_t N, int64_t naux) {
-  return (int64_t)half_reduce_bound(nao, N, naux) * nao * N;
+  const ReduceRegions R = reduce_regions(naux, nao, N, half_reduce_bound(nao, N, naux));
+  return region_part(R.a) + region_part(R.b) + region_part(R.t);
 }
 
 hipError_t launch_half_reduce(const double* B, int64_t naux, int64_t nao, const OpMap& Y, const OutMap& O,
@@ -2128,6 +2146,9 @@ hipError_t launch_gram(const OpMap& A, double* G, double* part, int64_t part_n, 
 
 int syrk_tile_for(int64_t n) { return n <= 640 ? CfgSyrk64::BM : CfgSyrk::BM; }
 
+static int scaled_splits(int unit, double w, int64_t kb_n) {
+  return (int)std::max<int64_t>(1, std::min<int64_t>(kb_n, (int64_t)((double)unit * w + 0.5)));
+}
 // Tiles of an n x n SYRK with `unit` splits of the 64 x 128 tiles over `slabs` slabs in kb_n blocks; a 64 x 64 tile
 // takes 0.58 and a 32 x 128 one 0.55 of their time (rates at CfgH128).
 static SyrkTiles syrk_tiles(int64_t n, int64_t kb_n, int64_t slabs, int unit) {

@@ -41,3 +41,20 @@ def test_k_chains(nao, naux, nocc, weighted, limit):
     assert lost.min().item() >= -8 * 128
     worst = lost.max().item()
     assert worst <= limit + 8 * 128, worst
+
+
+# 2048 slabs a chain of the 128-wide tiles, counted over slabs of 16 of each row of b^P, and none longer in the columns
+# and rows past them
+@pytest.mark.parametrize("nao,naux,nocc", [(600, 600, 150), (1200, 2400, 300), (450, 900, 300)])
+def test_adjoint_chains(nao, naux, nocc):
+    B = ones_with_big_column(naux, nao)
+    C = unit_columns(nao, nocc)
+    # S = gK + gK^T = 1, so dCocc_mc = sum_P b^P Y_P with Y_P = b^P C
+    gK = 0.5 * torch.eye(nao, dtype=torch.float64, device="cuda")
+    dC = dfmi.step_backward(B, nao, C, unit_columns(nao, 0), None, gK, None)[0]
+    scale = round(dC[1, 1].item() / (BIG * BIG))   # a whole factor of the cotangent
+    lost = BIG * BIG * scale - dC[1:, 1:] + scale * float(naux * nao - 1)
+    assert lost.min().item() >= -8 * 512 * scale
+    wide = lost[:nao // 128 * 128 - 1, :nocc // 128 * 128 - 1].max().item()
+    assert wide <= scale * (2048 * 16 + 8 * 512), wide
+    assert lost.max().item() <= wide + 16 * 512 * scale, (lost.max().item(), wide)
