@@ -58,3 +58,17 @@ def test_adjoint_chains(nao, naux, nocc):
     wide = lost[:nao // 128 * 128 - 1, :nocc // 128 * 128 - 1].max().item()
     assert wide <= scale * (2048 * 16 + 8 * 512), wide
     assert lost.max().item() <= wide + 16 * 512 * scale, (lost.max().item(), wide)
+
+
+def test_v_chain():
+    """v_0 = sum_m b_mm with 2^56 in the first row and 7 in one row of every other 64-row band: added to 2^56 one at a
+    time a 7 is lost.  With 128-row bands seven were; the partial sums that are kept round by 8 each."""
+    nao = 1024
+    B = torch.zeros((1, nao * (nao + 1) // 2), dtype=torch.float64, device="cuda")
+    m = torch.arange(0, nao, 64, device="cuda")
+    B[0, m * (m + 3) // 2] = 7.0
+    B[0, 0] = BIG * BIG
+    ones = torch.ones((nao, 1), dtype=torch.float64, device="cuda")
+    v = dfmi.step(B, nao, ones, unit_columns(nao, 0), unit_columns(nao, 1))["v"]
+    lost = BIG * BIG - v.item() + 7.0 * (len(m) - 1)
+    assert abs(lost) <= 7 * 7 + 8 * 3, lost
