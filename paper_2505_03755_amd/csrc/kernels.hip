@@ -2503,7 +2503,8 @@ hipError_t launch_subst_row(const double* L, int64_t ldl, int64_t k, const doubl
   Bm.kb_n = k;
   Bm.s_kb = kCholNB * npair;
   const int64_t nblk = cdiv(npair, CfgSub::BN);
-  if (nblk > 0x7fffffffLL || !offsets_fit(A) || !offsets_fit(Bm)) return hipErrorInvalidValue;
+  // without earlier blocks nothing is read through A and Bm; E and B take 64-bit offsets
+  if (nblk > 0x7fffffffLL || (k > 0 && (!offsets_fit(A) || !offsets_fit(Bm)))) return hipErrorInvalidValue;
   subst_row_kernel<<<(unsigned)nblk, CfgSub::NT, 0, s>>>(A, Bm, k * (kCholNB / CfgSub::BK), E, Linv, kb, npair,
                                                          B + k * kCholNB * npair);
   return hipGetLastError();

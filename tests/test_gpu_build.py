@@ -149,3 +149,17 @@ def test_first_bad_pivot_in_each_block(pivot):
         metric[naux - 1, naux - 1] = 0.0
     _, _, info = dfmi.build_cholesky(dev(metric), dev(np.ones((naux, 1))), 1, check=False)
     assert int(info.item()) == pivot + 1
+
+
+def test_build_of_few_rows_over_many_pairs():
+    """Up to 127 auxiliary rows the substitution has no earlier block rows, so N_ao is bounded by 2^25 pairs alone, not by
+    the 32-bit offsets of 128 + 15 earlier rows (N_ao 7749)."""
+    nao, naux = 7800, 3
+    npair = nao * (nao + 1) // 2
+    metric = synth.coulomb_metric(naux, 10.0, seed=8)
+    E = torch.randn((naux, npair), dtype=torch.float64, device="cuda")
+    ref = torch.linalg.solve_triangular(torch.linalg.cholesky(dev(metric)), E, upper=False)
+    L, B, info = dfmi.build_cholesky(dev(metric), E, nao, in_place=True)
+    assert int(info.item()) == 0
+    assert ((B - ref).norm() / ref.norm()).item() <= TOL
+    dfmi.context().release_workspace()
