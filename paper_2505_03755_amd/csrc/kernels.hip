@@ -1376,7 +1376,8 @@ __global__ void __launch_bounds__(256) pack_lower_kernel(const double* __restric
 // per wave, no barrier between: X_ij = -Linv_ii sum_{k=j}^{i-1} L_ik X_kj, kept in the upper blocks of S; the sum
 // leaves the matrix cores in the very layout in which the product with Linv_ii reads its right
 // operand.  One workgroup, so bound by latency: a column at a time (128 columns, three barriers each, and a
-// serial substitution for the inverse) took 331 us, so 81.  Outputs: the factor back to
+// serial substitution for the inverse) took 331 us, so 81.  Only the blocks that hold rows of A are worked on: all
+// eight of them for the 5 rows of an N_ao 20 build took the whole call from 24 to 80 us, 20 now.  Outputs: the factor back to
 // A (lower, the block's strictly upper part zeroed) and L^-1 to Linv [kCholNB][kCholNB] (lower,
 // upper zeroed).  info: the first block (first != 0) writes 0; a block that meets a pivot that
 // is not positive writes k0 + j + 1 unless info already holds an earlier one.  After such a
@@ -1395,13 +1396,14 @@ __global__ void __launch_bounds__(256) chol_block_kernel(double* __restrict__ A,
   __shared__ double D[NB][16][17];   // inverses of the diagonal blocks
   __shared__ int bad;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6, lr = lane & 15, lk = lane >> 4;
-  for (int idx = t; idx < N * N; idx += 256) {
+  const int nb = (kb + 15) / 16;   // blocks with rows of A
+  for (int idx = t; idx < nb * 16 * N; idx += 256) {
     const int i = idx / N, j = idx % N;
     S[i][j] = i < kb ? (j <= i ? A[i * lda + j] : 0.0) : (i == j ? 1.0 : 0.0);
   }
   if (t == 0) bad = -1;
   __syncthreads();
-  for (int p = 0; p < NB; ++p) {
+  for (int p = 0; p < nb; ++p) {
     const int o = p * 16;
     if (wave == 0) {
       // lane l < 16 holds row l of the block (the other lanes copies, never stored)
@@ -1439,7 +1441,7 @@ __global__ void __launch_bounds__(256) chol_block_kernel(double* __restrict__ A,
     }
     __syncthreads();
     // the blocks below: L_rp = A_rp Linv_pp^T
-    for (int r = p + 1 + wave; r < NB; r += 4) {
+    for (int r = p + 1 + wave; r < nb; r += 4) {
       d4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int kk = 0; kk < 16; kk += 4)
@@ -1449,7 +1451,7 @@ __global__ void __launch_bounds__(256) chol_block_kernel(double* __restrict__ A,
     }
     __syncthreads();
     // trailing blocks (r >= c > p): A_rc -= L_rp L_cp^T
-    const int m = NB - 1 - p;
+    const int m = nb - 1 - p;
     for (int w = wave; w < m * (m + 1) / 2; w += 4) {
       int r = 0;
       while ((r + 1) * (r + 2) / 2 <= w) ++r;
@@ -1469,7 +1471,7 @@ __global__ void __launch_bounds__(256) chol_block_kernel(double* __restrict__ A,
   // factor does not use and no other wave reads
   for (int h = 0; h < 2; ++h) {
     const int j = h == 0 ? wave : NB - 1 - wave;
-    for (int i = j + 1; i < NB; ++i) {
+    for (int i = j + 1; i < nb; ++i) {
       d4 acc = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
       for (int kk = 0; kk < 16; kk += 4)
@@ -1520,6 +1522,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) s
   const int64_t n0 = (int64_t)xcd_remap(blockIdx.x, gridDim.x) * C::BN;
   d4 acc[C::TM][C::TN];
   zero_acc<C>(acc);
+  const int nb = (kb + 15) / 16;   // 16-row blocks to form
   if (nslab > 0) {
     PairSrc<C, true, false, false, false> src;
     src.A = &A;
@@ -1548,8 +1551,9 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) s
     }
 #pragma unroll
   for (int h = 0; h < 2; ++h) {
+    if (4 * h >= nb) break;
     __syncthreads();   // the last reads of what is overwritten are done
-    for (int idx = t; idx < 64 * kCholNB; idx += 256) {
+    for (int idx = t; idx < min(64, 16 * nb - 64 * h) * kCholNB; idx += 256) {
       const int r = 64 * h + idx / kCholNB, k = idx % kCholNB;
       smem[(idx / kCholNB) * LS + k] = r < kb && k < kb ? Linv[r * kCholNB + k] : 0.0;
     }
@@ -1557,6 +1561,7 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) s
 #pragma unroll
     for (int i4 = 0; i4 < 4; ++i4) {
       const int i = 4 * h + i4;
+      if (i >= nb) break;
       d4 x[C::TN];
 #pragma unroll
       for (int j = 0; j < C::TN; ++j) x[j] = d4{0.0, 0.0, 0.0, 0.0};

@@ -163,3 +163,17 @@ def test_build_of_few_rows_over_many_pairs():
     assert int(info.item()) == 0
     assert ((B - ref).norm() / ref.norm()).item() <= TOL
     dfmi.context().release_workspace()
+
+
+@pytest.mark.parametrize("naux", [2, 15, 16, 17, 33, 64, 65, 96, 113, 128 + 1, 128 + 16, 256 + 70])
+def test_build_on_the_blocks_with_rows(naux):
+    """The last diagonal block and block row work on as many 16-row blocks as hold rows: one, two, the edge of the
+    first half of the inverse (64), all but one."""
+    nao = 11
+    metric = synth.coulomb_metric(naux, 1e4, seed=naux)
+    E = synth.cholesky_vectors(naux, nao, 10.0, seed=naux + 2)
+    L, B, info = dfmi.build_cholesky(dev(metric), dev(E), nao)
+    assert int(info.item()) == 0
+    assert rel(L, OB.metric_cholesky(metric)) <= TOL
+    assert rel(B, OB.cholesky_vectors(metric, E)) <= TOL
+    assert not torch.triu(L, 1).any()
