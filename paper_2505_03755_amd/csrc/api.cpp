@@ -411,19 +411,21 @@ static __device__ __align__(256) char scratch[kNoallocBytes];
 std::mutex g_scratch_mu;
 std::map<int, char*> g_scratch_addr;   // device -> address of `scratch` there
 
-// K split count of df_jk_noalloc's blocks of r auxiliary rows: at most 4, so that the K partials
-// leave room for X; non-decreasing in r.
-int noalloc_jk_splits(int64_t nao, int64_t r, int64_t ndm) {
-  return std::min(dfk::syrk_splits_bound(nao, r, ndm), 4);
+// The most K splits of df_jk_noalloc's blocks of r auxiliary rows: as many as an eighth of the scratch holds partials
+// for, so that they leave room for X, and at least four (four where K is not asked for); non-decreasing in r.  (Four in
+// every case left small bases on a dozen workgroups: 341 x 1365 x 85 4.93 ms, 1.62 now; 1100 x 600 x 275 21.2, 19.9.)
+int noalloc_jk_splits(int64_t nao, int64_t r, int64_t ndm, bool want_k) {
+  const int64_t room = want_k ? (int64_t)(kNoallocBytes / 8 / sizeof(double)) / (ndm * nao * nao) : 0;
+  return (int)std::min<int64_t>(dfk::syrk_splits_bound(nao, r, ndm), std::max<int64_t>(room, 4));
 }
 
 // Auxiliary rows per block of df_jk_noalloc (FP64): the most whose workspace fits the scratch.  The
 // workspace grows with the rows (the split count does not fall), so every block, the ragged last
 // one too, fits; 0 when one row does not fit.
-int64_t noalloc_jk_rows(int64_t naux, int64_t nao, int64_t ndm, int64_t nocc, bool weighted) {
+int64_t noalloc_jk_rows(int64_t naux, int64_t nao, int64_t ndm, int64_t nocc, bool weighted, bool want_k) {
   auto need = [&](int64_t r) {
     Plan pl;
-    plan_jk(pl, r, nao, ndm, nocc, weighted, 0, 0, noalloc_jk_splits(nao, r, ndm));
+    plan_jk(pl, r, nao, ndm, nocc, weighted, 0, 0, noalloc_jk_splits(nao, r, ndm, want_k));
     return pl.total;
   };
   if (need(1) > kNoallocBytes) return 0;
@@ -1590,7 +1592,7 @@ df_status df_jk_noalloc(df_ctx* ctx, const double* B, int64_t naux, int64_t nao,
   const bool work = nocc > 0 && (J || K || v);
   int64_t rows = 0;
   if (work) {
-    rows = noalloc_jk_rows(naux, nao, ndm, nocc, w != nullptr);
+    rows = noalloc_jk_rows(naux, nao, ndm, nocc, w != nullptr, K != nullptr);
     if (rows == 0)
       return fail(c, DF_ERR_WORKSPACE, "df_jk_noalloc: one auxiliary row needs more than the " +
                                            std::to_string(kNoallocBytes >> 20) + " MiB static scratch");
@@ -1606,7 +1608,9 @@ df_status df_jk_noalloc(df_ctx* ctx, const double* B, int64_t naux, int64_t nao,
   const bool timing = c->timing;
   c->timing = false;
   const int64_t npair = nao * (nao + 1) / 2;
-  const int nsplit = noalloc_jk_splits(nao, rows, ndm);
+  // the count of least time among those there is room for, four at least
+  const int room = noalloc_jk_splits(nao, rows, ndm, K != nullptr);
+  const int nsplit = K ? std::min(room, std::max(4, dfk::syrk_splits(nao, rows, nocc, ndm))) : room;
   df_status st = DF_OK;
   for (int64_t p0 = 0; p0 < naux && st == DF_OK; p0 += rows) {
     const int64_t r = std::min(rows, naux - p0);

@@ -91,3 +91,9 @@ def test_rejects_what_does_not_fit():
         ctx = dfmi.context()
         ctx.check(ctx._lib.df_jk_noalloc(ctx.handle, dfmi._ptr(B), 1, nao, 1, dfmi._ptr(C), 1, None,
                                          None, None, None, dfmi.DF_PREC_SPLIT))
+
+
+# blocks with as many K splits as an eighth of the scratch holds partials for (130, 52, four) or fewer, ragged last blocks
+@pytest.mark.parametrize("nao,naux,ndm,nocc", [(126, 1700, 1, 100), (200, 800, 1, 100), (500, 340, 2, 150)])
+def test_k_splits_of_the_blocks(nao, naux, ndm, nocc):
+    run_pair(nao, naux, ndm, nocc, seed=nao)
