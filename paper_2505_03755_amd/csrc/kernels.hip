@@ -1634,7 +1634,10 @@ bool offsets_fit(const OpMap& o) {
 // bound by latency, not by its padding).  Bands have 64 rows, 128 (`big`) where the packed b^P does not
 // fit the 4 MB L2 of an XCD: every band reads all of b^P's columns, from the last-level cache then
 // (P-summed product at 1200 x 4800 x 300: 79 ms with 64-row bands, 75 with 128; at N_ao = 1000 the
-// 64-row bands still win, 17.9 ms against 18.1).
+// 64-row bands still win, 17.9 ms against 18.1), but not beside a rest of at most 32 columns, which 128 rows
+// have no tile for: on one of 48 the half transform ran 4.45 ms at 1030 x 600 x 140 instead of 3.77, 5.79 instead of 5.29
+// at 1200 x 600 x 150.  64 or 96 columns alone take 128 rows too from N_ao = 449 on, where that pads no more rows
+// (64 x 64 and 128 x 64 tiles: 677 and 651 us at 512 x 1024, 1361 and 1323 at 720 x 1000, 575 and 576 at 384 x 1500).
 struct HalfCols {
   int64_t nA;
   int rest, tail;
@@ -1646,8 +1649,8 @@ static HalfCols half_cols(int64_t nao, int64_t ncol) {
   const int64_t rem = ncol % 128;
   if (rem > 96) ++h.nA;
   else if (rem > 0) h.rest = rem <= 16 ? 16 : rem <= 32 ? 32 : rem <= 48 ? 48 : rem <= 64 ? 64 : 96;
-  h.big = h.nA > 0 && nao * (nao + 1) / 2 > (int64_t(4) << 20) / 8;
-  if (h.big && h.rest > 0 && h.rest < 48) h.rest = 48;
+  if (h.nA > 0) h.big = nao * (nao + 1) / 2 > (int64_t(4) << 20) / 8 && (h.rest == 0 || h.rest >= 48);
+  else h.big = h.rest >= 64 && nao > 448 && cdiv(nao, CfgH128::BM) % 2 == 0;
   const int64_t rows = nao % h.bm();
   if (h.nA > 0 && rows > 0 && rows <= h.bm() / 2) h.tail = (int)rows;
   return h;
@@ -1670,6 +1673,10 @@ template <class F>
 static auto half_dispatch(const HalfCols& h, F&& f) {
   typedef CfgH128 A;
   typedef CfgHTail T;
+  if (h.big && h.nA == 0) {
+    if (h.rest == 64) return f(CfgQ64{}, CfgQ64{}, CfgQ64{});
+    return f(CfgQ96{}, CfgQ96{}, CfgQ96{});
+  }
   if (h.big) switch (h.rest) {
       case 0: return f(CfgQ128{}, CfgQ128{}, CfgQTail{});
       case 48: return f(CfgQ128{}, CfgQ48{}, CfgQTail{});
@@ -1995,7 +2002,7 @@ static int64_t half_reduce_bound(int64_t nao, int64_t N, int64_t naux) {
 static int64_t half_reduce_unit(int64_t naux, int64_t nao, int64_t N) {
   const HalfCols h = half_cols(nao, N);
   const int64_t res = half_resident(h);
-  const double slab = h.big ? 4.4 : 3.5 * (h.nA == 0 ? half_tile_time(h.rest) : 1.0);   // us, all resident
+  const double slab = (h.big ? 4.4 : 3.5) * (h.nA == 0 ? half_tile_time(h.rest) : 1.0);   // us, all resident
   const int64_t most = half_reduce_bound(nao, N, naux);
   int64_t best = 0;
   double best_us = 0.0;
@@ -2005,8 +2012,9 @@ static int64_t half_reduce_unit(int64_t naux, int64_t nao, int64_t N) {
     const int64_t ia = (int64_t)R.a.tilesM * R.a.tilesN * R.a.ns, ib = R.t.item0 - R.b.item0, it = R.items - R.t.item0;
     const double items = (double)ia + (h.rest == 96 ? 0.8 : 0.5) * (double)ib + 0.5 * (double)it;
     const int64_t w = (int64_t)ceil(items), full = w / res, rem = w % res;
+    const double last = h.big ? (rem * 2 <= res ? 0.6 : 1.0) : (rem * 3 <= res ? 0.5 : rem * 3 <= 2 * res ? 0.7 : 1.0);
     const double rounds = it > 0 || (ib > 0 && h.rest != 96) ? items / (double)res + 0.25
-                          : (double)full + (rem == 0 ? 0.0 : rem * 3 <= res ? 0.5 : rem * 3 <= 2 * res ? 0.7 : 1.0);
+                                                             : (double)full + (rem == 0 ? 0.0 : last);
     const double us = (rounds + 0.2) * (double)(cdiv(naux, u) * cdiv(nao, 16) + 4) * slab +
                       (double)u * (double)(nao * N) * 16.0 / 4.0e6;
     if (best == 0 || us < best_us) {

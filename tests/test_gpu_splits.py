@@ -175,6 +175,16 @@ def test_half_transform_tiles(nao, naux, ncol):
     close(dCo, sum(b[p] @ Y[p] for p in range(naux)), "dCocc")
 
 
+# 128-row bands of one 64- or 96-column tile (an even number of 64-row bands from nao 449 on, the last row band partial), the
+# same columns where the 64-row bands are odd; 64-row bands at 1024 and more for rests of 16 and 32, with and
+# without tail rows; bands of four column tiles, whose short one turns (385 ... 480 columns)
+@pytest.mark.parametrize("nao,naux,ncol", [(449, 2, 50), (512, 2, 64), (500, 3, 65), (512, 2, 96), (513, 2, 64), (448, 2, 96),
+                                           (1024, 2, 129), (1025, 2, 144), (1056, 2, 160), (1090, 2, 272),
+                                           (70, 3, 400), (129, 2, 432), (64, 5, 480)])
+def test_half_transform_bands(nao, naux, ncol):
+    test_half_transform_tiles(nao, naux, ncol)
+
+
 # K's triangle: one diagonal tile; with 1, 13 and 32 rows of tail; two, three and four bands (the last one partial);
 # contractions of whole slabs, with a remainder (flat), and shorter than one; weighted and not
 @pytest.mark.parametrize("nao,nocc", [(1, 1), (64, 16), (65, 20), (77, 19), (96, 5), (97, 32), (128, 17), (160, 33), (191, 16), (200, 21), (256, 3), (290, 40)])
