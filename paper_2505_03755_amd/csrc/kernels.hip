@@ -1130,9 +1130,12 @@ __global__ void __launch_bounds__(256) jvec_kernel(const double* __restrict__ X,
 // read as runs of 8 KB; v is staged through LDS in blocks of 256 P.  The pairs alone give 704
 // workgroups at N_ao = 1200 but 8 at 120, so the P range is split over grid y too (launch_coulomb):
 // partial sums go to part [split][z][npair] and coulomb_reduce_kernel adds them in split order.
+// Where the pairs alone fill the card (!DEEP) a thread reads one row at a time, four loads in flight: with sixteen, or with
+// the compiler's own choice, 1200 x 4800 took 4.67 ms instead of 4.38 (6.3 TB/s), 1400 x 2000 2.76 instead of 2.55.  Below that
+// sixteen are as good or better (1000 x 4000 2.92 -> 2.71 ms).
 constexpr int kCoulombZ = 4;
 constexpr int kCoulombPairs = 4;
-template <int NZ>
+template <int NZ, bool DEEP>
 __global__ void __launch_bounds__(256) coulomb_kernel(const double* __restrict__ B, int64_t naux, int64_t nao,
                                                       int64_t npair, const double* __restrict__ v, int64_t vstride,
                                                       double* __restrict__ J, int64_t jstride, int accumulate,
@@ -1157,20 +1160,37 @@ __global__ void __launch_bounds__(256) coulomb_kernel(const double* __restrict__
     __syncthreads();
     const double* Bp = B + P0 * npair;
     int q = 0;
-    for (; q + 4 <= cnt; q += 4) {   // 16 loads in flight per thread
-      double b[4][kCoulombPairs];
+    if constexpr (DEEP) {
+      for (; q + 4 <= cnt; q += 4) {   // 16 loads in flight per thread
+        double b[4][kCoulombPairs];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u)
 #pragma unroll
-        for (int r = 0; r < kCoulombPairs; ++r) b[u][r] = Bp[(int64_t)(q + u) * npair + pc[r]];
+          for (int r = 0; r < kCoulombPairs; ++r) b[u][r] = Bp[(int64_t)(q + u) * npair + pc[r]];
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int z = 0; z < NZ; ++z) {
+            const double w = vs[z][q + u];
+#pragma unroll
+            for (int r = 0; r < kCoulombPairs; ++r) acc[r][z] = fma(w, b[u][r], acc[r][z]);
+          }
+      }
+    } else {
+#pragma unroll 2
+      for (; q < cnt; ++q) {   // the fences keep the loads of later rows where they are
+        double b[kCoulombPairs];
+#pragma unroll
+        for (int r = 0; r < kCoulombPairs; ++r) b[r] = Bp[(int64_t)q * npair + pc[r]];
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int z = 0; z < NZ; ++z) {
-          const double w = vs[z][q + u];
+          const double w = vs[z][q];
 #pragma unroll
-          for (int r = 0; r < kCoulombPairs; ++r) acc[r][z] = fma(w, b[u][r], acc[r][z]);
+          for (int r = 0; r < kCoulombPairs; ++r) acc[r][z] = fma(w, b[r], acc[r][z]);
         }
+        __builtin_amdgcn_sched_barrier(0);
+      }
     }
     for (; q < cnt; ++q) {
 #pragma unroll
@@ -2412,9 +2432,10 @@ hipError_t launch_jvec(const double* X, int64_t naux, int64_t nao, int64_t ldx, 
 // each; with one split N_ao = 120 had 8 workgroups).  None where the pairs alone give 512 (at 704,
 // N_ao = 1200, two splits read B no faster).  Unsplit against split: step at 120 x 480 583 -> 415 us,
 // J and K at 77 x 310 260 -> 157 us, two densities at 455 x 1822 8.21 -> 7.31 ms.
+constexpr int64_t kCoulombFull = 512;
 static int coulomb_want(int64_t naux, int64_t nao) {
   const int64_t bx = cdiv(nao * (nao + 1) / 2, 256 * kCoulombPairs);
-  if (bx >= 512) return 1;
+  if (bx >= kCoulombFull) return 1;
   return (int)std::max<int64_t>(1, std::min<int64_t>({cdiv(1024, bx), naux / 4, 128}));
 }
 
@@ -2428,6 +2449,7 @@ hipError_t launch_coulomb(const double* B, int64_t naux, int64_t nao, const doub
   const int64_t npair = nao * (nao + 1) / 2;
   if (ldv == 0) ldv = naux;
   if (ldv < naux) return hipErrorInvalidValue;
+  const bool deep = cdiv(npair, 256 * kCoulombPairs) < kCoulombFull;
   for (int64_t z0 = 0; z0 < nz; z0 += kCoulombZ) {
     const int nzc = (int)(nz - z0 < kCoulombZ ? nz - z0 : kCoulombZ);
     const int64_t room = part ? part_n / (nzc * npair) : 0;
@@ -2436,11 +2458,16 @@ hipError_t launch_coulomb(const double* B, int64_t naux, int64_t nao, const doub
     const dim3 grid((unsigned)cdiv(npair, 256 * kCoulombPairs), (unsigned)ns);
     const double* vz = v + z0 * ldv;
     double* Jz = J + z0 * nao * nao;
+    auto go = [&](auto k) {
+      constexpr int NZ = decltype(k)::value;
+      if (deep) coulomb_kernel<NZ, true><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt);
+      else coulomb_kernel<NZ, false><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt);
+    };
     switch (nzc) {
-      case 1: coulomb_kernel<1><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt); break;
-      case 2: coulomb_kernel<2><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt); break;
-      case 3: coulomb_kernel<3><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt); break;
-      default: coulomb_kernel<4><<<grid, 256, 0, s>>>(B, naux, nao, npair, vz, ldv, Jz, nao * nao, accumulate, pt);
+      case 1: go(std::integral_constant<int, 1>{}); break;
+      case 2: go(std::integral_constant<int, 2>{}); break;
+      case 3: go(std::integral_constant<int, 3>{}); break;
+      default: go(std::integral_constant<int, 4>{});
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

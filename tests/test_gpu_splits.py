@@ -54,6 +54,22 @@ def test_jk_coulomb_splits(nao, naux, ndm, weighted):
     assert torch.equal(J, J.transpose(1, 2))
 
 
+# 512 workgroups of 1024 pairs from nao 1023 on: rows one at a time, no split; 256 rows of v a block
+@pytest.mark.parametrize("nao,naux,ndm", [(1023, 3, 1), (1024, 258, 2), (1022, 9, 1), (1050, 5, 5)])
+def test_coulomb_of_many_pairs(nao, naux, ndm):
+    B = torch.randn((naux, nao * (nao + 1) // 2), dtype=torch.float64, device="cuda")
+    C = torch.randn((ndm, nao, 1), dtype=torch.float64, device="cuda") / nao
+    J, _, v = dfmi.jk(B, nao, C, want_k=False)
+    out = {"J": torch.ones_like(J)}
+    dfmi.jk(B, nao, C, want_k=False, want_v=False, out=out, accumulate=True)
+    ref = v @ B
+    i, j = torch.tril_indices(nao, nao, device="cuda")
+    tol = TOL * ref.norm().item()
+    assert (J[:, i, j] - ref).norm().item() <= tol
+    assert torch.equal(J, J.transpose(1, 2))
+    assert (out["J"] - 1.0 - J).norm().item() <= 2 * tol
+
+
 @pytest.mark.parametrize("nao,naux", [(33, 40), (120, 480)])
 def test_adjoint_coulomb_under_scratch_limit(nao, naux):
     """The adjoint's Coulomb part takes its partial sums from the pieces a scratch limit leaves."""
