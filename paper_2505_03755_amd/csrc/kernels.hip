@@ -879,25 +879,31 @@ __device__ __forceinline__ void half_tile_at(const double* __restrict__ B, int n
   if constexpr (JV) {
     const int lr = lane & 15, lg = lane >> 4;
     double s = 0.0;
-    // rows past the end read the last one and columns past nv column 0, both dropped by a select: the loads
-    // are branch-free, so a column block's are in flight together
+    // rows past the end read the last one and columns past nv column 0, both dropped by a select: the loads are
+    // branch-free, so eight of a column block are in flight together.  (All sixteen of a 128-row tile, and the next
+    // block's moved up, spilled 38 registers: 84.5 ms at 1200 x 4800 x 340 instead of 83.8.)
+    constexpr int NQ = C::TM * 4, JB = NQ < 8 ? NQ : 8;
 #pragma unroll
     for (int j = 0; j < C::TN; ++j) {
       const int n = n0 + (wn * C::TN + j) * 16 + lr;
       const bool nok = n < jv->nv;
       const int nc = nok ? n : 0;
       const double wc = nok ? (jv->w ? jv->w[nc] : 1.0) : 0.0;
-      double cm[C::TM * 4];
-#pragma unroll
-      for (int q = 0; q < C::TM * 4; ++q) {
-        const int m = m0 + (wm * C::TM + q / 4) * 16 + 4 * (q % 4) + lg;
-        cm[q] = jv->C[(int64_t)(m < nao ? m : nao - 1) * jv->ldc + nc];
-      }
       double sj = 0.0;
 #pragma unroll
-      for (int q = 0; q < C::TM * 4; ++q) {
-        const int m = m0 + (wm * C::TM + q / 4) * 16 + 4 * (q % 4) + lg;
-        sj = m < nao ? fma(acc[q / 4][j][q % 4], cm[q], sj) : sj;
+      for (int h = 0; h < NQ; h += JB) {
+        double cm[JB];
+#pragma unroll
+        for (int e = 0; e < JB; ++e) {
+          const int q = h + e, m = m0 + (wm * C::TM + q / 4) * 16 + 4 * (q % 4) + lg;
+          cm[e] = jv->C[(int64_t)(m < nao ? m : nao - 1) * jv->ldc + nc];
+        }
+#pragma unroll
+        for (int e = 0; e < JB; ++e) {
+          const int q = h + e, m = m0 + (wm * C::TM + q / 4) * 16 + 4 * (q % 4) + lg;
+          sj = m < nao ? fma(acc[q / 4][j][q % 4], cm[e], sj) : sj;
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
       s = fma(sj, wc, s);
     }
