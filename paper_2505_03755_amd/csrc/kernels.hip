@@ -1824,19 +1824,23 @@ static hipError_t gemm_launch(const OpMap& A, const OpMap& Bm, const OutMap& O, 
   if (gemm_small(O.M, O.N, nz * nsplit, (double)gemm_slabs(A) / nsplit))
     return gemm_launch_cfg<CfgSmall>(A, Bm, O, nz, nsplit, part, s);
   const int64_t rem = O.M % CfgSq::BM, tn = cdiv(O.N, CfgSq::BN);
-  // at least 512 rows that the larger tiles pad by over 8% more than 64-row bands with a 32-row tail.  The bands read
-  // more per MFMA: 600 rows, 5% less padding, ran 2.05 ms on 128-row tiles and 2.17 so; with 210 rows, 14%, W
-  // of (pq|uv) at 600 x 2400 took 3.65 ms instead of 3.85, but the whole call 9.25 instead of 8.89 (the kernels after
-  // it ran slower: the card is at its power limit here)
+  // At least 512 rows that the larger tiles pad by over 8% more than 64-row bands with a 32-row tail.  Time of the
+  // product on bands against the larger tiles, second transform at 600 x 2400 (N 38400) / 480 x 1300 (N 16900), and of the whole adjoint
+  // with S X on that many rows: 513-576 rows (10 to 15% less padding) 0.92-0.98 / 0.99-1.00, 0.95-0.98; 769-800 (11%) 0.93 / 0.98-0.99,
+  // 0.95-0.98; 1025-1056 (8%) 0.97-0.99 / 0.79, 0.98-1.00.  The other side: 801-830 (7%) 0.93-0.97 / 0.93, 0.97-0.98; 577-608 (5%)
+  // 1.08-1.09 / 0.78, 1.01-1.03; 864 (4%) 1.00 / 1.07, 0.99; 1100 (3%) 1.04 / 0.92, 1.03; none, 1200 rows, 1.04 / 1.01, 1.00: a band
+  // reads more per MFMA, and its gain past the padding comes and goes with the last round.  Below 512 rows: 416 rows 0.77 / 1.00, 0.91;
+  // 341 1.00 / 1.01, 1.00; but with 210, W of (pq|uv) at 600 x 2400, 3.65 ms instead of 3.85, the whole call took 9.25 ms
+  // instead of 8.89, for a reason not found.
   const int64_t large = rem > 0 && rem <= CfgRowTail::BM && gemm_tall(O.M) ? O.M - rem + CfgRowTail::BM
                         : gemm_tall(O.M) ? cdiv(O.M, CfgTall::BM) * CfgTall::BM : cdiv(O.M, CfgSq::BM) * CfgSq::BM;
   const int64_t brem = O.M % CfgBand::BM, tail = brem > 0 && brem <= CfgBandTail::BM ? 1 : 0;
   const int64_t nband = tail ? O.M / CfgBand::BM : cdiv(O.M, CfgBand::BM);
-  if (O.M >= 512 && (nband * CfgBand::BM + tail * CfgBandTail::BM) * 108 < large * 100 && (part || (O.alpha == 1.0 && !O.accumulate)) &&
+  const bool ak = A.s_kc == 1, bk = Bm.s_kc == 1;
+  if (O.M >= 512 && (nband * CfgBand::BM + tail * CfgBandTail::BM) * 108 < large * 100 && (ak || !bk) && (part || (O.alpha == 1.0 && !O.accumulate)) &&
       (nband + tail) * tn <= 0x7fffffffLL && tn > 0 && nz > 0 && nz <= 65535 && nsplit >= 1 && nsplit <= 65535 &&
       offsets_fit(A) && offsets_fit(Bm) && A.kc_n == Bm.kc_n && A.kb_n == Bm.kb_n) {
     const dim3 grid((unsigned)((nband + tail) * tn), (unsigned)nsplit, (unsigned)nz);
-    const bool ak = A.s_kc == 1, bk = Bm.s_kc == 1;
     auto go = [&](auto k, auto l, auto cl) {
       gemm_band_kernel<decltype(k)::value, decltype(l)::value, decltype(cl)::value>
           <<<grid, CfgBand::NT, 0, s>>>(A, Bm, O, nband, nband + tail, tn, part);
@@ -1844,8 +1848,7 @@ static hipError_t gemm_launch(const OpMap& A, const OpMap& Bm, const OutMap& O, 
     auto pick = [&](auto cl) {
       if (ak && bk) go(std::true_type{}, std::true_type{}, cl);
       else if (ak) go(std::true_type{}, std::false_type{}, cl);
-      else if (bk) go(std::false_type{}, std::true_type{}, cl);
-      else go(std::false_type{}, std::false_type{}, cl);
+      else go(std::false_type{}, std::false_type{}, cl);   // no caller has k contiguous in B alone
     };
     if (A.kc_n % 16 != 0) pick(std::true_type{});
     else pick(std::false_type{});
@@ -1856,7 +1859,6 @@ static hipError_t gemm_launch(const OpMap& A, const OpMap& Bm, const OutMap& O, 
       offsets_fit(Bm) && A.kc_n == Bm.kc_n && A.kb_n == Bm.kb_n) {
     const int64_t nb = O.M / CfgSq::BM;
     const dim3 grid((unsigned)((nb + 1) * tn));
-    const bool ak = A.s_kc == 1, bk = Bm.s_kc == 1;
     if (ak && bk) gemm_tail_kernel<true, true><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nb, tn);
     else if (ak) gemm_tail_kernel<true, false><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nb, tn);
     else if (bk) gemm_tail_kernel<false, true><<<grid, CfgSq::NT, 0, s>>>(A, Bm, O, nb, tn);

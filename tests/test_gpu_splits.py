@@ -238,3 +238,48 @@ def test_adjoint_product_on_bands(nao):
         b = O.unpack(B[P:P + 1], nao)[0]
         ref += b @ ((gK + gK.T) @ (b @ Co))
     close(dCo, ref, "dCocc")
+
+
+# the products that take 64-row bands, each with a contraction in whole slabs and with a remainder, with and without the
+# 32-row tail: S X (above; whole slabs here), the second transform with its columns in blocks (np + nac rows) ...
+@pytest.mark.parametrize("nao", [528, 576, 800])
+def test_adjoint_product_on_bands_whole_slabs(nao):
+    test_adjoint_product_on_bands(nao)
+
+
+@pytest.mark.parametrize("nao,np_", [(40, 514), (48, 514), (48, 560), (41, 784)])
+def test_second_transform_on_bands(nao, np_):
+    naux, nac = 800, 16
+    rng = np.random.default_rng(nao + np_)
+    B = rng.standard_normal((naux, O.npair(nao)))
+    Cp, Ca = rng.standard_normal((nao, np_)) / nao, rng.standard_normal((nao, nac)) / nao
+    close(dfmi.papa(dev(B), nao, dev(Cp), dev(Ca)), O.papa(B, nao, Cp, Ca), "papa")
+
+
+# ... batched over P ...
+@pytest.mark.parametrize("nao,n2", [(50, 530), (48, 530), (48, 576), (35, 800)])
+def test_batched_second_transform_on_bands(nao, n2):
+    naux, ncol = 100, 100
+    rng = np.random.default_rng(nao + n2)
+    B = rng.standard_normal((naux, O.npair(nao)))
+    C, C2 = rng.standard_normal((nao, ncol)) / nao, rng.standard_normal((nao, n2)) / nao
+    X, Y = dfmi.half_transform(dev(B), nao, dev(C), C2=dev(C2))
+    ref = O.unpack(B, nao) @ C
+    close(X, ref, "X")
+    close(Y, C2.T @ ref, "Y")
+
+
+# ... and v of over 512 densities from packed B, both operands along k (210 pairs: a remainder; 496: whole slabs, split)
+@pytest.mark.parametrize("nao,ndm", [(20, 520), (31, 570)])
+def test_j_vectors_on_bands(nao, ndm):
+    naux, nocc, nac = 6400, 1, 1
+    g = torch.Generator(device="cuda").manual_seed(nao)
+    B = torch.randn((naux, O.npair(nao)), dtype=torch.float64, device="cuda", generator=g)
+    C = torch.randn((ndm, nao, nocc), dtype=torch.float64, device="cuda", generator=g) / nao
+    Ca = torch.randn((nao, nac), dtype=torch.float64, device="cuda", generator=g) / nao
+    o = dfmi.batched_step([{"B": B, "nao": nao, "Cocc": C, "Cact": Ca, "Cp": Ca}])[0]
+    i, j = torch.tril_indices(nao, nao, device="cuda")
+    D = C @ C.transpose(1, 2)
+    w = torch.where(i == j, D[:, i, j], D[:, i, j] + D[:, j, i])
+    ref = (w @ B.T) @ B
+    assert ((o["J"][:, i, j] - ref).norm() / ref.norm()).item() <= TOL
