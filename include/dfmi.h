@@ -431,12 +431,14 @@ df_status df_batched_set_tuning(df_ctx* ctx, const df_problem* probs, int nprob,
  * The tuning table outlives the context in a file (JSON, format "dfmi-autotune/1"): one entry per
  * problem-group shape with its operation ("df_batched_step"), precision ("fp64"), the device's gfx
  * architecture ("gfx950"; empty for choices set with df_batched_set_tuning, which hold on any
- * device) and the chosen half-transform tile, K tile and K split target.
+ * device), the chosen half-transform tile, K tile and K split target, and a number for the kernels
+ * they were measured with.
  *   df_autotune_save writes the context's whole table to path (a temporary file renamed into
  *     place); DF_ERR_ARG if it cannot be written.
  *   df_autotune_load merges the entries of path into the table (file entries replace stored ones
- *     of the same architecture and shape; entries of other operations or precisions, or with a
- *     configuration outside the candidate lists, are skipped); DF_ERR_ARG if the file cannot be
+ *     of the same architecture and shape; entries of other operations or precisions, with a
+ *     configuration outside the candidate lists, or measured with other kernels, are skipped:
+ *     such shapes are tuned again); DF_ERR_ARG if the file cannot be
  *     read or is not in this format.  Entries of another architecture stay unused.
  * With the environment variable DFMI_AUTOTUNE_CACHE naming a file, df_create loads it when it
  * exists (a file in another format fails df_create), and every df_batched_step that tunes merges

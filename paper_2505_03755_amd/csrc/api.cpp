@@ -694,8 +694,13 @@ bool json_field(const std::string& obj, const char* name, std::string* str, long
   return end != obj.c_str() + p;
 }
 
+// The kernels that a measured choice holds for; raised when the tiles behind a candidate change (1, not written: 128 was
+// 128 x 128 tiles with 64 x 176 ones below, 96 and 48 had 128 rows; 2: 64-row bands).
+constexpr long long kTuneKernels = 2;
+
 // Entries of a tuning file (format dfmi-autotune/1) merged into the table; entries of other
-// operations, precisions or unknown configurations are skipped.  A missing file is an error.
+// operations, precisions or unknown configurations, and choices measured with other kernels, are skipped.  A
+// missing file is an error.
 bool tune_read(df_ctx* c, const std::string& path, std::string* err) {
   std::ifstream f(path);
   if (!f) {
@@ -716,13 +721,14 @@ bool tune_read(df_ctx* c, const std::string& path, std::string* err) {
     if (q == std::string::npos) break;
     const std::string obj = text.substr(p, q - p + 1);
     std::string op, prec, arch, shape;
-    long long h = 0, kt = 0, kr = 0;
+    long long h = 0, kt = 0, kr = 0, rev = 1;
     if (json_field(obj, "op", &op, nullptr) && op == "df_batched_step" && json_field(obj, "precision", &prec, nullptr) &&
         prec == "fp64" && json_field(obj, "arch", &arch, nullptr) && json_field(obj, "shape", &shape, nullptr) &&
         json_field(obj, "half_tile_n", nullptr, &h) && json_field(obj, "k_tile", nullptr, &kt) &&
         json_field(obj, "k_rounds", nullptr, &kr)) {
       const BatchedTune t{(int)h, (int)kt, (int)kr};
-      if (tune_valid(t)) c->tune[arch + "|" + shape] = t;
+      json_field(obj, "kernels", nullptr, &rev);
+      if (tune_valid(t) && (arch.empty() || rev == kTuneKernels)) c->tune[arch + "|" + shape] = t;
     }
     p = q;
   }
@@ -744,7 +750,8 @@ bool tune_write(const df_ctx* c, const std::string& path, std::string* err) {
       const size_t bar = e.first.find('|');
       f << (first ? "\n" : ",\n") << "    {\"op\": \"df_batched_step\", \"precision\": \"fp64\", \"arch\": \""
         << e.first.substr(0, bar) << "\", \"shape\": \"" << e.first.substr(bar + 1) << "\", \"half_tile_n\": "
-        << e.second.half_n << ", \"k_tile\": " << e.second.k_tile << ", \"k_rounds\": " << e.second.k_rounds << "}";
+        << e.second.half_n << ", \"k_tile\": " << e.second.k_tile << ", \"k_rounds\": " << e.second.k_rounds
+        << ", \"kernels\": " << kTuneKernels << "}";
       first = false;
     }
     f << "\n  ]\n}\n";

@@ -533,3 +533,35 @@ def test_autotune_file_round_trip(L, tmp_path, monkeypatch):
     assert L.df_autotune_save(c, str(tmp_path / "no" / "dir.json").encode()) == dfmi.DF_ERR_ARG
     for h in (a, b, c, d):
         L.df_destroy(h)
+
+
+def test_autotune_file_of_other_kernels(L, tmp_path, monkeypatch):
+    """A choice measured with other kernels (an older file has no number for them) is not taken over; one set by hand is."""
+    import json
+    monkeypatch.delenv("DFMI_AUTOTUNE_CACHE", raising=False)
+    arr = (dfmi.Problem * 1)()
+    arr[0] = dfmi.Problem(1 << 30, 10, 7, 2, 2 << 30, 3, 3 << 30, 2, 4 << 30, 7, 5 << 30, 6 << 30, None, None)
+
+    def new_ctx():
+        h = ctypes.c_void_p()
+        assert L.df_create(ctypes.byref(h), 0, None) == dfmi.DF_OK
+        return h
+
+    a, b = new_ctx(), new_ctx()
+    path = str(tmp_path / "tune.json")
+    assert L.df_batched_set_tuning(a, arr, 1, 48, 128, 64) == dfmi.DF_OK
+    assert L.df_autotune_save(a, path.encode()) == dfmi.DF_OK
+    doc = json.load(open(path))
+    (hand,) = doc["entries"]
+    now = hand["kernels"]
+    old = {k: v for k, v in hand.items() if k != "kernels"}
+    measured = [dict(hand, arch="gfx950"), dict(old, arch="gfx950", shape="1;"), dict(hand, arch="gfx950", shape="2;", kernels=now - 1),
+                dict(hand, arch="gfx950", shape="3;", kernels=now + 1)]
+    doc["entries"] = [dict(old, shape="4;")] + measured
+    json.dump(doc, open(path, "w"))
+    assert L.df_autotune_load(b, path.encode()) == dfmi.DF_OK
+    assert L.df_autotune_save(b, path.encode()) == dfmi.DF_OK
+    got = {(e["arch"], e["shape"]) for e in json.load(open(path))["entries"]}
+    assert got == {("", "4;"), ("gfx950", hand["shape"])}
+    for h in (a, b):
+        L.df_destroy(h)
