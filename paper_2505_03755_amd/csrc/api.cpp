@@ -117,6 +117,7 @@ struct Plan {
 };
 
 // Offsets of the workspace pieces of each operation.
+
 // The active-space contractions (pu|vw) and (uv|wx): the operand [Cp | Cact], b^P over its rows
 // [naux][np + nac][nac], the packed pairs of b^P_uv [naux][nuv], and partial sums over P of the
 // products of the rows (pu) and (uv) with the packed pairs.
@@ -175,9 +176,8 @@ PpaaPlan plan_ppaa(Plan& pl, int64_t naux, int64_t nao, int64_t nac, int64_t nq)
   return p;
 }
 
-// Workspace of df_build_cholesky: the inverted diagonal blocks of L and a panel of the factorisation.  The
-// size keeps one block row of B besides, as it always had: the substitution no longer needs it, but
-// callers may count on the size.
+// Workspace of df_build_cholesky: the inverted diagonal blocks of L and a panel of the factorisation.  The size
+// holds one block row of B besides, which no kernel uses any more: the ABI's test asks for it.
 struct BuildPlan {
   size_t linv, panel;
   int64_t nblk;
@@ -929,7 +929,6 @@ size_t dbytes(int64_t n) { return (size_t)std::max<int64_t>(n, 0) * sizeof(doubl
 
 // ---- building blocks on the device ----
 
-// T_P = b^P C (ncol columns of C, row stride ldc), written through `out` with z = P
 // One block of columns, or two side by side.
 dfk::ColBlocks cols(const double* a, int64_t na, const double* b = nullptr, int64_t nb = 0) {
   return dfk::ColBlocks{a, na, nullptr, 0, 0, b, nb};
@@ -947,7 +946,7 @@ df_status pad_operand_plain(df_ctx* c, double* cc, int64_t nao, const dfk::ColBl
   return DF_OK;
 }
 
-// half transform against a padded operand from pad_operand
+// T_P = b^P C against a padded operand from pad_operand (ncol columns), written through `out` with z = P
 df_status run_half(df_ctx* c, const double* B, int64_t naux, int64_t nao, const double* cpad, int64_t ncol,
                    const dfk::OutMap& out) {
   DF_LAUNCH(DF_KERNEL_HALF_TRANSFORM, dfk::launch_half_transform(B, naux, nao, cpad, ncol, ncol, out, c->stream),
