@@ -42,8 +42,8 @@ struct Cfg {
   static_assert((BM * BK) % NT == 0 && (BN * BK) % NT == 0, "tile must split evenly over threads");
 };
 
-// Every MFMA kernel is sized for two waves per SIMD (at most 256 registers per lane, two
-// workgroups' LDS per CU), so one wave's barrier and LDS latency hide behind the other's MFMAs.
+// Every MFMA kernel is compiled for at least two waves per SIMD (256 registers per lane, two workgroups' LDS per
+// CU), so one wave's barrier and LDS latency hide behind the other's MFMAs; smaller tiles for three or four.
 // generic products and the K SYRK: 128 x 128 tiles, 2 x 2 waves of 64 x 64
 typedef Cfg<2, 2, 4, 4> CfgSq;
 // tall products (M >= 256): 256 x 128 tiles, 4 x 2 waves of 64 x 64, one workgroup per CU; the
@@ -473,7 +473,8 @@ __device__ __forceinline__ void pair_ij(int64_t p, int64_t* i, int64_t* j) {
 // Gram matrix  G(m, n) = sum_k A(m, k) A(n, k): the tiles on and below the diagonal only (tile pair I >= J
 // of the triangle), lanes along the rows of A.  Without a split a tile is stored to G and, mirrored,
 // to the transposed place (accumulate adds to both); with one the partial sums go to part [split][M][M],
-// lower tiles only, for syrk_reduce.  Bound by the matrix cores; half the MFMAs of the full product.
+// lower tiles only, for syrk_reduce.  Half the MFMAs of the full product; bound by the matrix cores and its last round
+// (6000 rows over 2000: 1128 workgroups, 2.2 rounds, busy 0.67).
 template <class C, bool CLAMP>
 __global__ void __launch_bounds__(C::NT) __attribute__((amdgpu_waves_per_eu(2))) gram_kernel(OpMap A, double* G, int64_t npairs, int accumulate, double* part) {
   static_assert(C::BM == C::BN, "square tiles");
@@ -652,7 +653,7 @@ __device__ __forceinline__ void syrk_run(const OpMap& A, const OpMap& Bw, int64_
 // T where the items are long: the chain of sums of a D item would be 1.7 times an A item's, and the diagonal is
 // the largest part of K.  (Relative error of K at 1200 x 4800 x 300 1.6e-15 so, 8.3e-16 with 37 equal chains,
 // 7.7e-16 now; at 800 6.9e-16, 4.0e-16, 3.1e-16.)  Bound by the
-// matrix cores (0.7 busy) and the padding of the triangle.  Against square tiles of 64 (128 past n = 640): K at
+// matrix cores (busy 0.78 at 1200 x 4800 x 300, 0.69 at 600 x 2400 x 150) and the padding of the triangle.  Against square tiles of 64 (128 past n = 640): K at
 // 341 x 1365 x 85 0.41 -> 0.38 ms, 600 x 2400 x 150 3.30 -> 3.03, 700 x 1400 x 128 1.91 -> 1.52, 1200 x 1200 x 300
 // 10.5 -> 9.8.  128 x 128 tiles with 64-row tails: 2.98 at 600, 1.69 at 700.
 struct SyrkTiles {
@@ -1532,8 +1533,8 @@ __global__ void __launch_bounds__(256) chol_block_kernel(double* __restrict__ A,
 // workgroup.  Waves side by side (1 x 4), so that a wave holds all kb <= 128 rows of its 32 columns of
 // T = E_k - sum: the accumulators then have the layout in which the product with Linv_k reads
 // its right operand, and T never leaves the registers.  Linv_k goes through LDS in two halves
-// of 64 rows; its zero upper part is skipped.  Bound by the matrix cores (49 TF/s; 1409 workgroups a block row
-// at 2400 x 180300 fill 2.75 rounds).  As a copy of E_k, a product that subtracts from it and a product with
+// of 64 rows; its zero upper part is skipped.  49 TF/s at 2400 x 180300, matrix cores busy 0.62: the waves wait a third
+// of their cycles, and 1409 workgroups a block row fill 2.75 rounds.  As a copy of E_k, a product that subtracts from it and a product with
 // Linv_k the substitution took 25.7 ms there, so 22.0.
 typedef Cfg<1, 4, 8, 2> CfgSub;
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) subst_row_kernel(OpMap A, OpMap B, int64_t nslab, const double* E,

@@ -302,9 +302,9 @@ def test_fragment_workload_64_densities(frag64):
 
 
 def test_fragment_workload_64_densities_2d_tiles(frag64):
-    """The same batch with the half transforms on the 2-D tiling (tuning candidate 128: 128 x 128
-    tiles, each fragment's rows past its last whole 128-row band on 64 x 176 tiles where that pads
-    less), in a context of its own."""
+    """The same batch with the half transforms on tuning candidate 128 set by hand (64-row bands of 128-wide
+    tiles, the rest of the columns on a 64-wide one and the last rows on 32 x 128 tiles where they fit), in a
+    context of its own."""
     probs, dps, refs = frag64
     ctx = dfmi.Context(dps[0]["B"].device)
     dfmi.batched_set_tuning(dps, 128, 64, 16, ctx=ctx)

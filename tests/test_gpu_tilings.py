@@ -1,10 +1,10 @@
 """The tilings of the packed products against the FP64 oracle.
 
 The half transform X_P = b^P C (Eq. ao2mo_1) and the adjoint's sum_P b^P Y_P are tiled in pieces
-by their shape: 128 x 128 tiles on whole 128-row bands, a one-tile remainder of the columns on
-one of five 128-row tile shapes (both in one launch), the rows past the last whole band on
-64 x 176 tiles, or 64 x 176 / 128 x 96 / 128 x 48 tiles for the whole.  The shapes below take
-every combination of pieces; for each the half transform (plain and accumulated onto what the
+by their shape, in one launch: 64-row bands of 128-wide column tiles, the rest of the columns on one
+narrower tile, and up to 32 rows past the last band on 32 x 128 tiles; or one narrow tile per band.  The
+shapes below take several combinations of pieces (test_gpu_splits.py has the others, 128-row bands
+among them); for each the half transform (plain and accumulated onto what the
 output holds), the step's J-vector from the half transform's epilogue and J (Eqs. J_1, J_2), K,
 and the adjoint for random cotangents are compared with the oracle at the FP64 bar (1e-10
 normwise and max relative).  N_aux is small and odd so the P splits are ragged.
@@ -36,14 +36,12 @@ def close(gpu, ref, what, tol=TOL):
 
 
 # (nao, N_occ + N_ac columns) -> pieces of the half transform:
-#   (130, 150): 128 x 128 + 128 x 48 remainder, rows 128-129 on 64 x 176 tiles
-#   (130, 180): 128 x 128 + 128 x 64 remainder on all rows
-#   (130, 200): 128 x 128 + 128 x 96 remainder
-#   (130, 230): 128 x 128 + a second 128 x 128 column tile as the remainder
-#   (130, 340): 128 x 128 (two column tiles) + 128 x 96, rows 128-129 on 64 x 176 tiles
-#   (130, 100), (130, 70), (130, 64): one 128-row tile shape for the whole
-#   (200, 150): 128 x 128 + 128 x 48 on all 200 rows
-#   (130, 130): 128 x 48 tiles on one row of waves
+#   (130, 150), (200, 150): one 128-wide tile + a 32-wide one per band, 32 x 128 tiles on the last 2 and 8 rows
+#   (130, 180), (130, 200), (130, 130): the same with 64, 96 and 16 columns for the rest
+#   (130, 230): two 128-wide tiles, the second partial, and tail rows
+#   (130, 340): two 128-wide tiles + a 96-wide one, and tail rows
+#   (130, 100): one 128-wide tile, partial, and a tail row tile
+#   (130, 70), (130, 64): one 96- or 64-wide tile on three bands
 SHAPES = [(130, 150), (130, 180), (130, 200), (130, 230), (130, 340), (130, 100), (130, 70), (130, 64),
           (200, 150), (130, 130)]
 NAUX = 13
