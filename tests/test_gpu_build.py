@@ -177,3 +177,21 @@ def test_build_on_the_blocks_with_rows(naux):
     assert rel(L, OB.metric_cholesky(metric)) <= TOL
     assert rel(B, OB.cholesky_vectors(metric, E)) <= TOL
     assert not torch.triu(L, 1).any()
+
+
+@pytest.mark.parametrize("seed", [0, 1, 2, 3])
+def test_factor_after_an_ill_conditioned_block(seed):
+    """Within a diagonal block the rows below a factored 16-row block take its inverse and a correction by the residual, so the
+    factor is as backward stable as one by columns: |L L^T - M| <= (n + 1) u |L| |L|^T (Higham, theorem 10.3), twice that
+    here for the reciprocals, where the metric's condition is below 1 / (n u).  The first block of L has condition 2e4 to 7e5 (of
+    the metric 5e11 at most); its inverse alone leaves residuals of 360 u to 8300 u."""
+    n, u = 48, 2.0 ** -53
+    r = np.random.default_rng(seed)
+    T = np.tril(r.uniform(-1, 1, (n, n)), -1) + np.diag(r.uniform(1, 2, n))
+    T[:16, :16] = np.tril(r.uniform(-1, 1, (16, 16)), -1) * 2 + np.diag(np.full(16, 0.6))
+    M = T @ T.T
+    L = dfmi.build_cholesky(dev(M), torch.zeros((n, 1), dtype=torch.float64, device="cuda"), 1)[0].cpu().numpy()
+    Ll = L.astype(np.longdouble)
+    res = np.abs((Ll @ Ll.T - M.astype(np.longdouble)).astype(np.float64))
+    worst = (res / (np.abs(L) @ np.abs(L).T)).max() / u
+    assert worst <= 2 * (n + 1), worst
