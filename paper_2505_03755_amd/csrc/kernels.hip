@@ -1403,7 +1403,7 @@ __global__ void __launch_bounds__(256) pack_lower_kernel(const double* __restric
 // per wave, no barrier between: X_ij = -Linv_ii sum_{k=j}^{i-1} L_ik X_kj, kept in the upper blocks of S; the sum
 // leaves the matrix cores in the very layout in which the product with Linv_ii reads its right
 // operand.  One workgroup, so bound by latency: a column at a time (128 columns, three barriers each, and a
-// serial substitution for the inverse) took 331 us, so 84.  Only the blocks that hold rows of A are worked on: all
+// serial substitution for the inverse) took 331 us, so 83.  Only the blocks that hold rows of A are worked on: all
 // eight of them for the 5 rows of an N_ao 20 build took the whole call from 24 to 80 us, 20 now.  Outputs: the factor back to
 // A (lower, the block's strictly upper part zeroed) and L^-1 to Linv [kCholNB][kCholNB] (lower,
 // upper zeroed).  info: the first block (first != 0) writes 0; a block that meets a pivot that
